@@ -400,10 +400,22 @@ void plan_search(const sched_problem& p, uint64_t lo, uint64_t hi, uint32_t n_ta
   const uint64_t cap = std::max<uint64_t>(1, kMaxBlocks / n_tables);
   a.blocks_per_table = uint32_t(std::min<uint64_t>(a.items_per_table, cap));
   a.n_tables = n_tables;
+  a.n_blocks = a.blocks_per_table * n_tables;
   a.full_range = full ? 1u : 0u;
   a.sharing = uint32_t(p.sharing);
   a.prefix = prefix ? 1u : 0u;
   a.lds_levels = table_levels(p);
+}
+
+// The walk of plan a in a table's header, where the full-order kernel reads it.
+void write_walk(const SearchArgs& a, uint32_t* table) {
+  table[kHdrOuterLoLo] = uint32_t(a.outer_lo);
+  table[kHdrOuterLoHi] = uint32_t(a.outer_lo >> 32);
+  table[kHdrNOuterLo] = uint32_t(a.n_outer);
+  table[kHdrNOuterHi] = uint32_t(a.n_outer >> 32);
+  table[kHdrInnerDigits] = a.inner_digits;
+  table[kHdrInnerCount] = a.inner_count;
+  table[kHdrPrefix] = a.prefix;
 }
 
 // Write the enumeration order seq[0..n) into a table built by build_table.
@@ -424,6 +436,89 @@ void set_enumeration(const sched_problem& p, const Seq& seq, uint32_t* table) {
 
 void set_enumeration(const sched_problem& p, const std::vector<int32_t>& seq, uint32_t* table) {
   set_enumeration(p, seq.data(), int(seq.size()), table);
+}
+
+// A partial range [lo, hi) as parts of a full-order search.  A part of level k
+// is a run of aligned blocks of W_k mappings (W_k: the product of the radices
+// of the first k tools with a choice): the modes of those k tools are free in
+// it, so they can be enumerated deepest first with shared prefixes as in a
+// full search, and the tools above them count through the run.  The largest
+// level that has a whole block in [lo, hi) takes the middle; each smaller
+// level takes what it can of the two ends, down to kPartMin mappings, and
+// what is left at the ends is walked in index order, one mapping per lane.
+// Two parts a level: kMaxParts reaches ten levels below the middle, so an end
+// left over by that limit holds less than 3^-10 of the range.
+struct Part {
+  uint64_t lo, hi;
+  int level;  // k; 0: index order
+};
+constexpr uint64_t kPartMin = 19683;
+constexpr int kMaxParts = 24;
+
+// The tables of a launch over parts, and where they are staged: a stack buffer
+// (the entry point that allocates nothing searches this way too).
+constexpr size_t kStageWords = size_t(1) << 15;
+
+int split_range(const sched_problem& p, uint64_t lo, uint64_t hi, Part* out) {
+  const int P = int(p.enum_tools.size());
+  uint64_t w[kMaxTools + 1];
+  w[0] = 1;
+  for (int k = 0; k < P; ++k) w[k + 1] = w[k] * p.radix[p.enum_tools[k]];
+  int n = 0, k = P;
+  uint64_t left = 0, right = 0;  // the middle covers [left, right)
+  for (; k >= int(kSharedInner) && w[k] >= kPartMin; --k) {
+    const uint64_t a = lo / w[k] + (lo % w[k] != 0), b = hi / w[k];
+    if (a < b) {
+      left = a * w[k];
+      right = b * w[k];
+      break;
+    }
+  }
+  if (left >= right) return 0;
+  out[n++] = {left, right, k};
+  for (--k; k >= int(kSharedInner) && w[k] >= kPartMin; --k) {
+    const uint64_t a = (lo / w[k] + (lo % w[k] != 0)) * w[k], b = hi / w[k] * w[k];
+    if (n + 4 > kMaxParts) break;
+    if (a < left) {
+      out[n++] = {a, left, k};
+      left = a;
+    }
+    if (b > right) {
+      out[n++] = {right, b, k};
+      right = b;
+    }
+  }
+  if (lo < left) out[n++] = {lo, left, 0};
+  if (right < hi) out[n++] = {right, hi, 0};
+  return n;
+}
+
+// Whether a partial range is searched in parts: the kernel has shared
+// prefixes for the problem whatever its inner tools' labels are, and the
+// range has lanes enough left to fill the GPU with kSharedInner inner digits
+// (the rule of a full search).  Below that, one mapping per lane in index
+// order is the shorter chain.  145 M of 3^19 mappings (mixed DAG): 3.97 ms in parts,
+// 19.9 ms in index order.
+bool range_in_parts(const sched_problem& p, uint64_t lo, uint64_t hi) {
+  if (p.n > (p.sharing ? kPrefixMaxNShare : kPrefixMaxN) || p.n >= kCompactSnapN ||
+      p.enum_tools.size() < kSharedInner || p.free_fanout)
+    return false;
+  uint64_t inner = 1;
+  for (uint32_t j = 0; j < kSharedInner; ++j) inner *= 3;
+  return (hi - lo) / inner >= kTargetLanes &&
+         size_t(kMaxParts) * p.table_words + kMaxParts + 1 <= kStageWords;
+}
+
+// Enumeration order of a part: its free tools deepest first, then the tools
+// that count through the run.
+Seq part_enumeration(const sched_problem& p, int level) {
+  Seq seq;
+  bool low[kMaxTools] = {};
+  for (int k = 0; k < level; ++k) low[p.enum_tools[k]] = true;
+  for (int32_t v : p.late)
+    if (low[v]) seq.push_back(v);
+  for (size_t k = size_t(level); k < p.enum_tools.size(); ++k) seq.push_back(p.enum_tools[k]);
+  return seq;
 }
 
 size_t partial_capacity(uint64_t n_tables) {
@@ -580,6 +675,7 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
     p->table_full = p->table;
     set_enumeration(*p, enumeration(*p, true, int(a.inner_digits), a.prefix != 0),
                     p->table_full.data());
+    write_walk(a, p->table_full.data());
   } catch (const std::bad_alloc&) {
     delete p;
     return SCHED_E_NOMEM;
@@ -691,9 +787,59 @@ PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
   return l;
 }
 
-// Workspace bytes of one search over one problem table.
+// Bytes of the tables of one search: one table, or those of a range's parts
+// and their first blocks.
+size_t one_search_tables(const sched_problem& p) {
+  const size_t table = size_t(p.table_words) * 4;
+  return range_in_parts(p, 0, ~0ull) ? kMaxParts * table + (kMaxParts + 1) * 4 : table;
+}
+
+// Workspace bytes of one search.
 size_t one_search_bytes(const sched_problem& p) {
-  return layout_for(size_t(p.table_words) * 4, partial_capacity(1), 1).total;
+  return layout_for(one_search_tables(p), partial_capacity(1), 1).total;
+}
+
+// Plan and tables of a search over the parts of [lo, hi), staged in `stage`
+// (kStageWords): n_tables tables, then their first blocks.  Returns the number
+// of staged words.
+size_t stage_parts(const sched_problem& p, uint64_t lo, uint64_t hi, SearchArgs& a,
+                   uint32_t* stage) {
+  Part parts[kMaxParts];
+  const int n = split_range(p, lo, hi, parts);
+  a.lo = lo;
+  a.hi = hi;
+  a.full_range = 1;
+  a.one_result = 1;
+  a.sharing = uint32_t(p.sharing);
+  a.lds_levels = table_levels(p);
+  a.n_tables = uint32_t(n);
+  uint32_t* const first = stage + size_t(n) * p.table_words;
+  // The middle (part 0) comes last: the short parts are then done when its
+  // last blocks are.
+  uint32_t blocks = 0;
+  for (int i = 0; i < n; ++i) {
+    const int at = n - 1 - i;
+    const Part& part = parts[at];
+    uint32_t* const tb = stage + size_t(i) * p.table_words;
+    std::copy(p.table.begin(), p.table.end(), tb);
+    const Seq seq = part_enumeration(p, part.level);
+    set_enumeration(p, seq, tb);
+    SearchArgs w{};
+    w.prefix = part.level > 0 ? 1u : 0u;
+    w.inner_digits = w.prefix ? kSharedInner : 0u;
+    const uint64_t inner = inner_count(p, seq, int(w.inner_digits));
+    w.inner_count = uint32_t(inner);
+    w.outer_lo = part.lo / inner;
+    w.n_outer = (part.hi - part.lo) / inner;
+    write_walk(w, tb);
+    first[i] = blocks;
+    const uint64_t items = (w.n_outer + kBlock - 1) / kBlock;
+    const uint64_t cap = at == 0 ? kMaxBlocks - blocks : kMaxBlocks / (2 * kMaxParts);
+    blocks += uint32_t(std::min(items, cap));
+  }
+  first[n] = blocks;
+  a.n_blocks = blocks;
+  return size_t(n) * p.table_words + size_t(n) + 1;
 }
 
 // One search of [lo, hi) in workspace ws (at least one_search_bytes): table
@@ -701,21 +847,27 @@ size_t one_search_bytes(const sched_problem& p) {
 // mapping's makespan (full ranges only; null: none).  Allocates nothing.
 int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
                uint32_t* record, sched_result* h_out) {
-  const Layout L = layout_for(size_t(p.table_words) * 4, partial_capacity(1), 1);
+  const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
   SearchArgs a{};
-  plan_search(p, lo, hi, 1, a);
+  uint32_t stage[kStageWords];
+  const uint32_t* src = stage;
+  size_t words = p.table_words;
+  if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi)) {
+    words = stage_parts(p, lo, hi, a, stage);
+  } else {
+    plan_search(p, lo, hi, 1, a);
+    src = (a.full_range ? p.table_full : p.table).data();
+  }
   a.tables = reinterpret_cast<const uint32_t*>(ws + L.tables);
   a.table_stride = p.table_words;
+  if (a.one_result) a.block_first = a.tables + size_t(a.n_tables) * p.table_words;
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
+  a.results = reinterpret_cast<DevResult*>(ws + L.results);
   a.record = record;
-  DevResult* d_res = reinterpret_cast<DevResult*>(ws + L.results);
-  const std::vector<uint32_t>& table = a.full_range ? p.table_full : p.table;
-  HIP_TRY(hipMemcpyAsync(ws + L.tables, table.data(), size_t(p.table_words) * 4,
-                         hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemcpyAsync(ws + L.tables, src, words * 4, hipMemcpyHostToDevice, s));
   HIP_TRY(launch_search(p.n, a, s));
-  HIP_TRY(launch_reduce(a.partials, a.blocks_per_table, 1, d_res, s));
   DevResult r;
-  HIP_TRY(hipMemcpyAsync(&r, d_res, sizeof(r), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   h_out->best_index = r.index;
   h_out->makespan_us = r.makespan;
@@ -790,13 +942,12 @@ int sched_workspace_bytes(const sched_problem* const* problems, int32_t n_proble
                           int32_t n_replicas, size_t* out) {
   if (problems == nullptr || out == nullptr) return SCHED_E_NULL;
   if (n_problems < 1 || n_replicas < 0) return SCHED_E_SIZE;
-  size_t max_stride = 0;
+  size_t max_stride = 0, need = 0;
   for (int32_t i = 0; i < n_problems; ++i) {
     if (problems[i] == nullptr) return SCHED_E_NULL;
     max_stride = std::max<size_t>(max_stride, problems[i]->table_words);
+    need = std::max(need, one_search_bytes(*problems[i]));  // single-problem calls
   }
-  // single-problem calls
-  size_t need = layout_for(max_stride * 4, partial_capacity(1), 1).total;
   if (n_replicas > 0) {
     const size_t r = size_t(n_replicas);
     need = std::max(need, layout_for(r * max_stride * 4, partial_capacity(r), r).total);
@@ -899,6 +1050,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     // The block cap is shared by the whole batch so partials stay bounded.
     const uint64_t cap = std::max<uint64_t>(1, kMaxBlocks / R);
     g.a.blocks_per_table = uint32_t(std::min<uint64_t>(g.a.items_per_table, cap));
+    g.a.n_blocks = g.a.blocks_per_table * g.a.n_tables;
     groups.push_back(g);
     first = last;
   }
@@ -910,6 +1062,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
       rc = build_table(p, replica_lat + lat_off[r], tb);
       if (rc != SCHED_OK) return rc;
       set_enumeration(p, enumeration(p, true, int(g.a.inner_digits), g.a.prefix != 0), tb);
+      write_walk(g.a, tb);
     }
   }
 
@@ -923,14 +1076,13 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
   size_t partial_cursor = 0;
   for (Group& g : groups) {
     const int n = problems[replica_problem[order[g.first]]]->n;
-    const uint32_t count = uint32_t(g.last - g.first);
     SearchArgs& a = g.a;
     a.tables = d_tables + g.first * max_stride;
     a.table_stride = uint32_t(max_stride);
     a.partials = d_partials + partial_cursor;
+    a.results = d_res + g.first;
     HIP_TRY(launch_search(n, a, s));
-    HIP_TRY(launch_reduce(a.partials, a.blocks_per_table, count, d_res + g.first, s));
-    partial_cursor += size_t(count) * a.blocks_per_table;
+    partial_cursor += a.n_blocks;
   }
   HIP_TRY(hipMemcpyAsync(host_res.data(), d_res, R * sizeof(DevResult), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -1062,8 +1214,7 @@ int sched_eval_reprobes(const sched_problem* p, uint64_t base_index, const sched
 
 int sched_pruned_workspace_bytes(const sched_problem* p, size_t* out) {
   if (p == nullptr || out == nullptr) return SCHED_E_NULL;
-  const size_t plain = layout_for(size_t(p->table_words) * 4, partial_capacity(1), 1).total;
-  size_t need = plain;
+  size_t need = one_search_bytes(*p);
   if (p->n_mappings >= kPruneMinSpace) need = std::max(need, prune_layout(*p, plan_prune(*p)).total);
   *out = need;
   return SCHED_OK;
@@ -1202,6 +1353,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       SearchArgs a{};
       plan_search(sub, 0, sub.n_mappings, count, a);
       set_enumeration(sub, enumeration(sub, true, int(a.inner_digits), a.prefix != 0), stab.data());
+      write_walk(a, stab.data());
       tables.assign(size_t(count) * stride, 0u);
       for (uint32_t t = 0; t < count; ++t) {
         uint32_t* tb = tables.data() + size_t(t) * stride;
@@ -1226,13 +1378,12 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       a.tables = d_tab;
       a.table_stride = stride;
       a.partials = reinterpret_cast<Partial*>(ws + L.partials);
-      DevResult* d_res = reinterpret_cast<DevResult*>(ws + L.results);
+      a.results = reinterpret_cast<DevResult*>(ws + L.results);
       HIP_TRY(hipMemcpyAsync(ws + L.tables, tables.data(), tables.size() * 4,
                              hipMemcpyHostToDevice, s));
       HIP_TRY(launch_search(n, a, s));
-      HIP_TRY(launch_reduce(a.partials, a.blocks_per_table, count, d_res, s));
       res.resize(count);
-      HIP_TRY(hipMemcpyAsync(res.data(), d_res, count * sizeof(DevResult), hipMemcpyDeviceToHost,
+      HIP_TRY(hipMemcpyAsync(res.data(), a.results, count * sizeof(DevResult), hipMemcpyDeviceToHost,
                              s));
       HIP_TRY(hipStreamSynchronize(s));
       for (const DevResult& r : res)

@@ -56,7 +56,17 @@ enum : uint32_t {
   kHdrFlags = 15,     // kFlag* bits
   kHdrDeferLo = 16,   // inner tools of a shared-prefix search that are sinks with
   kHdrDeferHi = 17,   // predecessors: the search defers them (bits 0..31, 32..63)
-  kHdrWords = 18,
+  // The walk of a full-order search over this table: which outer combinations
+  // it covers and how (see SearchArgs, whose fields of the same names these
+  // are).  In the table, so that one launch can serve tables of different sizes.
+  kHdrOuterLoLo = 18,
+  kHdrOuterLoHi = 19,
+  kHdrNOuterLo = 20,
+  kHdrNOuterHi = 21,
+  kHdrInnerDigits = 22,
+  kHdrInnerCount = 23,
+  kHdrPrefix = 24,
+  kHdrWords = 25,
 };
 
 // A fan-out (no edges) whose footprints all fit the budget together, scored
@@ -131,9 +141,17 @@ struct Partial {
   uint32_t pad;
 };
 
+struct DevResult {
+  uint64_t index;
+  int64_t makespan;
+};
+
 struct SearchArgs {
   const uint32_t* tables;     // n_tables tables, table_stride words apart
   Partial* partials;          // one per block
+  DevResult* results;         // one per table, or one for all of them (one_result)
+  const uint32_t* block_first;  // n_tables + 1 entries: the first block of each table, then
+                              // the number of blocks; null: blocks_per_table each
   uint64_t lo, hi;            // index range searched in every table
   uint64_t outer_lo;          // first outer combination
   uint64_t n_outer;           // outer combinations covering [lo, hi)
@@ -143,18 +161,16 @@ struct SearchArgs {
   uint32_t inner_count;       // product of the radices of positions 0..J-1
   uint64_t items_per_table;   // ceil(n_outer / kBlock)
   uint32_t blocks_per_table;
-  uint32_t full_range;        // 1: [lo, hi) is every mapping, any enumeration order
+  uint32_t full_range;        // 1: the tables' own walks, any enumeration order (lo and hi
+                              //    are not read)
   uint32_t sharing;           // 1: processor-sharing contention
   uint32_t prefix;            // 1: shared prefixes (kSharedInner inner digits on the
                               //    deepest tools, full range, fixed at start)
   uint32_t lds_levels;        // the most contention levels any of the tables stores
+  uint32_t n_blocks;          // blocks of the launch
+  uint32_t one_result;        // 1: the tables are parts of one search, results has one entry
   uint32_t* record;           // full range, one table: every scored mapping's makespan
                               // (kInf if infeasible) goes to record[index]; null: none
-};
-
-struct DevResult {
-  uint64_t index;
-  int64_t makespan;
 };
 
 }  // namespace devmap

@@ -989,6 +989,33 @@ struct RecordTo {
   }
 };
 
+// The walk of a search: from the launch's arguments (a partial range in index
+// order, and the host harness), or from a table's header (full order: tables
+// of one launch may differ).
+__host__ __device__ __forceinline__ uint64_t walk_outer_lo(const SearchArgs& a) { return a.outer_lo; }
+__host__ __device__ __forceinline__ uint64_t walk_n_outer(const SearchArgs& a) { return a.n_outer; }
+__host__ __device__ __forceinline__ uint32_t walk_inner_digits(const SearchArgs& a) {
+  return a.inner_digits;
+}
+__host__ __device__ __forceinline__ uint32_t walk_inner_count(const SearchArgs& a) {
+  return a.inner_count;
+}
+struct TabWalk {
+  Tab t;
+};
+__host__ __device__ __forceinline__ uint64_t walk_outer_lo(const TabWalk& w) {
+  return uint64_t(w.t[kHdrOuterLoLo]) | (uint64_t(w.t[kHdrOuterLoHi]) << 32);
+}
+__host__ __device__ __forceinline__ uint64_t walk_n_outer(const TabWalk& w) {
+  return uint64_t(w.t[kHdrNOuterLo]) | (uint64_t(w.t[kHdrNOuterHi]) << 32);
+}
+__host__ __device__ __forceinline__ uint32_t walk_inner_digits(const TabWalk& w) {
+  return w.t[kHdrInnerDigits];
+}
+__host__ __device__ __forceinline__ uint32_t walk_inner_count(const TabWalk& w) {
+  return w.t[kHdrInnerCount];
+}
+
 // One lane's share of one work item: outer combination
 // outer_lo + item * kBlock + lane (the digits of enumeration positions J..N-1),
 // combined with every inner combination (positions 0..J-1) in range.  All
@@ -998,8 +1025,8 @@ struct RecordTo {
 // index need not grow along the walk, so the running minimum compares
 // (makespan, index) in full.  Otherwise: index order, o * 3^J + i, clipped to
 // [lo, hi); indices grow, so a strict comparison keeps the lowest index.
-template <int N, bool FULL, bool SHARE, class Rec = NoRecord>
-__host__ __device__ __forceinline__ void lane_search(const SearchArgs& a,
+template <int N, bool FULL, bool SHARE, class Rec = NoRecord, class Walk>
+__host__ __device__ __forceinline__ void lane_search(const Walk& a,
                                                      const uint32_t* __restrict__ tab,
                                                      const uint32_t* __restrict__ lds,
                                                      uint64_t item, uint32_t lane,
@@ -1008,22 +1035,22 @@ __host__ __device__ __forceinline__ void lane_search(const SearchArgs& a,
   using M = MaskT<N>;
   using I = IdxT<N>;
   const uint64_t rel = item * kBlock + lane;
-  if (rel >= a.n_outer) return;
+  if (rel >= walk_n_outer(a)) return;
   const uint32_t levels = tab[kHdrLevels];
   const uint32_t budget = tab[kHdrBudget];
-  const uint32_t J = a.inner_digits;
-  const uint64_t o = a.outer_lo + rel;
+  const uint32_t J = walk_inner_digits(a), inner_count = walk_inner_count(a);
+  const uint64_t o = walk_outer_lo(a) + rel;
   M ogn, ogq;
   uint64_t xo64;  // index weight of the outer digits
   decode_positions<N>(tab, o, J, tab[kHdrPositions], ogn, ogq, xo64);
-  uint32_t ilo = 0, ihi = a.inner_count;
+  uint32_t ilo = 0, ihi = inner_count;
   uint64_t base = 0;
   if constexpr (!FULL) {
-    base = o * a.inner_count;
+    base = o * inner_count;
     const uint64_t ilo64 = a.lo > base ? a.lo - base : 0;
     const uint64_t ihi64 = a.hi - base;  // > 0 because o < ceil(hi / 3^J)
-    ilo = uint32_t(ilo64 < a.inner_count ? ilo64 : a.inner_count);
-    ihi = uint32_t(ihi64 < a.inner_count ? ihi64 : a.inner_count);
+    ilo = uint32_t(ilo64 < inner_count ? ilo64 : inner_count);
+    ihi = uint32_t(ihi64 < inner_count ? ihi64 : inner_count);
   }
   const I xo = I(xo64);
   I bx = I(best_x);
@@ -1038,7 +1065,7 @@ __host__ __device__ __forceinline__ void lane_search(const SearchArgs& a,
     if (m == 1u) ign |= b;
     if (m == 2u) igq |= b;
   }
-  for (uint32_t i = 0; i < a.inner_count; ++i) {
+  for (uint32_t i = 0; i < inner_count; ++i) {
     if (FULL || (i >= ilo && i < ihi)) {
       uint32_t ms;
       if constexpr (SHARE)
@@ -1329,8 +1356,8 @@ __host__ __device__ __forceinline__ SnapPS<N> pull_snap(const SnapPS<N>& m, uint
 // prefixes, so the wave-wide masks of a pass stay narrow, and lanes whose
 // prefix is infeasible take no round.  Every lane of the wave must call this
 // function for the same item (lanes beyond the range take part in the pulls).
-template <int N, bool SHARE, class Rec = NoRecord>
-__host__ __device__ __forceinline__ void lane_search_prefix(const SearchArgs& a,
+template <int N, bool SHARE, class Rec = NoRecord, class Walk>
+__host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
                                                             const uint32_t* __restrict__ tab,
                                                             const uint32_t* __restrict__ lds,
                                                             uint64_t item, uint32_t lane,
@@ -1373,8 +1400,8 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const SearchArgs& a,
   uint64_t xo64 = 0;
   int pstar = -1;
   SS sm{};
-  if (rel < a.n_outer) {
-    decode_positions<N>(tab, a.outer_lo + rel, J, tab[kHdrPositions], ogn, ogq, xo64);
+  if (rel < walk_n_outer(a)) {
+    decode_positions<N>(tab, walk_outer_lo(a) + rel, J, tab[kHdrPositions], ogn, ogq, xo64);
     // The prefix: inner tools on the CPU (their modes are never read).
     S sim;
     sim.init(tab, ogn, ogq);
@@ -1408,7 +1435,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const SearchArgs& a,
   const uint32_t rk = lanes_below(feas);
   const uint32_t owner_of_rank = push(wl, pstar >= 0 ? rk : nv + wl - rk);
   // Inner combinations: C of them, positions 0 and 1 of radices r0, r1.
-  const uint32_t C = a.inner_count;
+  const uint32_t C = walk_inner_count(a);
   const uint32_t o0 = tab[kEnumOptBase + 0], o1 = J > 1 ? tab[kEnumOptBase + 1] : 0u;
   const uint32_t r0 = opt_radix(o0);
   const M b0 = M(1) << tab[kEnumLabBase + 0];
@@ -1424,7 +1451,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const SearchArgs& a,
   // and recomputing it each round keeps no counters live across the rounds.
   const uint32_t cinv = (65536u + C - 1u) / C;
   I bx = I(best_x);
-  if (rec.on() && pstar < 0 && rel < a.n_outer) {
+  if (rec.on() && pstar < 0 && rel < walk_n_outer(a)) {
     // an infeasible prefix: every inner combination is infeasible
     for (uint32_t cc = 0; cc < C; ++cc) {
       const uint32_t d1 = cc >= r0 ? (cc >= 2u * r0 ? 2u : 1u) : 0u;
@@ -1488,33 +1515,54 @@ search_kernel(SearchArgs a) {
   MaskT<N>* const slot = reinterpret_cast<MaskT<N>*>(&s_wave_words[threadIdx.x / 64]);
   constexpr bool kPrefix = FULL && N <= (SHARE ? kPrefixMaxNShare : kPrefixMaxN);
   __shared__ uint32_t s_snap[kPrefix ? snap_words<N, SHARE>() * kBlock : 1];
-  const uint32_t table = blockIdx.x / a.blocks_per_table;
-  const uint32_t bb = blockIdx.x - table * a.blocks_per_table;
+  // The block's table, its place among the table's blocks, their number.
+  uint32_t table, bb, nb;
+  if (FULL && a.block_first != nullptr) {
+    const Tab first{a.block_first};
+    uint32_t hi = a.n_tables;
+    table = 0;
+    while (hi - table > 1u) {
+      const uint32_t mid = (table + hi) >> 1;
+      if (first[mid] <= blockIdx.x) table = mid;
+      else hi = mid;
+    }
+    bb = blockIdx.x - first[table];
+    nb = first[table + 1u] - first[table];
+  } else {
+    nb = a.blocks_per_table;
+    table = blockIdx.x / nb;
+    bb = blockIdx.x - table * nb;
+  }
   const uint32_t* tab = a.tables + size_t(table) * a.table_stride;
   stage_tables<N>(tab, s_lds);
 
   uint32_t best_ms = kInf;
   uint64_t best_x = ~0ull;
-  using Rec = typename std::conditional<FULL, RecordTo, NoRecord>::type;
-  Rec rec{};
-  if constexpr (FULL) rec.out = a.record;
-  if constexpr (kPrefix) {
-    if (a.prefix) {
-      for (uint64_t item = bb; item < a.items_per_table; item += a.blocks_per_table)
-        lane_search_prefix<N, SHARE, Rec>(a, tab, s_lds, item, threadIdx.x, slot,
-                                          s_snap + threadIdx.x, best_ms, best_x, rec);
+  if constexpr (FULL) {
+    const TabWalk walk{Tab{tab}};
+    const uint64_t items = (walk_n_outer(walk) + (kBlock - 1)) / kBlock;
+    const RecordTo rec{a.record};
+    if constexpr (kPrefix) {
+      if (walk.t[kHdrPrefix]) {
+        for (uint64_t item = bb; item < items; item += nb)
+          lane_search_prefix<N, SHARE>(walk, tab, s_lds, item, threadIdx.x, slot,
+                                       s_snap + threadIdx.x, best_ms, best_x, rec);
+      } else {
+        for (uint64_t item = bb; item < items; item += nb)
+          lane_search<N, FULL, SHARE>(walk, tab, s_lds, item, threadIdx.x, slot, best_ms, best_x,
+                                      rec);
+      }
     } else {
-      for (uint64_t item = bb; item < a.items_per_table; item += a.blocks_per_table)
-        lane_search<N, FULL, SHARE, Rec>(a, tab, s_lds, item, threadIdx.x,
-                                         slot, best_ms, best_x, rec);
+      for (uint64_t item = bb; item < items; item += nb)
+        lane_search<N, FULL, SHARE>(walk, tab, s_lds, item, threadIdx.x, slot, best_ms, best_x,
+                                    rec);
     }
   } else {
-    for (uint64_t item = bb; item < a.items_per_table; item += a.blocks_per_table)
-      lane_search<N, FULL, SHARE, Rec>(a, tab, s_lds, item, threadIdx.x, slot,
-                                       best_ms, best_x, rec);
+    for (uint64_t item = bb; item < a.items_per_table; item += nb)
+      lane_search<N, FULL, SHARE>(a, tab, s_lds, item, threadIdx.x, slot, best_ms, best_x);
   }
 
-  block_min(best_ms, best_x);
+  block_min<kBlock>(best_ms, best_x);
   if (threadIdx.x == 0) {
     Partial p;
     p.index = best_x;
@@ -1623,7 +1671,7 @@ __global__ __launch_bounds__(kBlock) void bound_kernel(const uint32_t* __restric
 // the inst_*.hip translation units).
 template <int N>
 hipError_t launch_search_n(const SearchArgs& a, hipStream_t s) {
-  const uint32_t blocks = a.n_tables * a.blocks_per_table;
+  const uint32_t blocks = a.n_blocks;
   if (a.lds_levels < 1 || a.lds_levels > lds_levels<N>()) return hipErrorInvalidValue;
   const size_t shm = size_t(lds_words_for(N, a.lds_levels)) * 4u;
   if (a.sharing) {

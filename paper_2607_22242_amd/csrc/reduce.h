@@ -16,9 +16,10 @@ __device__ __forceinline__ void lex_min(uint32_t& ms, uint64_t& x, uint32_t oms,
 }
 
 // Block-wide lexicographic min of (makespan, index); result valid in thread 0.
+template <int THREADS>
 __device__ __forceinline__ void block_min(uint32_t& ms, uint64_t& x) {
-  __shared__ uint32_t s_ms[kBlock / 64];
-  __shared__ uint64_t s_x[kBlock / 64];
+  __shared__ uint32_t s_ms[THREADS / 64];
+  __shared__ uint64_t s_x[THREADS / 64];
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const uint32_t oms = __shfl_xor(ms, off);
@@ -32,7 +33,7 @@ __device__ __forceinline__ void block_min(uint32_t& ms, uint64_t& x) {
   }
   __syncthreads();
   if (threadIdx.x == 0) {
-    for (int w = 1; w < kBlock / 64; ++w) lex_min(ms, x, s_ms[w], s_x[w]);
+    for (int w = 1; w < THREADS / 64; ++w) lex_min(ms, x, s_ms[w], s_x[w]);
   }
 }
 
