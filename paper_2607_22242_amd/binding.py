@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from typing import List, Optional, Sequence, Tuple
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -60,6 +61,10 @@ class sched_probe(ctypes.Structure):
     _fields_ = [("index", ctypes.c_uint64), ("makespan_us", ctypes.c_int64),
                 ("kind", ctypes.c_int32), ("tool", ctypes.c_int32),
                 ("mode", ctypes.c_int32), ("swap_tool", ctypes.c_int32)]
+
+
+_PROBE = struct.Struct("=Qqiiii")  # the fields of sched_probe
+assert _PROBE.size == ctypes.sizeof(sched_probe)
 
 
 class sched_problem_desc(ctypes.Structure):
@@ -392,13 +397,17 @@ def sched_eval_reprobes(handle, base_index: int, workspace, lat=None,
     got = ctypes.c_int32()
     latp = None
     if lat is not None:
-        latp = (sched_lat * n)(*[sched_lat(*map(int, r[:4])) for r in lat])
+        flat = [int(x) for r in lat for x in r[:4]]
+        if len(flat) == 4 * n and all(len(r) >= 4 for r in lat):
+            latp = (ctypes.c_int64 * (4 * n))(*flat)
+        else:
+            latp = (sched_lat * n)(*[sched_lat(*map(int, r[:4])) for r in lat])
     wp, wb = _ws(workspace)
     _check(lib().sched_eval_reprobes(handle, base_index, latp, wp, wb, _stream_ptr(stream), out,
                                      cap, ctypes.byref(got)), "sched_eval_reprobes")
-    return [{"index": out[k].index, "makespan_us": out[k].makespan_us, "kind": out[k].kind,
-             "tool": out[k].tool, "mode": out[k].mode, "swap_tool": out[k].swap_tool}
-            for k in range(got.value)]
+    keys = ("index", "makespan_us", "kind", "tool", "mode", "swap_tool")
+    return [dict(zip(keys, row)) for row in _PROBE.iter_unpack(
+        ctypes.string_at(out, got.value * ctypes.sizeof(sched_probe)))]
 
 
 def sched_pruned_workspace_bytes(handle) -> int:

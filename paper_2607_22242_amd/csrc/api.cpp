@@ -4,8 +4,10 @@
 
 #include <algorithm>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <numeric>
+#include <optional>
 #include <vector>
 
 #include "sched_search.h"
@@ -29,7 +31,6 @@ struct sched_problem {
   int32_t sharing = 0;                      // 1: processor-sharing contention
   bool free_fanout = false;                 // no edges, all footprints fit (kFlagFreeFanout)
   uint64_t n_mappings = 0;
-  int32_t n_preds = 0;
   uint32_t table_words = 0;
   std::vector<uint32_t> table;       // device image with the problem's own latencies
   std::vector<uint32_t> table_full;  // the same, ordered for a one-table full-range search
@@ -69,8 +70,10 @@ uint32_t options_word(const sched_problem& p, int v) {
   return o;
 }
 
-// round(b * f / 2^16), halves up, in 128-bit arithmetic.
+// round(b * f / 2^16), halves up, in 128-bit arithmetic where 64 bits do not
+// hold the product (f <= 2^24).
 uint64_t scale_q16(uint64_t b, uint32_t f) {
+  if (b < (1ull << 39)) return (b * f + 32768u) >> 16;
   unsigned __int128 p = (unsigned __int128)b * f + 32768u;
   unsigned __int128 r = p >> 16;
   return r > ~0ull ? ~0ull : uint64_t(r);
@@ -95,33 +98,59 @@ static void write_deferred(uint32_t* table) {
     if (pm) has_pred |= 1ull << i;
   }
   uint64_t inner = 0;
-  for (uint32_t j = 0; j < kSharedInner; ++j) inner |= 1ull << table[kEnumLabBase + j];
+  for (uint32_t j = 0; j < kSharedInner; ++j)
+    inner |= 1ull << table[enum_lab_base(uint32_t(n)) + j];
   const uint64_t d = inner & ~has_succ & has_pred;
   table[kHdrDeferLo] = uint32_t(d);
   table[kHdrDeferHi] = uint32_t(d >> 32);
 }
 
-// Fill the device table of problem p with latencies lat (nullptr: the
-// problem's own).  Returns SCHED_E_OVERFLOW when the 32-bit guards fail.
-int build_table(const sched_problem& p, const sched_lat* lat, uint32_t* out) {
+// A sequence of tools (an enumeration order) held without heap memory, so
+// that planning a search allocates nothing.
+struct Seq {
+  int32_t v[kMaxTools];
+  int n = 0;
+  void push_back(int32_t x) { v[n++] = x; }
+  int size() const { return n; }
+  int32_t operator[](int k) const { return v[k]; }
+};
+
+// Write the enumeration order seq[0..n) into a table whose tools are in place.
+void set_enumeration(const sched_problem& p, const int32_t* seq, int n, uint32_t* table) {
+  const uint32_t lay = table[kHdrN];
+  for (int k = 0; k < n; ++k) {
+    const int v = seq[k];
+    table[enum_lab_base(lay) + k] = table[pos_base(lay) + v];
+    table[enum_weight_base(lay) + 2 * k] = uint32_t(p.weight[v]);
+    table[enum_weight_base(lay) + 2 * k + 1] = uint32_t(p.weight[v] >> 32);
+    table[enum_opt_base(lay) + k] = options_word(p, v);
+  }
+  write_deferred(table);
+}
+
+void set_enumeration(const sched_problem& p, const Seq& seq, uint32_t* table) {
+  set_enumeration(p, seq.v, seq.n, table);
+}
+
+void set_enumeration(const sched_problem& p, const std::vector<int32_t>& seq, uint32_t* table) {
+  set_enumeration(p, seq.data(), int(seq.size()), table);
+}
+
+// Contention levels stored in a problem's table.
+uint32_t table_levels(const sched_problem& p) {
+  return uint32_t(std::min<int>(int(p.contention.size()), p.n));
+}
+
+// The words of a table that depend on latencies (lat; nullptr: the problem's
+// own): cpu_us and xfer_us, the duration and processor-sharing tables, and the
+// bound table if asked for.  The rest of the table is in place (lay_table).
+// Returns SCHED_E_VALUE, or SCHED_E_OVERFLOW when the 32-bit guards fail.
+int fill_latencies(const sched_problem& p, const sched_lat* lat, uint32_t* out, bool bounds) {
   const int n = p.n;
-  const int levels = std::min<int>(int(p.contention.size()), n);
-  std::memset(out, 0, sizeof(uint32_t) * p.table_words);
-
-  int64_t sum_mem = 0;
-  for (const auto& t : p.tools) sum_mem += t.mem_mib;
-  const int64_t budget = std::min<int64_t>(p.budget, sum_mem);
-  // VRAM sums of up to N footprints (each clamped to budget+1) plus the
-  // budget must stay below 2^32.
-  if ((unsigned __int128)(n + 1) * (unsigned __int128)(budget + 1) >= ((unsigned __int128)1 << 32))
-    return SCHED_E_OVERFLOW;
-
-  std::vector<int32_t> label(n);
-  for (int i = 0; i < n; ++i) label[p.order[i]] = i;
-  uint64_t big = 0;
+  const uint32_t lay = out[kHdrN], levels = out[kHdrLevels];
+  const uint32_t dur_off = out[kHdrDurOff], share_off = out[kHdrShareOff];
+  const uint64_t big = uint64_t(out[kHdrBigLo]) | (uint64_t(out[kHdrBigHi]) << 32);
   unsigned __int128 bound = 0;  // worst-case makespan: sum of longest durations + transfers
-  const uint32_t dur_off = kPredBase + ((uint32_t(p.n_preds) + 3u) & ~3u);
-  uint32_t pred_cursor = 0;
   for (int i = 0; i < n; ++i) {
     const int v = p.order[i];
     const sched_tool& tl = p.tools[v];
@@ -134,96 +163,36 @@ int build_table(const sched_problem& p, const sched_lat* lat, uint32_t* out) {
     uint64_t longest = uint64_t(cpu);
     for (int q = 0; q < 2; ++q) {
       const uint64_t base = q == 0 ? uint64_t(gpu) : uint64_t(gpu) + uint64_t(load);
-      for (int l = 0; l < levels; ++l) {
+      for (uint32_t l = 0; l < levels; ++l) {
         const uint64_t d = scale_q16(base, p.contention[l]);
         longest = std::max(longest, d);
-        if (d < (1ull << 31))
-          out[dur_off + (uint32_t(i) * 2u + uint32_t(q)) * uint32_t(levels) + l] = uint32_t(d);
+        out[dur_off + (uint32_t(i) * 2u + uint32_t(q)) * levels + l] =
+            d < (1ull << 31) ? uint32_t(d) : 0u;
       }
     }
     bound += (unsigned __int128)longest + (unsigned __int128)uint64_t(xfer);
     if (bound >= ((unsigned __int128)1 << 30)) return SCHED_E_OVERFLOW;
-
     uint32_t* rec = out + kHdrWords + kToolWords * uint32_t(i);
     rec[kToolCpu] = uint32_t(cpu);
-    rec[kToolMem] = uint32_t(std::min<int64_t>(tl.mem_mib, budget + 1));
     rec[kToolXfer] = uint32_t(xfer);
-    std::vector<int32_t> pl;
-    for (int32_t u : p.preds[v]) pl.push_back(label[u]);
-    std::sort(pl.begin(), pl.end());
-    uint64_t pm = 0;
-    for (int32_t u : pl) pm |= 1ull << u;
-    rec[kToolPredLo] = uint32_t(pm);
-    rec[kToolPredHi] = uint32_t(pm >> 32);
-    rec[kToolPredOff] = pred_cursor;
-    rec[kToolNPred] = uint32_t(pl.size());
-    rec[kToolOrig] = (uint32_t(v) << kOrigLabelBits) | uint32_t(i);
-    for (int32_t u : pl) out[kPredBase + pred_cursor++] = uint32_t(u);
-    out[kPosBase + v] = uint32_t(i);
-    if (tl.mem_mib > budget) big |= 1ull << i;
-  }
-  // Index order: position k holds the k-th tool with a choice; the others
-  // are fixed in the header.
-  uint64_t fix_gn = 0, fix_gq = 0;
-  for (int v = 0; v < n; ++v)
-    if (p.radix[v] == 1) {
-      const int m = mode_of_digit(p, v, 0);
-      if (m == 1) fix_gn |= 1ull << label[v];
-      if (m == 2) fix_gq |= 1ull << label[v];
-    }
-  for (size_t k = 0; k < p.enum_tools.size(); ++k) {
-    const int v = p.enum_tools[k];
-    out[kEnumLabBase + k] = uint32_t(label[v]);
-    out[kEnumWeightBase + 2 * k] = uint32_t(p.weight[v]);
-    out[kEnumWeightBase + 2 * k + 1] = uint32_t(p.weight[v] >> 32);
-    out[kEnumOptBase + k] = options_word(p, v);
-  }
-  out[kHdrPositions] = uint32_t(p.enum_tools.size());
-  out[kHdrFixGnLo] = uint32_t(fix_gn);
-  out[kHdrFixGnHi] = uint32_t(fix_gn >> 32);
-  out[kHdrFixGqLo] = uint32_t(fix_gq);
-  out[kHdrFixGqHi] = uint32_t(fix_gq >> 32);
-  out[kHdrN] = uint32_t(n);
-  out[kHdrLevels] = uint32_t(levels);
-  out[kHdrBudget] = uint32_t(budget);
-  out[kHdrBigLo] = uint32_t(big);
-  out[kHdrBigHi] = uint32_t(big >> 32);
-  out[kHdrDurOff] = dur_off;
-  write_deferred(out);
-  // Processor-sharing table: isolated GPU latencies per label, then the
-  // work rate of each contention level, round(2^32 / F) halves up.
-  const uint32_t bound_off = dur_off + uint32_t(n) * 2u * uint32_t(levels);
-  const uint32_t share_off = bound_off + kBoundWords * uint32_t(n);
-  for (int i = 0; i < n; ++i) {
-    const int v = p.order[i];
-    const int64_t gpu = lat ? lat[v].gpu_us : p.tools[v].gpu_us;
-    const int64_t load = lat ? lat[v].load_us : p.tools[v].load_us;
     out[share_off + 2 * uint32_t(i)] = uint32_t(gpu);
     out[share_off + 2 * uint32_t(i) + 1] = uint32_t(gpu + load);
   }
-  for (int l = 0; l < levels; ++l) {
-    const uint64_t f = p.contention[l];
-    const uint64_t w = ((1ull << 33) + f) / (2 * f);
-    out[share_off + 2 * uint32_t(n) + uint32_t(l)] = uint32_t(w);
-    // floor(2^48 / w): the device divides by w through this reciprocal
-    const uint64_t winv = (1ull << 48) / w;
-    out[share_off + 2 * uint32_t(n) + uint32_t(levels) + 2 * uint32_t(l)] = uint32_t(winv);
-    out[share_off + 2 * uint32_t(n) + uint32_t(levels) + 2 * uint32_t(l) + 1] = uint32_t(winv >> 32);
-  }
-  out[kHdrShareOff] = share_off;
+  if (!bounds) return SCHED_OK;
   // Bound table: shortest durations per mode and over the allowed modes.
   // Fixed at start, a GPU task lasts one of its scaled durations; under
   // processor sharing at least its work over the fastest rate.
+  const uint32_t bound_off = out[kHdrBoundOff];
   for (int i = 0; i < n; ++i) {
     const int v = p.order[i];
     uint32_t best[3] = {out[kHdrWords + kToolWords * uint32_t(i) + kToolCpu], kInf, kInf};
     if (!((big >> i) & 1))
       for (int q = 0; q < 2; ++q)
-        for (int l = 0; l < levels; ++l) {
-          uint32_t d = out[dur_off + (uint32_t(i) * 2u + uint32_t(q)) * uint32_t(levels) + l];
+        for (uint32_t l = 0; l < levels; ++l) {
+          uint32_t d = out[dur_off + (uint32_t(i) * 2u + uint32_t(q)) * levels + l];
           if (p.sharing) {
             const uint64_t work = uint64_t(out[share_off + 2 * uint32_t(i) + uint32_t(q)]) << 16;
-            const uint64_t w = out[share_off + 2 * uint32_t(n) + uint32_t(l)];
+            const uint64_t w = out[share_off + 2 * lay + l];
             d = uint32_t((work + w - 1) / w);
           }
           best[1 + q] = std::min(best[1 + q], d);
@@ -235,14 +204,84 @@ int build_table(const sched_problem& p, const sched_lat* lat, uint32_t* out) {
     }
     out[bound_off + kBoundWords * uint32_t(i) + 3] = any;
   }
-  out[kHdrBoundOff] = bound_off;
-  out[kHdrFlags] = p.free_fanout ? kFlagFreeFanout : 0u;
   return SCHED_OK;
 }
 
-// Contention levels stored in a problem's table.
-uint32_t table_levels(const sched_problem& p) {
-  return uint32_t(std::min<int>(int(p.contention.size()), p.n));
+// The words of problem p's table, laid out for `lay` tools (at least its own),
+// that do not depend on latencies; the others are 0.  Returns
+// SCHED_E_OVERFLOW when the 32-bit guard of VRAM sums fails.
+int lay_table(const sched_problem& p, uint32_t lay, uint32_t* out) {
+  const int n = p.n;
+  const uint32_t levels = table_levels(p);
+  std::memset(out, 0, sizeof(uint32_t) * table_words(lay, levels));
+
+  int64_t sum_mem = 0;
+  for (const auto& t : p.tools) sum_mem += t.mem_mib;
+  const int64_t budget = std::min<int64_t>(p.budget, sum_mem);
+  // VRAM sums of up to N footprints (each clamped to budget+1) plus the
+  // budget must stay below 2^32.
+  if ((unsigned __int128)(n + 1) * (unsigned __int128)(budget + 1) >= ((unsigned __int128)1 << 32))
+    return SCHED_E_OVERFLOW;
+
+  int32_t label[kMaxTools];
+  for (int i = 0; i < n; ++i) label[p.order[i]] = i;
+  uint64_t big = 0;
+  for (int i = 0; i < n; ++i) {
+    const int v = p.order[i];
+    const sched_tool& tl = p.tools[v];
+    uint32_t* rec = out + kHdrWords + kToolWords * uint32_t(i);
+    rec[kToolMem] = uint32_t(std::min<int64_t>(tl.mem_mib, budget + 1));
+    uint64_t pm = 0;
+    for (int32_t u : p.preds[v]) pm |= 1ull << label[u];
+    rec[kToolPredLo] = uint32_t(pm);
+    rec[kToolPredHi] = uint32_t(pm >> 32);
+    rec[kToolOrig] = (uint32_t(v) << kOrigLabelBits) | uint32_t(i);
+    out[pos_base(lay) + uint32_t(v)] = uint32_t(i);
+    if (tl.mem_mib > budget) big |= 1ull << i;
+  }
+  // Index order: position k holds the k-th tool with a choice; the others
+  // are fixed in the header.
+  uint64_t fix_gn = 0, fix_gq = 0;
+  for (int v = 0; v < n; ++v)
+    if (p.radix[v] == 1) {
+      const int m = mode_of_digit(p, v, 0);
+      if (m == 1) fix_gn |= 1ull << label[v];
+      if (m == 2) fix_gq |= 1ull << label[v];
+    }
+  out[kHdrN] = lay;
+  out[kHdrLevels] = levels;
+  out[kHdrBudget] = uint32_t(budget);
+  out[kHdrBigLo] = uint32_t(big);
+  out[kHdrBigHi] = uint32_t(big >> 32);
+  out[kHdrDurOff] = dur_base(lay);
+  out[kHdrPositions] = uint32_t(p.enum_tools.size());
+  out[kHdrFixGnLo] = uint32_t(fix_gn);
+  out[kHdrFixGnHi] = uint32_t(fix_gn >> 32);
+  out[kHdrFixGqLo] = uint32_t(fix_gq);
+  out[kHdrFixGqHi] = uint32_t(fix_gq >> 32);
+  out[kHdrShareOff] = share_base(lay, levels);
+  out[kHdrBoundOff] = bound_base(lay, levels);
+  out[kHdrFlags] = p.free_fanout ? kFlagFreeFanout : 0u;
+  set_enumeration(p, p.enum_tools, out);
+  // Processor sharing: the work rate of each contention level, round(2^32 / F)
+  // halves up, and floor(2^48 / w): the device divides by w through this
+  // reciprocal.
+  uint32_t* const rates = out + share_base(lay, levels) + 2 * lay;
+  for (uint32_t l = 0; l < levels; ++l) {
+    const uint64_t f = p.contention[l];
+    const uint64_t w = ((1ull << 33) + f) / (2 * f);
+    rates[l] = uint32_t(w);
+    const uint64_t winv = (1ull << 48) / w;
+    rates[levels + 2 * l] = uint32_t(winv);
+    rates[levels + 2 * l + 1] = uint32_t(winv >> 32);
+  }
+  return SCHED_OK;
+}
+
+// The table of problem p with latencies lat (nullptr: the problem's own).
+int build_table(const sched_problem& p, const sched_lat* lat, uint32_t* out) {
+  const int rc = lay_table(p, uint32_t(p.n), out);
+  return rc != SCHED_OK ? rc : fill_latencies(p, lat, out, true);
 }
 
 // Relabel p so that the first kSharedInner tools with a choice in p.late
@@ -327,16 +366,6 @@ bool prefix_plan(const sched_problem& p, uint64_t n_tables) {
   return (unsigned __int128)(p.n_mappings / inner) * n_tables >= kTargetLanes;
 }
 
-// A sequence of tools (an enumeration order) held without heap memory, so
-// that planning a search allocates nothing.
-struct Seq {
-  int32_t v[kMaxTools];
-  int n = 0;
-  void push_back(int32_t x) { v[n++] = x; }
-  int size() const { return n; }
-  int32_t operator[](int k) const { return v[k]; }
-};
-
 Seq enumeration(const sched_problem& p, bool full, int J, bool prefix) {
   Seq seq;
   if (!full) {
@@ -416,26 +445,6 @@ void write_walk(const SearchArgs& a, uint32_t* table) {
   table[kHdrInnerDigits] = a.inner_digits;
   table[kHdrInnerCount] = a.inner_count;
   table[kHdrPrefix] = a.prefix;
-}
-
-// Write the enumeration order seq[0..n) into a table built by build_table.
-void set_enumeration(const sched_problem& p, const int32_t* seq, int n, uint32_t* table) {
-  for (int k = 0; k < n; ++k) {
-    const int v = seq[k];
-    table[kEnumLabBase + k] = table[kPosBase + v];
-    table[kEnumWeightBase + 2 * k] = uint32_t(p.weight[v]);
-    table[kEnumWeightBase + 2 * k + 1] = uint32_t(p.weight[v] >> 32);
-    table[kEnumOptBase + k] = options_word(p, v);
-  }
-  write_deferred(table);
-}
-
-void set_enumeration(const sched_problem& p, const Seq& seq, uint32_t* table) {
-  set_enumeration(p, seq.v, seq.n, table);
-}
-
-void set_enumeration(const sched_problem& p, const std::vector<int32_t>& seq, uint32_t* table) {
-  set_enumeration(p, seq.data(), int(seq.size()), table);
 }
 
 // A partial range [lo, hi) as parts of a full-order search.  A part of level k
@@ -545,11 +554,6 @@ int check_workspace(void* ws, size_t ws_bytes, size_t need) {
   return SCHED_OK;
 }
 
-#define HIP_TRY(expr)                                  \
-  do {                                                 \
-    if ((expr) != hipSuccess) return SCHED_E_DEVICE;   \
-  } while (0)
-
 int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* edges,
                    int32_t n_edges, const uint32_t* contention_q16, int32_t n_levels,
                    int64_t vram_budget_mib, const uint8_t* allowed, int32_t sharing,
@@ -594,7 +598,6 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
       pl.erase(std::unique(pl.begin(), pl.end()), pl.end());
       total += int32_t(pl.size());
     }
-    p->n_preds = total;
     // Kahn's algorithm: every tool must be reachable in a topological order.
     std::vector<int32_t> indeg(n_tools, 0);
     std::vector<std::vector<int32_t>> succ(n_tools);
@@ -662,7 +665,7 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
     bool identity = true;
     for (int32_t i = 0; i < n_tools; ++i) identity = identity && p->order[i] == i;
     p->free_fanout = fanout_fits && identity;
-    p->table_words = table_words(n_tools, total, std::min<int>(n_levels, n_tools));
+    p->table_words = table_words(uint32_t(n_tools), table_levels(*p));
     p->table.assign(p->table_words, 0u);
     const int rc = build_table(*p, nullptr, p->table.data());
     if (rc != SCHED_OK) {
@@ -681,6 +684,104 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
     return SCHED_E_NOMEM;
   }
   *out = p;
+  return SCHED_OK;
+}
+
+#define HIP_TRY(expr)                                  \
+  do {                                                 \
+    if ((expr) != hipSuccess) return SCHED_E_DEVICE;   \
+  } while (0)
+
+// Page-locked host memory that kernels read and write directly, so that a
+// small call needs no copies: its indices and its results (or its blocks'
+// partial minima) cross the link as part of the kernel.  One allocation of
+// kSlots slots for the process, made at the first call that wants one; a call
+// holds one slot from before its launch until its stream is done with it, and
+// gives it back.  With every slot taken (or none to be had) a call copies
+// through its workspace instead.  A 16-byte result and its copy back measured
+// 26.4 us from launch to host, written straight to the host 17.6 us.
+constexpr int kSlots = 8;
+constexpr size_t kSlotBytes = size_t(32) << 10;
+std::mutex g_slot_mutex;
+char* g_slots = nullptr;
+bool g_slots_failed = false;
+uint32_t g_slots_taken = 0;
+
+class Slot {
+ public:
+  explicit Slot(hipStream_t s) : stream_(s) {
+    std::lock_guard<std::mutex> lock(g_slot_mutex);
+    if (g_slots == nullptr && !g_slots_failed) {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kSlots * kSlotBytes, hipHostMallocPortable) == hipSuccess) {
+        g_slots = static_cast<char*>(p);
+      } else {
+        (void)hipGetLastError();
+        g_slots_failed = true;
+      }
+    }
+    for (int k = 0; g_slots != nullptr && k < kSlots; ++k)
+      if (!((g_slots_taken >> k) & 1u)) {
+        g_slots_taken |= 1u << k;
+        at_ = k;
+        break;
+      }
+  }
+  Slot(const Slot&) = delete;
+  Slot& operator=(const Slot&) = delete;
+  ~Slot() {
+    if (at_ < 0) return;
+    if (launched_) (void)hipStreamSynchronize(stream_);  // an error left the call early
+    std::lock_guard<std::mutex> lock(g_slot_mutex);
+    g_slots_taken &= ~(1u << at_);
+  }
+  char* data() const { return at_ < 0 ? nullptr : g_slots + size_t(at_) * kSlotBytes; }
+  // Between launched() and waited() the stream may still write the slot.
+  void launched() { launched_ = true; }
+  void waited() { launched_ = false; }
+
+ private:
+  hipStream_t stream_;
+  int at_ = -1;
+  bool launched_ = false;
+};
+
+// Whether a table (up to its bound table) fits a kernel's arguments.
+bool fits_arguments(const uint32_t* table) {
+  return bound_base(table[kHdrN], table[kHdrLevels]) <= kArgWords;
+}
+
+// Makespans of m mapping indices of problem p with the host table `table`
+// (INT64_MAX: infeasible), through a slot, or through device memory: d_tab
+// (the table), d_idx and d_ms (m entries each).  Waits for the stream.
+int score(const sched_problem& p, const uint32_t* table, const uint64_t* idx, size_t m,
+          int64_t* ms, uint32_t* d_tab, uint64_t* d_idx, int64_t* d_ms, hipStream_t s) {
+  uint32_t flags = p.sharing ? kEvalSharing : 0u;
+  const uint32_t* tab = table;
+  if (fits_arguments(table)) {
+    flags |= kEvalHostTable;
+  } else {
+    HIP_TRY(hipMemcpyAsync(d_tab, table, size_t(p.table_words) * 4, hipMemcpyHostToDevice, s));
+    tab = d_tab;
+  }
+  if (m * 16 <= kSlotBytes) {
+    Slot slot(s);
+    if (char* h = slot.data()) {
+      std::memcpy(h, idx, m * 8);
+      int64_t* const h_ms = reinterpret_cast<int64_t*>(h) + m;
+      slot.launched();
+      HIP_TRY(launch_eval(p.n, tab, reinterpret_cast<const uint64_t*>(h), int64_t(m), p.n_mappings,
+                          h_ms, flags, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      slot.waited();
+      std::memcpy(ms, h_ms, m * 8);
+      return SCHED_OK;
+    }
+  }
+  HIP_TRY(hipMemcpyAsync(d_idx, idx, m * 8, hipMemcpyHostToDevice, s));
+  HIP_TRY(launch_eval(p.n, tab, d_idx, int64_t(m), p.n_mappings, d_ms, flags, s));
+  HIP_TRY(hipMemcpyAsync(ms, d_ms, m * 8, hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
   return SCHED_OK;
 }
 
@@ -745,7 +846,7 @@ PrunePlan plan_prune(const sched_problem& p) {
   const uint32_t* bt = p.table.data() + p.table[kHdrBoundOff];
   std::vector<std::pair<uint64_t, int32_t>> spread;
   for (int32_t v : p.enum_tools) {
-    const uint32_t i = p.table[kPosBase + v];
+    const uint32_t i = p.table[pos_base(uint32_t(p.n)) + uint32_t(v)];
     uint32_t lo = kInf, hi = 0;
     for (int m = 0; m < 3; ++m) {
       if (!((p.allowed[v] >> m) & 1)) continue;
@@ -791,7 +892,7 @@ PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
 // and their first blocks.
 size_t one_search_tables(const sched_problem& p) {
   const size_t table = size_t(p.table_words) * 4;
-  return range_in_parts(p, 0, ~0ull) ? kMaxParts * table + (kMaxParts + 1) * 4 : table;
+  return range_in_parts(p, 0, p.n_mappings) ? kMaxParts * table + (kMaxParts + 1) * 4 : table;
 }
 
 // Workspace bytes of one search.
@@ -842,33 +943,95 @@ size_t stage_parts(const sched_problem& p, uint64_t lo, uint64_t hi, SearchArgs&
   return size_t(n) * p.table_words + size_t(n) + 1;
 }
 
-// One search of [lo, hi) in workspace ws (at least one_search_bytes): table
-// copy, search and reduction on stream s, then the result.  record: every
-// mapping's makespan (full ranges only; null: none).  Allocates nothing.
-int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
-               uint32_t* record, sched_result* h_out) {
+// A partial range searched in parts, in workspace ws.  Allocates nothing.
+int search_parts(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
+                 sched_result* h_out) {
   const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
   SearchArgs a{};
   uint32_t stage[kStageWords];
-  const uint32_t* src = stage;
-  size_t words = p.table_words;
-  if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi)) {
-    words = stage_parts(p, lo, hi, a, stage);
-  } else {
-    plan_search(p, lo, hi, 1, a);
-    src = (a.full_range ? p.table_full : p.table).data();
-  }
+  const size_t words = stage_parts(p, lo, hi, a, stage);
   a.tables = reinterpret_cast<const uint32_t*>(ws + L.tables);
   a.table_stride = p.table_words;
-  if (a.one_result) a.block_first = a.tables + size_t(a.n_tables) * p.table_words;
+  a.block_first = a.tables + size_t(a.n_tables) * p.table_words;
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
   a.results = reinterpret_cast<DevResult*>(ws + L.results);
-  a.record = record;
-  HIP_TRY(hipMemcpyAsync(ws + L.tables, src, words * 4, hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemcpyAsync(ws + L.tables, stage, words * 4, hipMemcpyHostToDevice, s));
   HIP_TRY(launch_search(p.n, a, s));
   DevResult r;
   HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  h_out->best_index = r.index;
+  h_out->makespan_us = r.makespan;
+  return SCHED_OK;
+}
+
+// Blocks up to which the host takes the minimum of a search's partials
+// itself: they are written to the call's slot, 16 B each, and no reduction is
+// launched.  As many as fit a slot: whole calls on 8 to 11 tools (26 to 692
+// blocks) took 35.5, 36.8, 41.0 and 46.2 us, against 39.2, 40.4, 44.2 and 48.8
+// with the reduction.
+constexpr uint32_t kHostPartials = 2048;
+static_assert(kHostPartials * sizeof(Partial) <= kSlotBytes, "partials of a small search");
+
+// One search of [lo, hi) in workspace ws (at least one_search_bytes) on stream
+// s, then the result.  record: every mapping's makespan (full ranges only;
+// null: none).  slots: whether the call may use page-locked memory (which the
+// first call allocates); otherwise it allocates nothing.
+int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
+               uint32_t* record, bool slots, sched_result* h_out) {
+  const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
+  SearchArgs a{};
+  if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi))
+    return search_parts(p, lo, hi, ws, s, h_out);
+  plan_search(p, lo, hi, 1, a);
+  const std::vector<uint32_t>& table = a.full_range ? p.table_full : p.table;
+  a.table_stride = p.table_words;
+  a.partials = reinterpret_cast<Partial*>(ws + L.partials);
+  a.results = reinterpret_cast<DevResult*>(ws + L.results);
+  a.record = record;
+  if (fits_arguments(table.data())) {
+    a.host_table = table.data();
+    a.host_words = bound_base(uint32_t(p.n), a.lds_levels);
+  } else {
+    a.tables = reinterpret_cast<const uint32_t*>(ws + L.tables);
+    HIP_TRY(hipMemcpyAsync(ws + L.tables, table.data(), size_t(p.table_words) * 4,
+                           hipMemcpyHostToDevice, s));
+  }
+  DevResult r;
+  std::optional<Slot> slot;
+  if (slots) slot.emplace(s);
+  char* const h = slots ? slot->data() : nullptr;
+  if (h != nullptr) {
+    const bool small = a.n_blocks <= kHostPartials;
+    if (small) {
+      a.partials = reinterpret_cast<Partial*>(h);
+      a.results = nullptr;
+    } else {
+      a.results = reinterpret_cast<DevResult*>(h);
+    }
+    slot->launched();
+    HIP_TRY(launch_search(p.n, a, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    slot->waited();
+    if (small) {
+      const Partial* const part = reinterpret_cast<const Partial*>(h);
+      uint32_t ms = kInf;
+      uint64_t x = ~0ull;
+      for (uint32_t k = 0; k < a.n_blocks; ++k)
+        if (part[k].makespan < ms || (part[k].makespan == ms && part[k].index < x)) {
+          ms = part[k].makespan;
+          x = part[k].index;
+        }
+      r.index = ms == kInf ? ~0ull : x;
+      r.makespan = ms == kInf ? INT64_MAX : int64_t(ms);
+    } else {
+      std::memcpy(&r, h, sizeof(r));
+    }
+  } else {
+    HIP_TRY(launch_search(p.n, a, s));
+    HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  }
   h_out->best_index = r.index;
   h_out->makespan_us = r.makespan;
   return SCHED_OK;
@@ -963,7 +1126,7 @@ int sched_bruteforce_argmin(const sched_problem* p, uint64_t lo, uint64_t hi, vo
   const int rc = check_workspace(d_workspace, ws_bytes, one_search_bytes(*p));
   if (rc != SCHED_OK) return rc;
   return search_one(*p, lo, hi, static_cast<char*>(d_workspace),
-                    reinterpret_cast<hipStream_t>(hip_stream), nullptr, h_out);
+                    reinterpret_cast<hipStream_t>(hip_stream), nullptr, true, h_out);
 }
 
 int sched_bruteforce_argmin_noalloc(const sched_problem* p, uint64_t lo, uint64_t hi,
@@ -974,7 +1137,7 @@ int sched_bruteforce_argmin_noalloc(const sched_problem* p, uint64_t lo, uint64_
   void* ws = nullptr;
   HIP_TRY(scratch_buffer(&ws));
   return search_one(*p, lo, hi, static_cast<char*>(ws), reinterpret_cast<hipStream_t>(hip_stream),
-                    nullptr, h_out);
+                    nullptr, false, h_out);
 }
 
 int sched_bruteforce_record(const sched_problem* p, void* d_workspace, size_t ws_bytes,
@@ -985,7 +1148,7 @@ int sched_bruteforce_record(const sched_problem* p, void* d_workspace, size_t ws
   const int rc = check_workspace(d_workspace, ws_bytes, one_search_bytes(*p));
   if (rc != SCHED_OK) return rc;
   return search_one(*p, 0, p->n_mappings, static_cast<char*>(d_workspace),
-                    reinterpret_cast<hipStream_t>(hip_stream), d_makespan, h_out);
+                    reinterpret_cast<hipStream_t>(hip_stream), d_makespan, true, h_out);
 }
 
 int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
@@ -1104,10 +1267,15 @@ int sched_eval_mappings_device(const sched_problem* p, const uint64_t* d_idx, in
   int rc = check_workspace(d_workspace, ws_bytes, need);
   if (rc != SCHED_OK) return rc;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  HIP_TRY(hipMemcpyAsync(d_workspace, p->table.data(), size_t(p->table_words) * 4,
-                         hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_eval(p->n, static_cast<const uint32_t*>(d_workspace), d_idx, n, p->n_mappings,
-                      d_makespan, uint32_t(p->sharing), s));
+  uint32_t flags = p->sharing ? kEvalSharing : 0u;
+  const uint32_t* tab = p->table.data();
+  if (fits_arguments(tab)) {
+    flags |= kEvalHostTable;
+  } else {
+    HIP_TRY(hipMemcpyAsync(d_workspace, tab, size_t(p->table_words) * 4, hipMemcpyHostToDevice, s));
+    tab = static_cast<const uint32_t*>(d_workspace);
+  }
+  HIP_TRY(launch_eval(p->n, tab, d_idx, n, p->n_mappings, d_makespan, flags, s));
   HIP_TRY(hipStreamSynchronize(s));
   return SCHED_OK;
 }
@@ -1132,16 +1300,12 @@ int sched_eval_mappings(const sched_problem* p, const uint64_t* h_idx, int64_t n
   uint64_t* d_idx = reinterpret_cast<uint64_t*>(ws + head);
   int64_t* d_out = reinterpret_cast<int64_t*>(ws + head + align_up(size_t(chunk) * 8));
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  HIP_TRY(hipMemcpyAsync(ws, p->table.data(), size_t(p->table_words) * 4,
-                         hipMemcpyHostToDevice, s));
   for (int64_t at = 0; at < n; at += chunk) {
     const int64_t m = std::min(chunk, n - at);
-    HIP_TRY(hipMemcpyAsync(d_idx, h_idx + at, size_t(m) * 8, hipMemcpyHostToDevice, s));
-    HIP_TRY(launch_eval(p->n, reinterpret_cast<const uint32_t*>(ws), d_idx, m, p->n_mappings,
-                        d_out, uint32_t(p->sharing), s));
-    HIP_TRY(hipMemcpyAsync(h_makespan + at, d_out, size_t(m) * 8, hipMemcpyDeviceToHost, s));
+    rc = score(*p, p->table.data(), h_idx + at, size_t(m), h_makespan + at,
+               reinterpret_cast<uint32_t*>(ws), d_idx, d_out, s);
+    if (rc != SCHED_OK) return rc;
   }
-  HIP_TRY(hipStreamSynchronize(s));
   return SCHED_OK;
 }
 
@@ -1153,46 +1317,36 @@ int sched_eval_reprobes(const sched_problem* p, uint64_t base_index, const sched
   const int n = p->n;
   const int64_t worst = 1 + 2 * int64_t(n) + int64_t(n) * (n - 1);
   if (capacity < worst) return SCHED_E_SIZE;
-  const Layout L = layout_for(size_t(p->table_words) * 4, partial_capacity(1), 1);
+  const Layout L = layout_for(one_search_tables(*p), partial_capacity(1), 1);
   int rc = check_workspace(d_workspace, ws_bytes, L.total);
   if (rc != SCHED_OK) return rc;
 
   std::vector<uint32_t> table;
   std::vector<uint64_t> idx;
   std::vector<int64_t> ms;
+  std::vector<Cand> cands;
   try {
-    table.assign(p->table_words, 0u);
+    table = p->table;
     idx.reserve(size_t(worst));
+    neighbourhood(*p, base_index, idx, cands);
+    ms.assign(idx.size(), 0);
   } catch (const std::bad_alloc&) {
     return SCHED_E_NOMEM;
   }
   if (lat != nullptr) {
-    rc = build_table(*p, lat, table.data());
+    rc = fill_latencies(*p, lat, table.data(), false);
     if (rc != SCHED_OK) return rc;
-  } else {
-    table = p->table;
-  }
-  std::vector<Cand> cands;
-  try {
-    neighbourhood(*p, base_index, idx, cands);
-  } catch (const std::bad_alloc&) {
-    return SCHED_E_NOMEM;
   }
   const size_t m = idx.size();
-  ms.assign(m, 0);
   // Scratch for the index list and the makespans: the partials region.
   if (m * 16 > partial_capacity(1) * sizeof(Partial)) return SCHED_E_WORKSPACE;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   char* ws = static_cast<char*>(d_workspace);
   uint64_t* d_idx = reinterpret_cast<uint64_t*>(ws + L.partials);
   int64_t* d_ms = reinterpret_cast<int64_t*>(ws + L.partials + m * 8);
-  HIP_TRY(hipMemcpyAsync(ws + L.tables, table.data(), size_t(p->table_words) * 4,
-                         hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(d_idx, idx.data(), m * 8, hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_eval(n, reinterpret_cast<const uint32_t*>(ws + L.tables), d_idx, int64_t(m),
-                      p->n_mappings, d_ms, uint32_t(p->sharing), s));
-  HIP_TRY(hipMemcpyAsync(ms.data(), d_ms, m * 8, hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  rc = score(*p, table.data(), idx.data(), m, ms.data(), reinterpret_cast<uint32_t*>(ws + L.tables),
+             d_idx, d_ms, s);
+  if (rc != SCHED_OK) return rc;
   // Keep a swap only when its move to gpu_now was infeasible.
   int32_t out = 0;
   int64_t move_ms = 0;
@@ -1257,19 +1411,15 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       std::vector<uint64_t> idx;
       std::vector<Cand> cands;
       std::vector<int64_t> ms;
-      HIP_TRY(hipMemcpyAsync(ws + L.tables, p->table.data(), size_t(stride) * 4,
-                             hipMemcpyHostToDevice, s));
       uint64_t x = 0;
       for (int round = 0; round < 4 * n + 4; ++round) {
         neighbourhood(*p, x, idx, cands);
         ms.assign(idx.size(), 0);
         uint64_t* d_idx = reinterpret_cast<uint64_t*>(ws + L.probe_idx);
         int64_t* d_ms = reinterpret_cast<int64_t*>(ws + L.probe_ms);
-        HIP_TRY(hipMemcpyAsync(d_idx, idx.data(), idx.size() * 8, hipMemcpyHostToDevice, s));
-        HIP_TRY(launch_eval(n, d_tab, d_idx, int64_t(idx.size()), p->n_mappings, d_ms,
-                            uint32_t(p->sharing), s));
-        HIP_TRY(hipMemcpyAsync(ms.data(), d_ms, idx.size() * 8, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        rc = score(*p, p->table.data(), idx.data(), idx.size(), ms.data(),
+                   reinterpret_cast<uint32_t*>(ws + L.tables), d_idx, d_ms, s);
+        if (rc != SCHED_OK) return rc;
         ++st.descent_rounds;
         size_t best = 0;
         for (size_t k = 1; k < idx.size(); ++k)
@@ -1291,9 +1441,9 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       if (std::find(pl.prefix.begin(), pl.prefix.end(), v) == pl.prefix.end()) seq.push_back(v);
     set_enumeration(*p, seq, btab.data());
     uint64_t known = 0;
-    for (int32_t v : pl.prefix) known |= 1ull << p->table[kPosBase + v];
+    for (int32_t v : pl.prefix) known |= 1ull << p->table[pos_base(uint32_t(n)) + uint32_t(v)];
     for (int v = 0; v < n; ++v)
-      if (p->radix[v] == 1) known |= 1ull << p->table[kPosBase + v];
+      if (p->radix[v] == 1) known |= 1ull << p->table[pos_base(uint32_t(n)) + uint32_t(v)];
     HIP_TRY(hipMemcpyAsync(ws + L.tables, btab.data(), size_t(stride) * 4, hipMemcpyHostToDevice,
                            s));
     uint32_t* d_count = reinterpret_cast<uint32_t*>(ws + L.bounds);
@@ -1364,7 +1514,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
           y /= p->radix[v];
           base += uint64_t(d) * p->weight[v];
           const int m = mode_of_digit(*p, v, d);
-          const uint64_t b = 1ull << p->table[kPosBase + v];
+          const uint64_t b = 1ull << p->table[pos_base(uint32_t(n)) + uint32_t(v)];
           if (m == 1) gn |= b;
           if (m == 2) gq |= b;
         }

@@ -83,10 +83,8 @@ enum : uint32_t {
   kToolXfer = 2,      // input transfer across devices
   kToolPredLo = 3,    // predecessor mask bits 0..31
   kToolPredHi = 4,    // predecessor mask bits 32..63
-  kToolPredOff = 5,   // offset of the predecessor list (from kPredBase)
-  kToolNPred = 6,     // number of predecessors
-  kToolOrig = 7,      // (original tool number << kOrigLabelBits) | label
-  kToolWords = 8,
+  kToolOrig = 5,      // (original tool number << kOrigLabelBits) | label
+  kToolWords = 6,
 };
 
 // kToolOrig holds the original number above the label, so that the lowest
@@ -96,19 +94,25 @@ constexpr uint32_t kOrigLabelBits = 6;
 constexpr uint32_t kOrigLabelMask = (1u << kOrigLabelBits) - 1u;
 static_assert(kMaxTools <= (1 << kOrigLabelBits), "labels must fit below the original number");
 
+// A table is laid out for n tools: those of its problem, or more where
+// problems of several sizes share one launch (a kernel for n tools then runs
+// a smaller problem with tools n_tools..n-1 on the CPU, of no length).  The
+// layout is as short as the problem allows, so that one table travels in a
+// kernel's arguments (TableArg).
+//
 // pos[v]: internal label of original tool v.
-constexpr uint32_t kPosBase = kHdrWords + kToolWords * kMaxTools;  // 338
+constexpr uint32_t pos_base(uint32_t n) { return kHdrWords + kToolWords * n; }
 // Enumeration order of a search over positions 0..P-1: position p holds the
 // digit of the tool with internal label elab[p], whose weight in the mapping
 // index is ew[p] = W_v of its original number v (two words, low first), and
 // whose options eo[p] give its radix (bits 0-1, 2 or 3) and the mode of
 // digit d in bits 2+2d..3+2d.  Positions 0..J-1 are the inner digits, J.. the
 // outer ones.
-constexpr uint32_t kEnumLabBase = kPosBase + kMaxTools;          // 378
-constexpr uint32_t kEnumWeightBase = kEnumLabBase + kMaxTools;   // 418
-constexpr uint32_t kEnumOptBase = kEnumWeightBase + 2 * kMaxTools;  // 498
-// Predecessor lists (internal labels), then the duration table.
-constexpr uint32_t kPredBase = kEnumOptBase + kMaxTools;  // 538
+constexpr uint32_t enum_lab_base(uint32_t n) { return pos_base(n) + n; }
+constexpr uint32_t enum_weight_base(uint32_t n) { return enum_lab_base(n) + n; }
+constexpr uint32_t enum_opt_base(uint32_t n) { return enum_weight_base(n) + 2u * n; }
+// The duration table follows.
+constexpr uint32_t dur_base(uint32_t n) { return enum_opt_base(n) + n; }
 
 // Radix and digit -> mode of an enumeration position's options word.
 inline constexpr uint32_t opt_radix(uint32_t o) { return o & 3u; }
@@ -117,23 +121,36 @@ inline constexpr uint32_t opt_mode(uint32_t o, uint32_t d) { return (o >> (2u + 
 // Duration table: dur[(i * 2 + q) * levels + (level - 1)] for internal label
 // i, q = 0 for gpu_now (base gpu_us), q = 1 for gpu_queue (gpu_us + load_us).
 //
-// Bound table (after the duration table): for internal label i, four words
-// bt[4i + m] = the shortest duration tool i can have in mode m (cpu, gpu_now,
-// gpu_queue: the least over contention levels), and bt[4i + 3] = the least
-// of those over the modes the problem allows it; kInf for a GPU mode of a
-// tool whose footprint exceeds the budget (it can never run there).
-constexpr uint32_t kBoundWords = 4;
-
-// Processor-sharing table (after the bound table): for internal label i,
+// Processor-sharing table (after the duration table): for internal label i,
 // b[2i] = gpu_us and b[2i + 1] = gpu_us + load_us (isolated latencies), then
 // for each contention level the work rate w = round(2^32 / F) in 2^-16 us of
 // isolated work per us, then for each level floor(2^48 / w) (two words, low
 // first), the reciprocal the device divides by.
-inline uint32_t table_words(int n, int n_preds, int levels) {
-  uint32_t dur_off = kPredBase + ((uint32_t(n_preds) + 3u) & ~3u);
-  return dur_off + uint32_t(n) * 2u * uint32_t(levels) + kBoundWords * uint32_t(n) +
-         2u * uint32_t(n) + 3u * uint32_t(levels);
+//
+// Bound table (last; only the bound kernel and the host read it): for internal
+// label i, four words bt[4i + m] = the shortest duration tool i can have in
+// mode m (cpu, gpu_now, gpu_queue: the least over contention levels), and
+// bt[4i + 3] = the least of those over the modes the problem allows it; kInf
+// for a GPU mode of a tool whose footprint exceeds the budget (it can never
+// run there).
+constexpr uint32_t kBoundWords = 4;
+
+constexpr uint32_t share_base(uint32_t n, uint32_t levels) {
+  return dur_base(n) + n * 2u * levels;
 }
+constexpr uint32_t bound_base(uint32_t n, uint32_t levels) {
+  return share_base(n, levels) + 2u * n + 3u * levels;
+}
+constexpr uint32_t table_words(uint32_t n, uint32_t levels) {
+  return bound_base(n, levels) + kBoundWords * n;
+}
+
+// One table (without its bound table) in a kernel's arguments, which saves a
+// small call its copy to the device.
+constexpr uint32_t kArgWords = 960;
+struct TableArg {
+  uint32_t w[kArgWords];
+};
 
 struct Partial {
   uint64_t index;
@@ -147,15 +164,19 @@ struct DevResult {
 };
 
 struct SearchArgs {
-  const uint32_t* tables;     // n_tables tables, table_stride words apart
+  const uint32_t* tables;     // n_tables tables, table_stride words apart; null: one table,
+                              // in the kernel's arguments
+  const uint32_t* host_table; // that table on the host, host_words of it
   Partial* partials;          // one per block
-  DevResult* results;         // one per table, or one for all of them (one_result)
+  DevResult* results;         // one per table, or one for all of them (one_result); null:
+                              // the caller reduces the partials
   const uint32_t* block_first;  // n_tables + 1 entries: the first block of each table, then
                               // the number of blocks; null: blocks_per_table each
   uint64_t lo, hi;            // index range searched in every table
   uint64_t outer_lo;          // first outer combination
   uint64_t n_outer;           // outer combinations covering [lo, hi)
   uint32_t table_stride;
+  uint32_t host_words;
   uint32_t n_tables;
   uint32_t inner_digits;      // J: enumeration positions 0..J-1 are walked per lane
   uint32_t inner_count;       // product of the radices of positions 0..J-1
@@ -171,6 +192,19 @@ struct SearchArgs {
   uint32_t one_result;        // 1: the tables are parts of one search, results has one entry
   uint32_t* record;           // full range, one table: every scored mapping's makespan
                               // (kInf if infeasible) goes to record[index]; null: none
+};
+
+// Scoring of explicit indices.
+struct EvalArgs {
+  const uint32_t* tab;        // null: the table in the kernel's arguments
+  const uint64_t* idx;
+  int64_t n;
+  uint64_t n_mappings;
+  int64_t* out;
+};
+enum : uint32_t {
+  kEvalSharing = 1u,          // processor sharing
+  kEvalHostTable = 2u,        // tab is the host's table, to go into the kernel's arguments
 };
 
 }  // namespace devmap

@@ -15,8 +15,7 @@ namespace devmap {
 template <int N>
 hipError_t launch_search_n(const SearchArgs& a, hipStream_t s);
 template <int N>
-hipError_t launch_eval_n(const uint32_t* tab, const uint64_t* idx, int64_t n, uint64_t n_mappings,
-                         int64_t* out, uint32_t sharing, hipStream_t s);
+hipError_t launch_eval_n(const EvalArgs& e, uint32_t host_words, uint32_t flags, hipStream_t s);
 template <int N>
 hipError_t launch_bound_n(const uint32_t* tab, uint32_t K, uint64_t known, int64_t n,
                           uint32_t ub, uint32_t* count, uint2* out, hipStream_t s);
@@ -55,8 +54,7 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_kernel(const Partial* _
 }
 
 using SearchFn = hipError_t (*)(const SearchArgs&, hipStream_t);
-using EvalFn = hipError_t (*)(const uint32_t*, const uint64_t*, int64_t, uint64_t, int64_t*,
-                              uint32_t, hipStream_t);
+using EvalFn = hipError_t (*)(const EvalArgs&, uint32_t, uint32_t, hipStream_t);
 
 template <size_t... I>
 static constexpr auto make_search_table(std::index_sequence<I...>) {
@@ -79,7 +77,7 @@ static const auto kBoundFns = make_bound_table(std::make_index_sequence<kMaxTool
 
 hipError_t launch_search(int n_tools, const SearchArgs& a, hipStream_t s) {
   const hipError_t e = kSearchFns[n_tools - 1](a, s);
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || a.results == nullptr) return e;
   const uint32_t results = a.one_result ? 1u : a.n_tables;
   hipLaunchKernelGGL(reduce_kernel, dim3(results), dim3(kReduceThreads), 0, s, a.partials,
                      a.one_result ? nullptr : a.block_first, a.n_blocks / results, a.results);
@@ -87,8 +85,11 @@ hipError_t launch_search(int n_tools, const SearchArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_eval(int n_tools, const uint32_t* tab, const uint64_t* idx, int64_t n,
-                       uint64_t n_mappings, int64_t* out, uint32_t sharing, hipStream_t s) {
-  return kEvalFns[n_tools - 1](tab, idx, n, n_mappings, out, sharing, s);
+                       uint64_t n_mappings, int64_t* out, uint32_t flags, hipStream_t s) {
+  const EvalArgs e{tab, idx, n, n_mappings, out};
+  const uint32_t words =
+      flags & kEvalHostTable ? bound_base(uint32_t(n_tools), tab[kHdrLevels]) : 0u;
+  return kEvalFns[n_tools - 1](e, words, flags, s);
 }
 
 hipError_t launch_bound(int n_tools, const uint32_t* tab, uint32_t K, uint64_t known, int64_t n,

@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include <array>
+#include <cstring>
 #include <type_traits>
 #include <utility>
 
@@ -928,13 +929,13 @@ __host__ __device__ __forceinline__ void decode_positions(const uint32_t* __rest
   gq = load_mask<N>(Tab{tab}, kHdrFixGqLo);
   x = uint64_t(tab[kHdrBaseLo]) | (uint64_t(tab[kHdrBaseHi]) << 32);
   for (uint32_t p = p0; p < p1; ++p) {
-    const uint32_t o = tab[kEnumOptBase + p];
+    const uint32_t o = tab[enum_opt_base(N) + p];
     const uint64_t q = opt_radix(o) == 3u ? y / 3u : y >> 1;
     const uint32_t d = uint32_t(y - uint64_t(opt_radix(o)) * q);
     const uint32_t m = opt_mode(o, d);
-    const M b = M(1) << tab[kEnumLabBase + p];
-    const uint64_t w = uint64_t(tab[kEnumWeightBase + 2 * p]) |
-                       (uint64_t(tab[kEnumWeightBase + 2 * p + 1]) << 32);
+    const M b = M(1) << tab[enum_lab_base(N) + p];
+    const uint64_t w = uint64_t(tab[enum_weight_base(N) + 2 * p]) |
+                       (uint64_t(tab[enum_weight_base(N) + 2 * p + 1]) << 32);
     // (selects, not branches: a branch per mask let the optimiser pick the
     // mask through a pointer, which put both masks in scratch memory)
     gn |= m == 1u ? b : M(0);
@@ -1060,8 +1061,8 @@ __host__ __device__ __forceinline__ void lane_search(const Walk& a,
   uint32_t idig = 0;
   I xi = 0;
   for (uint32_t j = 0; j < J; ++j) {
-    const uint32_t m = opt_mode(tab[kEnumOptBase + j], 0u);
-    const M b = M(1) << tab[kEnumLabBase + j];
+    const uint32_t m = opt_mode(tab[enum_opt_base(N) + j], 0u);
+    const M b = M(1) << tab[enum_lab_base(N) + j];
     if (m == 1u) ign |= b;
     if (m == 2u) igq |= b;
   }
@@ -1090,11 +1091,11 @@ __host__ __device__ __forceinline__ void lane_search(const Walk& a,
     }
     // odometer step on the inner digits
     for (uint32_t j = 0; j < J; ++j) {
-      const uint32_t o = tab[kEnumOptBase + j];
+      const uint32_t o = tab[enum_opt_base(N) + j];
       const uint32_t d = (idig >> (2u * j)) & 3u;
-      const M b = M(1) << tab[kEnumLabBase + j];
-      const I w = I(uint64_t(tab[kEnumWeightBase + 2 * j]) |
-                    (uint64_t(tab[kEnumWeightBase + 2 * j + 1]) << 32));
+      const M b = M(1) << tab[enum_lab_base(N) + j];
+      const I w = I(uint64_t(tab[enum_weight_base(N) + 2 * j]) |
+                    (uint64_t(tab[enum_weight_base(N) + 2 * j + 1]) << 32));
       ign &= ~b;
       igq &= ~b;
       const bool carry = d + 1u == opt_radix(o);
@@ -1377,7 +1378,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
   const Tab tu{tab};
   M inner = 0;
 #pragma unroll
-  for (uint32_t j = 0; j < J; ++j) inner |= M(1) << tu[kEnumLabBase + j];
+  for (uint32_t j = 0; j < J; ++j) inner |= M(1) << tu[enum_lab_base(N) + j];
   const M big = load_mask<N>(tu, kHdrBigLo);
 
   using S = typename std::conditional<SHARE, SimPS<N>, Sim<N>>::type;
@@ -1436,12 +1437,12 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
   const uint32_t owner_of_rank = push(wl, pstar >= 0 ? rk : nv + wl - rk);
   // Inner combinations: C of them, positions 0 and 1 of radices r0, r1.
   const uint32_t C = walk_inner_count(a);
-  const uint32_t o0 = tab[kEnumOptBase + 0], o1 = J > 1 ? tab[kEnumOptBase + 1] : 0u;
+  const uint32_t o0 = tab[enum_opt_base(N) + 0], o1 = J > 1 ? tab[enum_opt_base(N) + 1] : 0u;
   const uint32_t r0 = opt_radix(o0);
-  const M b0 = M(1) << tab[kEnumLabBase + 0];
-  const M b1 = J > 1 ? M(1) << tab[kEnumLabBase + 1] : M(0);
-  const I w0 = I(uint64_t(tab[kEnumWeightBase + 0]) | (uint64_t(tab[kEnumWeightBase + 1]) << 32));
-  const I w1 = J > 1 ? I(uint64_t(tab[kEnumWeightBase + 2]) | (uint64_t(tab[kEnumWeightBase + 3]) << 32))
+  const M b0 = M(1) << tab[enum_lab_base(N) + 0];
+  const M b1 = J > 1 ? M(1) << tab[enum_lab_base(N) + 1] : M(0);
+  const I w0 = I(uint64_t(tab[enum_weight_base(N) + 0]) | (uint64_t(tab[enum_weight_base(N) + 1]) << 32));
+  const I w1 = J > 1 ? I(uint64_t(tab[enum_weight_base(N) + 2]) | (uint64_t(tab[enum_weight_base(N) + 3]) << 32))
                      : I(0);
   const uint32_t pairs = nv * C;
   constexpr uint32_t W = wave_lanes();
@@ -1495,6 +1496,20 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
   if (best_ms != kInf) best_x = bx;
 }
 
+// The given table, or (null) the TableArg behind `args` bytes of the kernel's
+// arguments, where they lie: a by-value struct that is indexed would be copied
+// to scratch memory first.  Both are taken as global pointers, so that the
+// compiler need not treat reads through the result as flat.
+__device__ __forceinline__ const uint32_t* table_or_args(const uint32_t* table, uint32_t args) {
+  typedef const __attribute__((address_space(4))) char* ConstBytes;
+  typedef const __attribute__((address_space(1))) uint32_t* Global;
+  const ConstBytes arg = (ConstBytes)__builtin_amdgcn_kernarg_segment_ptr() + args;
+  const Global g = table != nullptr ? (Global)table : (Global)(uint64_t)arg;
+  return (const uint32_t*)g;
+}
+static_assert(sizeof(SearchArgs) % 8 == 0 && sizeof(EvalArgs) % 8 == 0 &&
+              sizeof(SearchArgs) + sizeof(TableArg) <= 4096, "kernel arguments");
+
 // Exhaustive search.  Block b serves table b / blocks_per_table and walks its
 // work items (kBlock consecutive outer combinations each) with a stride of
 // blocks_per_table.  Each lane keeps its own (makespan, index) minimum; the
@@ -1508,7 +1523,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
                      // per lane) leaves LDS for 5 blocks per CU
                      : (FULL && N >= kCompactSnapN && N <= kPrefixMaxN ? 5
                                                                         : DEVMAP_SEARCH_WAVES_LARGE))))) void
-search_kernel(SearchArgs a) {
+search_kernel(SearchArgs a, TableArg) {
   // the staged tables: lds_words_for(N, a.lds_levels) words, sized at launch
   extern __shared__ uint32_t s_lds[];
   __shared__ uint64_t s_wave_words[kBlock / 64];  // one 8-byte word per wave
@@ -1533,7 +1548,9 @@ search_kernel(SearchArgs a) {
     table = blockIdx.x / nb;
     bb = blockIdx.x - table * nb;
   }
-  const uint32_t* tab = a.tables + size_t(table) * a.table_stride;
+  const uint32_t* tab = table_or_args(
+      a.tables != nullptr ? a.tables + size_t(table) * a.table_stride : nullptr,
+      sizeof(SearchArgs));
   stage_tables<N>(tab, s_lds);
 
   uint32_t best_ms = kInf;
@@ -1574,10 +1591,8 @@ search_kernel(SearchArgs a) {
 
 // Score explicit indices (grid-stride).
 template <int N, bool SHARE>
-__global__ __launch_bounds__(kBlock) void eval_kernel(const uint32_t* __restrict__ tab,
-                                                      const uint64_t* __restrict__ idx,
-                                                      int64_t n, uint64_t n_mappings,
-                                                      int64_t* __restrict__ out) {
+__global__ __launch_bounds__(kBlock) void eval_kernel(EvalArgs a, TableArg) {
+  const uint32_t* const tab = table_or_args(a.tab, sizeof(EvalArgs));
   using M = MaskT<N>;
   __shared__ uint32_t s_lds[lds_words<N>()];
   __shared__ uint64_t s_wave_words[kBlock / 64];  // one 8-byte word per wave
@@ -1585,11 +1600,11 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const uint32_t* __restrict
   stage_tables<N>(tab, s_lds);
   const uint32_t levels = tab[kHdrLevels];
   const uint32_t budget = tab[kHdrBudget];
-  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < n;
+  for (int64_t i = int64_t(blockIdx.x) * kBlock + threadIdx.x; i < a.n;
        i += int64_t(gridDim.x) * kBlock) {
-    const uint64_t x = idx[i];
+    const uint64_t x = a.idx[i];
     int64_t r = INT64_MAX;
-    if (x < n_mappings) {
+    if (x < a.n_mappings) {
       M gn, gq;
       uint64_t xw;
       decode_positions<N>(tab, x, 0, tab[kHdrPositions], gn, gq, xw);
@@ -1600,7 +1615,7 @@ __global__ __launch_bounds__(kBlock) void eval_kernel(const uint32_t* __restrict
         ms = evaluate<N>(tab, s_lds, levels, budget, gn, gq, slot);
       if (ms != kInf) r = int64_t(ms);
     }
-    out[i] = r;
+    a.out[i] = r;
   }
 }
 
@@ -1674,16 +1689,21 @@ hipError_t launch_search_n(const SearchArgs& a, hipStream_t s) {
   const uint32_t blocks = a.n_blocks;
   if (a.lds_levels < 1 || a.lds_levels > lds_levels<N>()) return hipErrorInvalidValue;
   const size_t shm = size_t(lds_words_for(N, a.lds_levels)) * 4u;
+  TableArg t;
+  if (a.tables == nullptr) {
+    if (a.host_words > kArgWords) return hipErrorInvalidValue;
+    memcpy(t.w, a.host_table, size_t(a.host_words) * 4u);
+  }
   if (a.sharing) {
     if (a.full_range)
-      hipLaunchKernelGGL((search_kernel<N, true, true>), dim3(blocks), dim3(kBlock), shm, s, a);
+      hipLaunchKernelGGL((search_kernel<N, true, true>), dim3(blocks), dim3(kBlock), shm, s, a, t);
     else
-      hipLaunchKernelGGL((search_kernel<N, false, true>), dim3(blocks), dim3(kBlock), shm, s, a);
+      hipLaunchKernelGGL((search_kernel<N, false, true>), dim3(blocks), dim3(kBlock), shm, s, a, t);
   } else {
     if (a.full_range)
-      hipLaunchKernelGGL((search_kernel<N, true, false>), dim3(blocks), dim3(kBlock), shm, s, a);
+      hipLaunchKernelGGL((search_kernel<N, true, false>), dim3(blocks), dim3(kBlock), shm, s, a, t);
     else
-      hipLaunchKernelGGL((search_kernel<N, false, false>), dim3(blocks), dim3(kBlock), shm, s, a);
+      hipLaunchKernelGGL((search_kernel<N, false, false>), dim3(blocks), dim3(kBlock), shm, s, a, t);
   }
   return hipGetLastError();
 }
@@ -1700,18 +1720,21 @@ hipError_t launch_bound_n(const uint32_t* tab, uint32_t K, uint64_t known, int64
 }
 
 template <int N>
-hipError_t launch_eval_n(const uint32_t* tab, const uint64_t* idx, int64_t n,
-                                uint64_t n_mappings, int64_t* out, uint32_t sharing,
-                                hipStream_t s) {
-  int64_t blocks = (n + kBlock - 1) / kBlock;
+hipError_t launch_eval_n(const EvalArgs& e, uint32_t host_words, uint32_t flags, hipStream_t s) {
+  int64_t blocks = (e.n + kBlock - 1) / kBlock;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
-  if (sharing)
-    hipLaunchKernelGGL((eval_kernel<N, true>), dim3(uint32_t(blocks)), dim3(kBlock), 0, s, tab,
-                       idx, n, n_mappings, out);
+  EvalArgs a = e;
+  TableArg t;
+  if (flags & kEvalHostTable) {
+    if (host_words > kArgWords) return hipErrorInvalidValue;
+    memcpy(t.w, a.tab, size_t(host_words) * 4u);
+    a.tab = nullptr;
+  }
+  if (flags & kEvalSharing)
+    hipLaunchKernelGGL((eval_kernel<N, true>), dim3(uint32_t(blocks)), dim3(kBlock), 0, s, a, t);
   else
-    hipLaunchKernelGGL((eval_kernel<N, false>), dim3(uint32_t(blocks)), dim3(kBlock), 0, s, tab,
-                       idx, n, n_mappings, out);
+    hipLaunchKernelGGL((eval_kernel<N, false>), dim3(uint32_t(blocks)), dim3(kBlock), 0, s, a, t);
   return hipGetLastError();
 }
 

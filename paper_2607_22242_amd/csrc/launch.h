@@ -6,10 +6,13 @@
 
 namespace devmap {
 
-// The search over a.tables and the reduction of its partials into a.results.
+// The search over a.tables (or a.host_table) and the reduction of its partials
+// into a.results, if given.
 hipError_t launch_search(int n_tools, const SearchArgs& a, hipStream_t s);
+// flags: kEval*.  With kEvalHostTable, tab is the host's copy of a table of at
+// most kArgWords words up to its bound table.
 hipError_t launch_eval(int n_tools, const uint32_t* tab, const uint64_t* idx, int64_t n,
-                       uint64_t n_mappings, int64_t* out, uint32_t sharing, hipStream_t s);
+                       uint64_t n_mappings, int64_t* out, uint32_t flags, hipStream_t s);
 hipError_t launch_bound(int n_tools, const uint32_t* tab, uint32_t K, uint64_t known, int64_t n,
                         uint32_t ub, uint32_t* count, uint2* out, hipStream_t s);
 // Bytes of the per-GPU scratch array of the entry point that allocates
