@@ -348,22 +348,31 @@ static bool inner_last(const sched_problem& p) {
 // kSharedInner inner digits on the deepest tools (the kernel then computes
 // each lane's schedule prefix once for all of their modes) and the next four
 // deepest on the lanes: the plain deepest-first order.
-bool prefix_plan(const sched_problem& p, uint64_t n_tables) {
-  if (p.n > (p.sharing ? kPrefixMaxNShare : kPrefixMaxN) || p.enum_tools.size() < kSharedInner)
+// prefix_able: the kernel for `lay` tools has shared prefixes for the problem.
+bool prefix_able(const sched_problem& p, int lay) {
+  if (lay > (p.sharing ? kPrefixMaxNShare : kPrefixMaxN) || p.enum_tools.size() < kSharedInner)
     return false;
   // from kCompactSnapN tools the kernel's LDS column leaves out the last labels
-  if (p.n >= kCompactSnapN && !inner_last(p)) return false;
-  if (p.free_fanout) return false;  // scored in closed form, nothing to share
-  // enough lanes left to fill the GPU with kSharedInner inner digits
-  const std::vector<int32_t>& v = p.late;
+  if (lay >= kCompactSnapN && (p.n != lay || !inner_last(p))) return false;
+  return !p.free_fanout;  // scored in closed form, nothing to share
+}
+
+// Combinations of a shared-prefix search's inner digits.
+uint64_t shared_inner_count(const sched_problem& p) {
   uint64_t inner = 1;
   int taken = 0;
-  for (int32_t t : v)
+  for (int32_t t : p.late)
     if (p.radix[t] > 1 && taken < int(kSharedInner)) {
       inner *= p.radix[t];
       ++taken;
     }
-  return (unsigned __int128)(p.n_mappings / inner) * n_tables >= kTargetLanes;
+  return inner;
+}
+
+bool prefix_plan(const sched_problem& p, uint64_t n_tables) {
+  // enough lanes left to fill the GPU with kSharedInner inner digits
+  return prefix_able(p, p.n) &&
+         (unsigned __int128)(p.n_mappings / shared_inner_count(p)) * n_tables >= kTargetLanes;
 }
 
 Seq enumeration(const sched_problem& p, bool full, int J, bool prefix) {
@@ -382,14 +391,6 @@ Seq enumeration(const sched_problem& p, bool full, int J, bool prefix) {
   for (int k = 0; k < lanes; ++k) seq.push_back(late[k]);
   for (int k = lanes + J; k < P; ++k) seq.push_back(late[k]);
   return seq;
-}
-
-// Replicas whose problems share this key share one search plan.
-std::vector<uint8_t> plan_key(const sched_problem& p) {
-  std::vector<uint8_t> k{uint8_t(p.n), uint8_t(p.sharing), uint8_t(p.free_fanout)};
-  for (int32_t v : p.late)
-    if (p.radix[v] > 1) k.push_back(p.radix[v]);
-  return k;
 }
 
 uint64_t inner_count(const sched_problem& p, const Seq& seq, int J) {
@@ -509,9 +510,7 @@ int split_range(const sched_problem& p, uint64_t lo, uint64_t hi, Part* out) {
 // order is the shorter chain.  145 M of 3^19 mappings (mixed DAG): 3.97 ms in parts,
 // 19.9 ms in index order.
 bool range_in_parts(const sched_problem& p, uint64_t lo, uint64_t hi) {
-  if (p.n > (p.sharing ? kPrefixMaxNShare : kPrefixMaxN) || p.n >= kCompactSnapN ||
-      p.enum_tools.size() < kSharedInner || p.free_fanout)
-    return false;
+  if (p.n >= kCompactSnapN || !prefix_able(p, p.n)) return false;
   uint64_t inner = 1;
   for (uint32_t j = 0; j < kSharedInner; ++j) inner *= 3;
   return (hi - lo) / inner >= kTargetLanes &&
@@ -965,6 +964,106 @@ int search_parts(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hip
   return SCHED_OK;
 }
 
+// One launch of a batch: replicas [first, last) of the launch order, on the
+// kernel for `lay` tools.
+struct Launch {
+  size_t first, last;
+  int lay;
+  uint64_t work;  // mappings of its replicas
+  SearchArgs a;
+};
+
+// Words between the tables of a batch of these problems: any of them may be
+// laid out for the most tools among them.
+size_t batch_stride(const sched_problem* const* problems, int32_t n_problems) {
+  uint32_t lay = 1, levels = 1;
+  for (int32_t i = 0; i < n_problems; ++i) {
+    lay = std::max(lay, uint32_t(problems[i]->n));
+    levels = std::max(levels, table_levels(*problems[i]));
+  }
+  return bound_base(lay, levels);
+}
+
+// Bytes of a batch's tables and of its launches' first blocks (one more entry
+// than tables per launch, at most one launch per table).
+size_t batch_table_bytes(size_t stride, size_t n_replicas) {
+  return (n_replicas * stride + 2 * n_replicas) * 4;
+}
+
+// Launches of a batch.  Replicas of one tool count and contention reading
+// share a launch, whatever their shapes, masks and sizes.  A launch that would
+// leave the GPU partly idle (fewer mappings than kTargetLanes lanes) joins the
+// next larger tool count: its tables are laid out for more tools, at the cost
+// of one more resolution per added tool, instead of a launch in series.  13
+// scenarios of 4 to 9 tools, 8 replicas each: 108 us in one launch, 320 us in
+// eleven.
+void plan_batch(const sched_problem* const* problems, int32_t n_problems,
+                const int32_t* replica_problem, size_t R, std::vector<Launch>& launches,
+                std::vector<int32_t>& order) {
+  order.resize(R);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+    const int32_t a = replica_problem[x], b = replica_problem[y];
+    if (problems[a]->sharing != problems[b]->sharing)
+      return problems[a]->sharing < problems[b]->sharing;
+    if (problems[a]->n != problems[b]->n) return problems[a]->n < problems[b]->n;
+    return a < b;
+  });
+  (void)n_problems;
+  for (size_t i = 0; i < R; ++i) {
+    const sched_problem& p = *problems[replica_problem[order[i]]];
+    Launch* const g = launches.empty() ? nullptr : &launches.back();
+    if (g == nullptr || g->a.sharing != uint32_t(p.sharing) ||
+        (g->lay != p.n && g->work >= kTargetLanes)) {
+      Launch n{i, i, p.n, 0, SearchArgs{}};
+      n.a.full_range = 1;
+      n.a.sharing = uint32_t(p.sharing);
+      launches.push_back(n);
+    }
+    Launch& l = launches.back();
+    l.lay = p.n;
+    l.last = i + 1;
+    l.work += p.n_mappings;
+    l.a.n_tables = uint32_t(l.last - l.first);
+  }
+}
+
+// The table of problem p in a launch, without latencies: laid out for the
+// launch's tools, enumerated and walked for its work in all.
+int lay_replica(const sched_problem& p, const Launch& g, uint32_t* table) {
+  const int rc = lay_table(p, uint32_t(g.lay), table);
+  if (rc != SCHED_OK) return rc;
+  SearchArgs w{};
+  const uint64_t shared = shared_inner_count(p);
+  // (a problem smaller than one wave of prefixes has nothing to gain)
+  w.prefix = prefix_able(p, g.lay) && g.work / shared >= kTargetLanes &&
+             p.n_mappings / shared >= 64u;
+  int J = 0;
+  if (w.prefix) {
+    J = int(kSharedInner);
+  } else {
+    while (J < kMaxInnerDigits && J < int(p.enum_tools.size())) {
+      const uint64_t next = inner_count(p, enumeration(p, true, J + 1, false), J + 1);
+      if ((unsigned __int128)next * kTargetLanes > g.work) break;
+      ++J;
+    }
+  }
+  const Seq seq = enumeration(p, true, J, w.prefix != 0);
+  const uint64_t inner = inner_count(p, seq, J);
+  w.inner_digits = uint32_t(J);
+  w.inner_count = uint32_t(inner);
+  w.n_outer = p.n_mappings / inner;
+  set_enumeration(p, seq, table);
+  write_walk(w, table);
+  return SCHED_OK;
+}
+
+// Work items (kBlock outer combinations) of a table's walk.
+uint64_t table_items(const uint32_t* table) {
+  const uint64_t n = uint64_t(table[kHdrNOuterLo]) | (uint64_t(table[kHdrNOuterHi]) << 32);
+  return (n + kBlock - 1) / kBlock;
+}
+
 // Blocks up to which the host takes the minimum of a search's partials
 // itself: they are written to the call's slot, 16 B each, and no reduction is
 // launched.  As many as fit a slot: whole calls on 8 to 11 tools (26 to 692
@@ -1105,15 +1204,15 @@ int sched_workspace_bytes(const sched_problem* const* problems, int32_t n_proble
                           int32_t n_replicas, size_t* out) {
   if (problems == nullptr || out == nullptr) return SCHED_E_NULL;
   if (n_problems < 1 || n_replicas < 0) return SCHED_E_SIZE;
-  size_t max_stride = 0, need = 0;
+  size_t need = 0;
   for (int32_t i = 0; i < n_problems; ++i) {
     if (problems[i] == nullptr) return SCHED_E_NULL;
-    max_stride = std::max<size_t>(max_stride, problems[i]->table_words);
     need = std::max(need, one_search_bytes(*problems[i]));  // single-problem calls
   }
   if (n_replicas > 0) {
     const size_t r = size_t(n_replicas);
-    need = std::max(need, layout_for(r * max_stride * 4, partial_capacity(r), r).total);
+    need = std::max(need, layout_for(batch_table_bytes(batch_stride(problems, n_problems), r),
+                                     partial_capacity(r), r).total);
   }
   *out = need;
   return SCHED_OK;
@@ -1159,99 +1258,93 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
       h_out == nullptr)
     return SCHED_E_NULL;
   if (n_problems < 1 || n_replicas < 1) return SCHED_E_SIZE;
-  size_t max_stride = 0;
-  for (int32_t i = 0; i < n_problems; ++i) {
+  for (int32_t i = 0; i < n_problems; ++i)
     if (problems[i] == nullptr) return SCHED_E_NULL;
-    max_stride = std::max<size_t>(max_stride, problems[i]->table_words);
-  }
-  std::vector<size_t> lat_off(static_cast<size_t>(n_replicas));
-  size_t off = 0;
-  for (int32_t r = 0; r < n_replicas; ++r) {
-    const int32_t pi = replica_problem[r];
-    if (pi < 0 || pi >= n_problems) return SCHED_E_RANGE;
-    lat_off[r] = off;
-    off += size_t(problems[pi]->n);
-  }
   const size_t R = size_t(n_replicas);
-  const Layout L = layout_for(R * max_stride * 4, partial_capacity(R), R);
+  for (size_t r = 0; r < R; ++r)
+    if (replica_problem[r] < 0 || replica_problem[r] >= n_problems) return SCHED_E_RANGE;
+  const size_t stride = batch_stride(problems, n_problems);
+  const Layout L = layout_for(batch_table_bytes(stride, R), partial_capacity(R), R);
   int rc = check_workspace(d_workspace, ws_bytes, L.total);
   if (rc != SCHED_OK) return rc;
 
-  // Replicas grouped by search plan: tool count (one kernel instantiation
-  // per count) and the radices along the enumeration order, which fix the
-  // inner digits and the outer combinations.
-  std::vector<std::vector<uint8_t>> keys(static_cast<size_t>(n_problems));
-  for (int32_t i = 0; i < n_problems; ++i) keys[size_t(i)] = plan_key(*problems[i]);
-  std::vector<int32_t> order(R);
-  std::iota(order.begin(), order.end(), 0);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-    return keys[size_t(replica_problem[x])] < keys[size_t(replica_problem[y])];
-  });
-  std::vector<uint32_t> host_tables;
-  std::vector<DevResult> host_res;
+  hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
+  char* const ws = static_cast<char*>(d_workspace);
+  uint32_t* const d_tables = reinterpret_cast<uint32_t*>(ws + L.tables);
   try {
-    host_tables.assign(R * max_stride, 0u);
-    host_res.resize(R);
+    std::vector<size_t> lat_off(R);
+    size_t off = 0;
+    for (size_t r = 0; r < R; ++r) {
+      lat_off[r] = off;
+      off += size_t(problems[replica_problem[r]]->n);
+    }
+    std::vector<Launch> launches;
+    std::vector<int32_t> order;  // replicas in launch order
+    plan_batch(problems, n_problems, replica_problem, R, launches, order);
+
+    // The tables: what does not depend on latencies once per problem, then
+    // each replica's latencies; behind them each launch's first blocks.
+    std::vector<uint32_t> host(batch_table_bytes(stride, R) / 4);
+    std::vector<uint32_t> laid(stride + kBoundWords * kMaxTools);  // (with room for a bound table)
+    uint32_t* first = host.data() + R * stride;
+    for (Launch& g : launches) {
+      const sched_problem* built = nullptr;
+      for (size_t i = g.first; i < g.last; ++i) {
+        const int32_t r = order[i];
+        const sched_problem& p = *problems[replica_problem[r]];
+        uint32_t* const tb = host.data() + i * stride;
+        if (&p != built) {
+          rc = lay_replica(p, g, laid.data());
+          if (rc != SCHED_OK) return rc;
+          built = &p;
+        }
+        std::copy_n(laid.data(), bound_base(uint32_t(g.lay), laid[kHdrLevels]), tb);
+        rc = fill_latencies(p, replica_lat + lat_off[r], tb, false);
+        if (rc != SCHED_OK) return rc;
+        g.a.lds_levels = std::max(g.a.lds_levels, table_levels(p));
+      }
+      // Blocks in proportion to the tables' mappings, one per work item at
+      // most and at least one each.
+      const uint64_t most = partial_capacity(R), count = g.last - g.first;
+      uint32_t blocks = 0;
+      for (size_t i = g.first; i < g.last; ++i) {
+        const unsigned __int128 m = problems[replica_problem[order[i]]]->n_mappings;
+        const uint64_t share = uint64_t(m * (most - count) / g.work) + 1;
+        *first++ = blocks;
+        blocks += uint32_t(std::min(table_items(host.data() + i * stride), share));
+      }
+      *first++ = blocks;
+      g.a.n_blocks = blocks;
+    }
+
+    HIP_TRY(hipMemcpyAsync(d_tables, host.data(), host.size() * 4, hipMemcpyHostToDevice, s));
+    Slot slot(s);
+    char* const h = R * sizeof(DevResult) <= kSlotBytes ? slot.data() : nullptr;
+    DevResult* const results = reinterpret_cast<DevResult*>(h ? h : ws + L.results);
+    const uint32_t* d_first = d_tables + R * stride;
+    if (h) slot.launched();
+    for (Launch& g : launches) {
+      SearchArgs& a = g.a;
+      a.tables = d_tables + g.first * stride;
+      a.table_stride = uint32_t(stride);
+      a.block_first = d_first;
+      a.partials = reinterpret_cast<Partial*>(ws + L.partials);
+      a.results = results + g.first;
+      HIP_TRY(launch_search(g.lay, a, s));
+      d_first += g.last - g.first + 1;
+    }
+    std::vector<DevResult> res(R);
+    if (!h)
+      HIP_TRY(hipMemcpyAsync(res.data(), results, R * sizeof(DevResult), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    slot.waited();
+    if (h) std::memcpy(res.data(), h, R * sizeof(DevResult));
+    for (size_t i = 0; i < R; ++i) {
+      h_out[order[i]].best_index = res[i].index;
+      h_out[order[i]].makespan_us = res[i].makespan;
+    }
   } catch (const std::bad_alloc&) {
     return SCHED_E_NOMEM;
-  }
-  // Per group of equal tool count: the search plan, then the tables.
-  struct Group {
-    size_t first, last;
-    SearchArgs a;
-  };
-  std::vector<Group> groups;
-  for (size_t first = 0; first < R;) {
-    const int32_t pf = replica_problem[order[first]];
-    size_t last = first;
-    while (last < R && keys[size_t(replica_problem[order[last]])] == keys[size_t(pf)]) ++last;
-    Group g{first, last, SearchArgs{}};
-    const sched_problem& p0 = *problems[pf];
-    plan_search(p0, 0, p0.n_mappings, uint32_t(last - first), g.a);
-    for (size_t i = first; i < last; ++i)
-      g.a.lds_levels = std::max(g.a.lds_levels, table_levels(*problems[replica_problem[order[i]]]));
-    // The block cap is shared by the whole batch so partials stay bounded.
-    const uint64_t cap = std::max<uint64_t>(1, kMaxBlocks / R);
-    g.a.blocks_per_table = uint32_t(std::min<uint64_t>(g.a.items_per_table, cap));
-    g.a.n_blocks = g.a.blocks_per_table * g.a.n_tables;
-    groups.push_back(g);
-    first = last;
-  }
-  for (const Group& g : groups) {
-    for (size_t i = g.first; i < g.last; ++i) {
-      const int32_t r = order[i];
-      const sched_problem& p = *problems[replica_problem[r]];
-      uint32_t* tb = host_tables.data() + i * max_stride;
-      rc = build_table(p, replica_lat + lat_off[r], tb);
-      if (rc != SCHED_OK) return rc;
-      set_enumeration(p, enumeration(p, true, int(g.a.inner_digits), g.a.prefix != 0), tb);
-      write_walk(g.a, tb);
-    }
-  }
-
-  hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
-  char* ws = static_cast<char*>(d_workspace);
-  const uint32_t* d_tables = reinterpret_cast<const uint32_t*>(ws + L.tables);
-  Partial* d_partials = reinterpret_cast<Partial*>(ws + L.partials);
-  DevResult* d_res = reinterpret_cast<DevResult*>(ws + L.results);
-  HIP_TRY(hipMemcpyAsync(ws + L.tables, host_tables.data(), R * max_stride * 4,
-                         hipMemcpyHostToDevice, s));
-  size_t partial_cursor = 0;
-  for (Group& g : groups) {
-    const int n = problems[replica_problem[order[g.first]]]->n;
-    SearchArgs& a = g.a;
-    a.tables = d_tables + g.first * max_stride;
-    a.table_stride = uint32_t(max_stride);
-    a.partials = d_partials + partial_cursor;
-    a.results = d_res + g.first;
-    HIP_TRY(launch_search(n, a, s));
-    partial_cursor += a.n_blocks;
-  }
-  HIP_TRY(hipMemcpyAsync(host_res.data(), d_res, R * sizeof(DevResult), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
-  for (size_t i = 0; i < R; ++i) {
-    h_out[order[i]].best_index = host_res[i].index;
-    h_out[order[i]].makespan_us = host_res[i].makespan;
   }
   return SCHED_OK;
 }

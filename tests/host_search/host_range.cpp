@@ -3,11 +3,13 @@
 // host, one lane per wave, over every work item of every part.  Writes how
 // often each mapping of [0, n_mappings) was scored (uint32) and its makespan
 // (uint32, 0xFFFFFFFF infeasible) to argv[1], and prints the number of parts.
-// Built for HOST_RANGE_N tools.
+// The kernel is that for HOST_RANGE_N tools.  A problem with fewer tools (or
+// hi = 0) is walked as a batch replica on it instead (lay_replica, with lo
+// mappings in its launch).
 //
-// Input (text, stdin): lo hi share n_edges n_levels budget, then HOST_RANGE_N
-// lines "gpu cpu load xfer mem allowed", n_edges lines "src dst", then the
-// n_levels Q16 contention factors.
+// Input (text, stdin): n_tools lo hi share n_edges n_levels budget, then
+// n_tools lines "gpu cpu load xfer mem allowed", n_edges lines "src dst", then
+// the n_levels Q16 contention factors.
 #include "../../paper_2607_22242_amd/csrc/api.cpp"
 #include "../../paper_2607_22242_amd/csrc/kernels.h"
 
@@ -50,12 +52,22 @@ static int run(const sched_problem& p, uint64_t lo, uint64_t hi, const char* pat
   std::vector<uint32_t> stage(kStageWords), times(p.n_mappings, 0u), ms(p.n_mappings, 0u);
   const Count rec{times.data(), ms.data()};
   SearchArgs a{};
-  if (stage_parts(p, lo, hi, a, stage.data()) > kStageWords) return 1;
+  size_t stride = p.table_words;
+  if (p.n < N || hi == 0) {
+    const Launch g{0, 1, N, lo, SearchArgs{}};
+    a.n_tables = 1;
+    stride = kStageWords;
+    if (lay_replica(p, g, stage.data()) != SCHED_OK ||
+        fill_latencies(p, nullptr, stage.data(), false) != SCHED_OK)
+      return 1;
+  } else if (stage_parts(p, lo, hi, a, stage.data()) > kStageWords) {
+    return 1;
+  }
   std::vector<uint32_t> snap(snap_words<N, SHARE>() * kBlock);
   uint64_t slot_word = 0;
   MaskT<N>* slot = reinterpret_cast<MaskT<N>*>(&slot_word);
   for (uint32_t t = 0; t < a.n_tables; ++t) {
-    const uint32_t* tab = stage.data() + size_t(t) * p.table_words;
+    const uint32_t* tab = stage.data() + size_t(t) * stride;
     std::vector<uint32_t> lds(lds_words_for(N, tab[kHdrLevels]));
     stage_image<N>(tab, lds.data(), 0, 1);
     const TabWalk walk{Tab{tab}};
@@ -81,11 +93,11 @@ static int run(const sched_problem& p, uint64_t lo, uint64_t hi, const char* pat
 }
 
 int main(int argc, char** argv) {
-  constexpr int n = HOST_RANGE_N;
   unsigned long long lo, hi;
-  int share, ne, nl;
+  int n, share, ne, nl;
   long long budget;
-  if (argc < 2 || scanf("%llu %llu %d %d %d %lld", &lo, &hi, &share, &ne, &nl, &budget) != 6)
+  if (argc < 2 ||
+      scanf("%d %llu %llu %d %d %d %lld", &n, &lo, &hi, &share, &ne, &nl, &budget) != 7)
     return 2;
   std::vector<sched_tool> tools(n);
   std::vector<uint8_t> allowed(n);
@@ -105,7 +117,8 @@ int main(int argc, char** argv) {
   sched_problem* p = nullptr;
   sched_problem_desc d{tools.data(), n, e.data(), ne, f.data(), nl, budget, allowed.data(), share};
   if (sched_problem_create_desc(&d, &p) != SCHED_OK) return 1;
-  const int rc = share ? run<n, true>(*p, lo, hi, argv[1]) : run<n, false>(*p, lo, hi, argv[1]);
+  const int rc = share ? run<HOST_RANGE_N, true>(*p, lo, hi, argv[1])
+                       : run<HOST_RANGE_N, false>(*p, lo, hi, argv[1]);
   sched_problem_destroy(p);
   return rc;
 }

@@ -1,0 +1,40 @@
+"""Batches whose replicas of different tool counts share a launch (smaller
+problems laid out for the kernel of the largest), against single searches."""
+import pytest
+
+import paper_2607_22242_amd as S
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# (tools, shape, sharing, two modes per tool from this tool on)
+@pytest.mark.parametrize("name,problems", [
+    ("one tool to twelve", [(n, ("chain", "fanout", "permuted", "random")[n % 4], False, n)
+                            for n in range(1, 13)]),
+    ("both readings", [(5, "random", False, 5), (8, "permuted", True, 8), (3, "chain", True, 3),
+                       (8, "fanout", False, 8), (11, "random", True, 11)]),
+    ("onto a kernel without prefixes for them", [(6, "random", False, 6), (33, "random", False, 3),
+                                                 (13, "permuted", False, 13)]),
+    ("onto 64-bit indices", [(4, "fanout", False, 4), (9, "random", True, 9),
+                             (24, "permuted", False, 4), (22, "random", True, 2)])])
+def test_mixed_launch_matches_single_searches(name, problems):
+    handles, want, rp, lat = [], [], [], []
+    keep = []
+    for k, (n, shape, sharing, three) in enumerate(problems):
+        inst = synth.random_instance(9300 + k, n, shape, tight=k % 2 == 0)
+        allowed = [7 if v < three else (1, 2, 3, 1)[v % 4] for v in range(n)]
+        for rep in range(3):
+            new = synth.perturb(inst["tools"], 10 * k + rep)
+            measured = dict(inst, tools=[r + [t[4]] for r, t in zip(new, inst["tools"])])
+            P = S.Problem.from_instance(measured, allowed, sharing=sharing)
+            want.append(S.sched_bruteforce_argmin(P.handle, 0, P.n_mappings, S.workspace([P.handle])))
+            rp.append(k)
+            lat.append(new)
+        keep.append(S.Problem.from_instance(inst, allowed, sharing=sharing))
+        handles.append(keep[-1].handle)
+    order = sorted(range(len(rp)), key=lambda i: (i * 7) % len(rp))  # replicas in no order
+    print(f"batch {name}: {len(rp)} replicas", flush=True)
+    got = S.sched_eval_batch(handles, [rp[i] for i in order], [lat[i] for i in order],
+                             S.workspace(handles, len(rp)))
+    assert got == [want[i] for i in order]

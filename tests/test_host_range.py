@@ -3,7 +3,9 @@ tables (split_range, stage_parts) driven through the kernels' per-lane code
 must score every mapping of [lo, hi) exactly once, nothing outside it, and
 with the oracle's makespan.  Ranges start and end inside blocks, on their
 edges, and at the ends of the space; spaces have three modes per tool, mixed
-radices and fixed tools; both contention readings."""
+radices and fixed tools; both contention readings.  And a batch's replica on the
+kernel for more tools than it has (lay_replica): every mapping scored once and
+as the oracle has it, with and without shared prefixes, fan-outs included."""
 import os
 import shutil
 import subprocess
@@ -33,7 +35,7 @@ def host_range(tmp_path_factory):
                            "-o", exe], stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
 
     def run(inst, allowed, lo, hi, share):
-        text = [f"{lo} {hi} {int(share)} {len(inst['edges'])} {len(inst['contention_q16'])} "
+        text = [f"{len(allowed)} {lo} {hi} {int(share)} {len(inst['edges'])} {len(inst['contention_q16'])} "
                 f"{inst['vram_budget_mib']}"]
         text += [" ".join(map(str, t)) + f" {a}" for t, a in zip(inst["tools"], allowed)]
         text += [f"{u} {v}" for u, v in inst["edges"]]
@@ -43,6 +45,19 @@ def host_range(tmp_path_factory):
         times, ms = np.fromfile(out, dtype=np.uint32).reshape(2, -1)
         return parts, times, ms.astype(np.int64)
     return run
+
+
+def check(oracle_mod, inst, allowed, share, got, lo, hi):
+    parts, times, ms = got
+    space = oracle_mod.Space(allowed)
+    assert parts >= 1
+    want_times = np.zeros(space.size(), dtype=np.uint32)
+    want_times[lo:hi] = 1
+    assert (times == want_times).all()
+    Q = oracle_mod.Problem.from_instance(inst, sharing=share)
+    want = Q.eval_many(space.base3(np.arange(lo, hi, dtype=np.uint64)))
+    want = np.where(want == oracle_mod.INFEASIBLE, 0xFFFFFFFF, want)
+    np.testing.assert_array_equal(ms[lo:hi], want)
 
 
 @pytest.mark.parametrize("shape,tight,masked,share,lo,hi", [
@@ -59,15 +74,22 @@ def test_parts_cover_the_range_once(host_range, oracle_mod, shape, tight, masked
     inst = synth.random_instance(seed, N, shape, tight=tight)
     allowed = [(7, 7, 7, 7, 7, 6, 7, 7, 7, 3, 7, 2)[(v + seed) % N] for v in range(N)] if masked \
         else [7] * N
-    space = oracle_mod.Space(allowed)
-    total = space.size()
+    total = oracle_mod.Space(allowed).size()
     hi = int(hi * total) if isinstance(hi, float) else hi
-    parts, times, ms = host_range(inst, allowed, lo, hi, share)
-    assert parts >= 1
-    want_times = np.zeros(total, dtype=np.uint32)
-    want_times[lo:hi] = 1
-    assert (times == want_times).all()
-    Q = oracle_mod.Problem.from_instance(inst, sharing=share)
-    want = Q.eval_many(space.base3(np.arange(lo, hi, dtype=np.uint64)))
-    want = np.where(want == oracle_mod.INFEASIBLE, 0xFFFFFFFF, want)
-    np.testing.assert_array_equal(ms[lo:hi], want)
+    check(oracle_mod, inst, allowed, share, host_range(inst, allowed, lo, hi, share), lo, hi)
+
+
+# work: mappings of the launch (1: a mapping per lane; 10^10: six inner digits,
+# or shared prefixes where the problem has them)
+@pytest.mark.parametrize("n,shape,fits,share,work", [
+    (1, "chain", False, False, 1), (4, "permuted", False, False, 1),
+    (9, "random", False, False, 10**10), (11, "permuted", False, True, 10**10),
+    (8, "random", False, True, 1), (7, "fanout", True, False, 10**10),
+    (12, "random", False, False, 10**10), (12, "fanout", True, False, 1)])
+def test_replica_on_a_wider_kernel(host_range, oracle_mod, n, shape, fits, share, work):
+    inst = synth.random_instance(9150 + n, n, shape, tight=not fits)
+    if fits:
+        inst["vram_budget_mib"] = sum(t[4] for t in inst["tools"])
+    allowed = [(7, 5, 7, 3, 7, 2)[v % 6] if n == 9 else 7 for v in range(n)]
+    got = host_range(inst, allowed, work, 0, share)
+    check(oracle_mod, inst, allowed, share, got, 0, oracle_mod.Space(allowed).size())
