@@ -1,11 +1,13 @@
 """Batches whose replicas of different tool counts share a launch (smaller
 problems laid out for the kernel of the largest), against single searches."""
 import pytest
+import torch  # (before the library: one HIP runtime in the process)
 
 import paper_2607_22242_amd as S
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
+assert torch.version.hip
 
 
 # (tools, shape, sharing, two modes per tool from this tool on)

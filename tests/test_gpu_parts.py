@@ -2,11 +2,13 @@
 their low tools enumerated deepest first on the shared-prefix kernel)."""
 import numpy as np
 import pytest
+import torch  # (before the library: one HIP runtime in the process)
 
 import paper_2607_22242_amd as S
 from workloads import synth
 
 pytestmark = pytest.mark.gpu
+assert torch.version.hip
 
 
 def test_part_ranges_match_oracle(oracle_mod):
