@@ -30,6 +30,7 @@ struct sched_problem {
   int64_t budget = 0;
   int32_t sharing = 0;                      // 1: processor-sharing contention
   bool free_fanout = false;                 // no edges, all footprints fit (kFlagFreeFanout)
+  uint32_t closed = kClosedNone;            // kind of closed form, if any
   uint64_t n_mappings = 0;
   uint32_t table_words = 0;
   std::vector<uint32_t> table;       // device image with the problem's own latencies
@@ -448,6 +449,39 @@ void write_walk(const SearchArgs& a, uint32_t* table) {
   table[kHdrPrefix] = a.prefix;
 }
 
+// Labels walked per lane by a closed-form launch over `work` mappings (0: the
+// general kernel, one mapping per lane).  A lane's walk is a series of up to
+// 243 dependent steps, so labels are added while 2^16 outer combinations are
+// left to hide it behind: a 14-tool chain took 29.2 us with 3 labels, 48.4
+// with 5, a 14-tool fan-out 42.9 with 3 and 58.9 with 4.  A chain is worth it
+// at any size (8 tools: 23 us, event loop 36), a fan-out from 2^15 lanes of 9
+// (12 tools: 29.7 us, one by one 41.9; 11 tools 28.9 either way).
+uint32_t closed_inner(uint32_t closed, uint64_t work) {
+  uint32_t j = closed == kClosedChain ? 1 : 0;
+  if (closed == kClosedFanout && work / 9 >= (1ull << 15)) j = 2;
+  if (j == 0) return 0;
+  for (uint64_t c = j == 1 ? 9 : 27; j < kClosedInner && work / c >= (1ull << 16); c *= 3) ++j;
+  return j;
+}
+
+// Outer combinations of a closed-form walk of problem p over its last j labels.
+uint64_t closed_outer(const sched_problem& p, uint32_t j) {
+  uint64_t inner = 1;
+  for (uint32_t k = 0; k < j; ++k) inner *= p.radix[p.order[p.n - 1 - int(k)]];
+  return p.n_mappings / inner;
+}
+
+// Turns the plan of a one-table full-range search into a closed-form one where
+// the problem has one.
+void plan_closed(const sched_problem& p, SearchArgs& a) {
+  const uint32_t j = closed_inner(p.closed, p.n_mappings);
+  if (j == 0) return;
+  a.closed = p.closed;
+  a.inner_digits = j;
+  const uint64_t items = (closed_outer(p, j) + kBlock - 1) / kBlock;
+  a.n_blocks = a.blocks_per_table = uint32_t(std::min<uint64_t>(items, kMaxBlocks));
+}
+
 // A partial range [lo, hi) as parts of a full-order search.  A part of level k
 // is a run of aligned blocks of W_k mappings (W_k: the product of the radices
 // of the first k tools with a choice): the modes of those k tools are free in
@@ -664,6 +698,17 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
     bool identity = true;
     for (int32_t i = 0; i < n_tools; ++i) identity = identity && p->order[i] == i;
     p->free_fanout = fanout_fits && identity;
+    bool chain = n_tools >= 2 && sharing == 0;
+    for (int32_t i = 0; i < n_tools && chain; ++i) {
+      const auto& pl = p->preds[p->order[i]];
+      chain = i == 0 ? pl.empty() : pl.size() == 1 && pl[0] == p->order[i - 1];
+    }
+    if (n_tools >= int32_t(kClosedInner)) {
+      if (chain) p->closed = kClosedChain;
+      if (p->free_fanout && n_tools <= kClosedFanoutTools &&
+          table_levels(*p) <= kClosedFanoutLevels)
+        p->closed = kClosedFanout;
+    }
     p->table_words = table_words(uint32_t(n_tools), table_levels(*p));
     p->table.assign(p->table_words, 0u);
     const int rc = build_table(*p, nullptr, p->table.data());
@@ -991,32 +1036,44 @@ size_t batch_table_bytes(size_t stride, size_t n_replicas) {
 }
 
 // Launches of a batch.  Replicas of one tool count and contention reading
-// share a launch, whatever their shapes, masks and sizes.  A launch that would
+// share a launch, whatever their shapes, masks and sizes, but that serial
+// chains and free fan-outs, where they are enough, have a launch of their own
+// kind (of any tool counts).  A launch that would
 // leave the GPU partly idle (fewer mappings than kTargetLanes lanes) joins the
 // next larger tool count: its tables are laid out for more tools, at the cost
 // of one more resolution per added tool, instead of a launch in series.  13
 // scenarios of 4 to 9 tools, 8 replicas each: 108 us in one launch, 320 us in
 // eleven.
-void plan_batch(const sched_problem* const* problems, int32_t n_problems,
-                const int32_t* replica_problem, size_t R, std::vector<Launch>& launches,
-                std::vector<int32_t>& order) {
+void plan_batch(const sched_problem* const* problems, const int32_t* replica_problem, size_t R,
+                std::vector<Launch>& launches, std::vector<int32_t>& order) {
   order.resize(R);
   std::iota(order.begin(), order.end(), 0);
+  // closed forms with work enough for one of their launches
+  uint64_t work[3] = {};
+  for (size_t r = 0; r < R; ++r)
+    work[problems[replica_problem[r]]->closed] += problems[replica_problem[r]]->n_mappings;
+  const auto kind = [&](int32_t i) {
+    const uint32_t c = problems[i]->closed;
+    return closed_inner(c, work[c]) > 0 ? c : uint32_t(kClosedNone);
+  };
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
     const int32_t a = replica_problem[x], b = replica_problem[y];
+    if (kind(a) != kind(b)) return kind(a) < kind(b);
     if (problems[a]->sharing != problems[b]->sharing)
       return problems[a]->sharing < problems[b]->sharing;
     if (problems[a]->n != problems[b]->n) return problems[a]->n < problems[b]->n;
     return a < b;
   });
-  (void)n_problems;
   for (size_t i = 0; i < R; ++i) {
     const sched_problem& p = *problems[replica_problem[order[i]]];
+    const uint32_t closed = kind(replica_problem[order[i]]);
     Launch* const g = launches.empty() ? nullptr : &launches.back();
-    if (g == nullptr || g->a.sharing != uint32_t(p.sharing) ||
-        (g->lay != p.n && g->work >= kTargetLanes)) {
+    if (g == nullptr || g->a.closed != closed || g->a.sharing != uint32_t(p.sharing) ||
+        (closed == kClosedNone && g->lay != p.n && g->work >= kTargetLanes)) {
       Launch n{i, i, p.n, 0, SearchArgs{}};
       n.a.full_range = 1;
+      n.a.closed = closed;
+      n.a.inner_digits = closed_inner(closed, work[closed]);
       n.a.sharing = uint32_t(p.sharing);
       launches.push_back(n);
     }
@@ -1031,9 +1088,15 @@ void plan_batch(const sched_problem* const* problems, int32_t n_problems,
 // The table of problem p in a launch, without latencies: laid out for the
 // launch's tools, enumerated and walked for its work in all.
 int lay_replica(const sched_problem& p, const Launch& g, uint32_t* table) {
+  SearchArgs w{};
+  if (g.a.closed != kClosedNone) {  // (closed.hip's kernels serve any tool count)
+    const int rc = lay_table(p, uint32_t(p.n), table);
+    w.n_outer = closed_outer(p, g.a.inner_digits);
+    write_walk(w, table);
+    return rc;
+  }
   const int rc = lay_table(p, uint32_t(g.lay), table);
   if (rc != SCHED_OK) return rc;
-  SearchArgs w{};
   const uint64_t shared = shared_inner_count(p);
   // (a problem smaller than one wave of prefixes has nothing to gain)
   w.prefix = prefix_able(p, g.lay) && g.work / shared >= kTargetLanes &&
@@ -1083,6 +1146,7 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipSt
   if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi))
     return search_parts(p, lo, hi, ws, s, h_out);
   plan_search(p, lo, hi, 1, a);
+  if (a.full_range) plan_closed(p, a);
   const std::vector<uint32_t>& table = a.full_range ? p.table_full : p.table;
   a.table_stride = p.table_words;
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
@@ -1280,7 +1344,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     }
     std::vector<Launch> launches;
     std::vector<int32_t> order;  // replicas in launch order
-    plan_batch(problems, n_problems, replica_problem, R, launches, order);
+    plan_batch(problems, replica_problem, R, launches, order);
 
     // The tables: what does not depend on latencies once per problem, then
     // each replica's latencies; behind them each launch's first blocks.
@@ -1298,7 +1362,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
           if (rc != SCHED_OK) return rc;
           built = &p;
         }
-        std::copy_n(laid.data(), bound_base(uint32_t(g.lay), laid[kHdrLevels]), tb);
+        std::copy_n(laid.data(), bound_base(laid[kHdrN], laid[kHdrLevels]), tb);
         rc = fill_latencies(p, replica_lat + lat_off[r], tb, false);
         if (rc != SCHED_OK) return rc;
         g.a.lds_levels = std::max(g.a.lds_levels, table_levels(p));

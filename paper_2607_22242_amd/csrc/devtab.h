@@ -76,6 +76,17 @@ enum : uint32_t {
 // original tool numbers.
 constexpr uint32_t kFlagFreeFanout = 1u;
 
+// Full-order searches in closed form (closed.hip), by the kind of problem: a
+// fan-out as above with at most four contention levels, or a serial chain (the
+// tool with label i depends on the tool with label i - 1 alone) scored with
+// fixed-at-start contention.  The combinations of the last kClosedInner labels
+// (or fewer) are walked per lane.
+enum : uint32_t { kClosedNone = 0, kClosedChain = 1, kClosedFanout = 2 };
+constexpr uint32_t kClosedInner = 5;
+constexpr uint32_t kClosedInnerMost = 243;  // 3^kClosedInner
+constexpr int kClosedFanoutTools = 32;
+constexpr uint32_t kClosedFanoutLevels = 4;
+
 // Record of the tool with internal label i at kHdrWords + kToolWords * i.
 enum : uint32_t {
   kToolCpu = 0,       // cpu_us
@@ -189,6 +200,9 @@ struct SearchArgs {
                               //    deepest tools, full range, fixed at start)
   uint32_t lds_levels;        // the most contention levels any of the tables stores
   uint32_t n_blocks;          // blocks of the launch
+  uint32_t closed;            // kClosed*: all tables are of this kind; inner_digits is then the
+                              // number of last labels walked per lane
+  uint32_t pad;
   uint32_t one_result;        // 1: the tables are parts of one search, results has one entry
   uint32_t* record;           // full range, one table: every scored mapping's makespan
                               // (kInf if infeasible) goes to record[index]; null: none

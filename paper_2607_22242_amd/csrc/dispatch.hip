@@ -76,7 +76,8 @@ static const auto kEvalFns = make_eval_table(std::make_index_sequence<kMaxTools>
 static const auto kBoundFns = make_bound_table(std::make_index_sequence<kMaxTools>{});
 
 hipError_t launch_search(int n_tools, const SearchArgs& a, hipStream_t s) {
-  const hipError_t e = kSearchFns[n_tools - 1](a, s);
+  const hipError_t e =
+      a.closed != kClosedNone ? launch_closed(a, s) : kSearchFns[n_tools - 1](a, s);
   if (e != hipSuccess || a.results == nullptr) return e;
   const uint32_t results = a.one_result ? 1u : a.n_tables;
   hipLaunchKernelGGL(reduce_kernel, dim3(results), dim3(kReduceThreads), 0, s, a.partials,

@@ -9,6 +9,8 @@ namespace devmap {
 // The search over a.tables (or a.host_table) and the reduction of its partials
 // into a.results, if given.
 hipError_t launch_search(int n_tools, const SearchArgs& a, hipStream_t s);
+// Searches in closed form (a.closed), without the reduction.
+hipError_t launch_closed(const SearchArgs& a, hipStream_t s);
 // flags: kEval*.  With kEvalHostTable, tab is the host's copy of a table of at
 // most kArgWords words up to its bound table.
 hipError_t launch_eval(int n_tools, const uint32_t* tab, const uint64_t* idx, int64_t n,
