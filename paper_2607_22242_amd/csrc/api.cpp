@@ -31,6 +31,7 @@ struct sched_problem {
   int32_t sharing = 0;                      // 1: processor-sharing contention
   bool free_fanout = false;                 // no edges, all footprints fit (kFlagFreeFanout)
   uint32_t closed = kClosedNone;            // kind of closed form, if any
+  int32_t variant = kVarAll;                // of a shared-prefix search (kVar*)
   uint64_t n_mappings = 0;
   uint32_t table_words = 0;
   std::vector<uint32_t> table;       // device image with the problem's own latencies
@@ -412,6 +413,7 @@ void plan_search(const sched_problem& p, uint64_t lo, uint64_t hi, uint32_t n_ta
   const bool prefix = full && prefix_plan(p, n_tables);
   if (prefix) {
     J = int(kSharedInner);
+    a.variant = p.variant;
   } else {
     while (J < kMaxInnerDigits && J < P) {
       const uint64_t next = inner_count(p, enumeration(p, full, J + 1, false), J + 1);
@@ -703,6 +705,10 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
       const auto& pl = p->preds[p->order[i]];
       chain = i == 0 ? pl.empty() : pl.size() == 1 && pl[0] == p->order[i - 1];
     }
+    bool queue = false;
+    for (uint8_t m : p->allowed) queue = queue || (m & 4);
+    if (!queue && sharing == 0 && n_tools >= kVarMinN && n_tools <= kPrefixMaxN)
+      p->variant = p->budget >= sum_mem ? kVarFree : kVarNoQueue;
     if (n_tools >= int32_t(kClosedInner)) {
       if (chain) p->closed = kClosedChain;
       if (p->free_fanout && n_tools <= kClosedFanoutTools &&

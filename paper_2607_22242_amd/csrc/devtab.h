@@ -26,6 +26,17 @@ constexpr int kMaxInnerDigits = 6;      // inner (wave-uniform) digits per lane
 #define DEVMAP_SHARED_INNER 2
 #endif
 constexpr uint32_t kSharedInner = DEVMAP_SHARED_INNER;  // inner digits of a shared-prefix search
+// Variants of the fixed-at-start shared-prefix search for spaces without
+// gpu_queue (the GPU/CPU spaces): a pass then has no queue to look after, and
+// (kVarFree: the budget holds every footprint together) no VRAM to sum.  Built
+// from kVarMinN tools: below, such a space has too few mappings for shared
+// prefixes to fill the GPU.  Mixed DAGs of 22, 26 and 32 tools (2^21 to 2^30
+// mappings) without a budget: 152 us, 2.35 ms, 76.1 ms, against 190 us, 2.86
+// ms, 88.5 ms.  Three inner digits, to share a prefix among 8 combinations in
+// place of 4, helped some DAGs (26 tools 2.16 ms) and cost others more (22
+// tools 314 us, 32 tools 99.6 ms).
+enum : int { kVarAll = 0, kVarNoQueue = 1, kVarFree = 2 };
+constexpr int kVarMinN = 21;
 constexpr int kPrefixMaxN = 32;         // tool counts served by shared prefixes (fixed at start:
                                         // N LDS words per lane)
 constexpr int kPrefixMaxNShare = 24;    // the same under processor sharing (1.5N words per lane)
@@ -202,7 +213,7 @@ struct SearchArgs {
   uint32_t n_blocks;          // blocks of the launch
   uint32_t closed;            // kClosed*: all tables are of this kind; inner_digits is then the
                               // number of last labels walked per lane
-  uint32_t pad;
+  int32_t variant;            // kVar*
   uint32_t one_result;        // 1: the tables are parts of one search, results has one entry
   uint32_t* record;           // full range, one table: every scored mapping's makespan
                               // (kInf if infeasible) goes to record[index]; null: none

@@ -248,9 +248,12 @@ constexpr uint32_t kTagNow = kH;
 constexpr uint32_t kTagQueue = 2u * kH;
 constexpr uint32_t kTagCpu = 3u * kH;
 
-template <int N>
+//
+// VAR: what the problem's space leaves out of a pass (see kVar*).
+template <int N, int VAR = kVarAll>
 struct Sim {
   using M = MaskT<N>;
+  static constexpr bool kQueue = VAR == kVarAll, kVram = VAR != kVarFree;
   uint32_t T[N];
   M gnm, gqm;
   M started;   // started GPU tools and resolved CPU tools
@@ -277,7 +280,7 @@ struct Sim {
     mk = 0;
     rgs = kInf;
     // a GPU mode whose footprint exceeds the budget never fits
-    dead = ((gn | gq) & load_mask<N>(Tab{tab}, kHdrBigLo)) != 0;
+    dead = kVram && ((gn | gq) & load_mask<N>(Tab{tab}, kHdrBigLo)) != 0;
   }
 
   // Pass number `pass` (wave-uniform: the lanes of a wave start their
@@ -308,7 +311,7 @@ struct Sim {
     gnm = opaque_v(gnm);
     gqm = opaque_v(gqm);
     const M ALL = all_tools<N>();
-    const M gpum = gnm | gqm;
+    const M gpum = kQueue ? gnm | gqm : gnm;
     const uint32_t* s_dur = lds + lds_dur_off<N>();
     const uint32_t* s_mem = lds + lds_mem_off<N>();
     const Tab tp = fresh(tab);
@@ -329,32 +332,35 @@ struct Sim {
     // the queue head, if the queue is free and a queued tool ready: ready at
     // minq (the earliest), lowest original number (the table's word holds
     // the number above the label)
-    const bool qfree = minq <= t && qfin <= t;
+    const bool qfree = kQueue && minq <= t && qfin <= t;
     // (formed once: the tag is the top bit, and a compare against the sum
     // would otherwise become a per-tool flip of T's top bit)
-    const uint32_t key = opaque_v(kTagQueue + minq);
+    const uint32_t key = kQueue ? opaque_v(kTagQueue + minq) : 0u;
     uint32_t hO = kInf;
     const M wr_a = opaque(wr), ww_a = opaque(ww), wa_a = opaque(wr | ww);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
       if (!((wa_a >> i) & 1)) continue;  // one test for a tool in neither state
       DEVMAP_KEEP_BRANCH();
-      const uint32_t mem = opaque(tp[kHdrWords + kToolWords * i + kToolMem]);
+      uint32_t mem = 0;
+      if constexpr (kVram) mem = opaque(tp[kHdrWords + kToolWords * i + kToolMem]);
       if ((wr_a >> i) & 1) {
         DEVMAP_KEEP_BRANCH();
         const uint32_t d = T[i] - t1;
         const bool on = d < lim;  // finishes after t
-        in_use = add_if(in_use, mem, on);
+        if constexpr (kVram) in_use = add_if(in_use, mem, on);
         run = or_if(run, M(1) << i, on);
-        tf = umin32(tf, d);
+        if constexpr (kQueue) tf = umin32(tf, d);
       }
       if ((ww_a >> i) & 1) {
         DEVMAP_KEEP_BRANCH();
         const bool on = T[i] == now_t;  // gpu_now, ready at t
-        in_use = add_if(in_use, mem, on);
+        if constexpr (kVram) in_use = add_if(in_use, mem, on);
         k += on ? 1u : 0u;
-        const uint32_t orig = opaque(tp[kHdrWords + kToolWords * i + kToolOrig]);
-        hO = T[i] == key ? umin32(hO, orig) : hO;  // read only if qfree
+        if constexpr (kQueue) {
+          const uint32_t orig = opaque(tp[kHdrWords + kToolWords * i + kToolOrig]);
+          hO = T[i] == key ? umin32(hO, orig) : hO;  // read only if qfree
+        }
       }
     }
     if constexpr (N <= 32) {
@@ -362,7 +368,7 @@ struct Sim {
     } else {
       k += __builtin_popcountll(uint64_t(run));
     }
-    if (in_use > budget) return true;  // out of memory: infeasible
+    if (kVram && in_use > budget) return true;  // out of memory: infeasible
     uint32_t hsel = kInf;              // label of the queued tool admitted at t
     if (qfree) {
       const uint32_t lab = hO & kOrigLabelMask;
@@ -385,19 +391,19 @@ struct Sim {
       if (!((wb_b >> i) & 1)) continue;  // one test for a tool in neither state
       DEVMAP_KEEP_BRANCH();
       if ((ww_b >> i) & 1) {
-        const bool adm = (hsel == uint32_t(i));
+        const bool adm = kQueue && (hsel == uint32_t(i));
         if (T[i] == now_t || adm) {
           const uint32_t d = s_row[2u * uint32_t(i) + (adm ? 1u : 0u)];
           T[i] = t + d;
           started |= bi;
           run |= bi;
-          tf = umin32(tf, d - 1u);  // finish after t
+          if constexpr (kQueue) tf = umin32(tf, d - 1u);  // finish after t
           mk = umax32(mk, T[i]);
           if (adm) qfin = T[i];
         }
         const uint32_t x = T[i];
         tn = umin32(tn, x - now_t1);           // gpu_now ready after t
-        minq = umin32(minq, x - kTagQueue);   // queued ready time (>= H: none)
+        if constexpr (kQueue) minq = umin32(minq, x - kTagQueue);  // queued ready time (>= H: none)
       }
       if ((wu_b >> i) & 1) {
         const M pm = load_mask<N>(tp, kHdrWords + kToolWords * i + kToolPredLo);
@@ -425,7 +431,7 @@ struct Sim {
             started |= bi;
           } else {
             // selects, not branches: the modes are per lane
-            const bool on_gpu = (gpum >> i) & 1, now = (gnm >> i) & 1;
+            const bool on_gpu = (gpum >> i) & 1, now = !kQueue || ((gnm >> i) & 1);
             const uint32_t f = umax32(c, g ? g + xw : 0u) + rec[kToolCpu];  // CPU finish
             T[i] = on_gpu ? (now ? kTagNow : kTagQueue) + rg : kTagCpu + f;
             started = or_if(started, bi, !on_gpu);
@@ -434,7 +440,7 @@ struct Sim {
             // word: outside its own mode a term lands at or above the range
             // it is read in (as in the sweep over waiting tools)
             tn = umin32(tn, T[i] - now_t1);
-            minq = umin32(minq, T[i] - kTagQueue);
+            if constexpr (kQueue) minq = umin32(minq, T[i] - kTagQueue);
           }
         }
       }
@@ -446,7 +452,7 @@ struct Sim {
     if (pass == 0) return false;  // sources resolved: now the events at t = 0
     uint32_t next = kInf;
     if (tn < lim) next = tn + t1;
-    if (minq <= t) {
+    if (kQueue && minq <= t) {
       // A ready queued tool is still waiting: the queue head can only move
       // when the queue frees or VRAM is released, whatever else turns ready.
       if (qfin > t) {
@@ -454,7 +460,7 @@ struct Sim {
       } else if (tf < lim) {
         next = umin32(next, tf + t1);  // blocked on VRAM: wait for a release
       }
-    } else if (minq < kH) {
+    } else if (kQueue && minq < kH) {
       next = umin32(next, minq);       // the next queued tool turns ready
     }
     if (DEFER) next = umin32(next, rgs);
@@ -470,7 +476,7 @@ struct Sim {
   // ordinary passes resolve them.
   __host__ __device__ __forceinline__ void settle_deferred(const uint32_t* __restrict__ tab,
                                                            M defer) {
-    const M gpum = gnm | gqm;
+    const M gpum = kQueue ? gnm | gqm : gnm;
     const Tab tp = fresh(tab);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -500,7 +506,7 @@ struct Sim {
             mk = umax32(mk, f);
           } else {
             started &= ~bi;
-            if (gnm & bi) {
+            if (!kQueue || (gnm & bi)) {
               T[i] = kTagNow + r;
             } else {
               T[i] = kTagQueue + r;
@@ -1156,8 +1162,9 @@ struct Snap {
   uint32_t t, qfin, minq, mk;
 };
 
-template <int N>
-__host__ __device__ __forceinline__ void snap_save(uint32_t* s, Snap<N>& m, const Sim<N>& sim) {
+template <int N, int VAR>
+__host__ __device__ __forceinline__ void snap_save(uint32_t* s, Snap<N>& m,
+                                                   const Sim<N, VAR>& sim) {
 #pragma unroll
   for (int i = 0; i < int(snap_tools<N>()); ++i) s[i * kBlock] = sim.T[i];
   m.started = sim.started;
@@ -1169,9 +1176,9 @@ __host__ __device__ __forceinline__ void snap_save(uint32_t* s, Snap<N>& m, cons
   m.mk = sim.mk;
 }
 
-template <int N>
+template <int N, int VAR>
 __host__ __device__ __forceinline__ void snap_load(const uint32_t* s, const Snap<N>& m,
-                                                   Sim<N>& sim) {
+                                                   Sim<N, VAR>& sim) {
 #pragma unroll
   for (int i = 0; i < N; ++i) sim.T[i] = i < int(snap_tools<N>()) ? s[i * kBlock] : 0u;
   sim.started = m.started;
@@ -1184,8 +1191,8 @@ __host__ __device__ __forceinline__ void snap_load(const uint32_t* s, const Snap
 }
 
 // The tools whose mode the last pass read for the first time.
-template <int N>
-__host__ __device__ __forceinline__ MaskT<N> first_read(const Sim<N>& sim) {
+template <int N, int VAR>
+__host__ __device__ __forceinline__ MaskT<N> first_read(const Sim<N, VAR>& sim) {
   return sim.resolved;
 }
 
@@ -1315,20 +1322,20 @@ __host__ __device__ __forceinline__ M pull_mask(M x, uint32_t src) {
 }
 
 // The register part of lane src's saved state.
-template <int N>
+template <int N, int VAR>
 __host__ __device__ __forceinline__ Snap<N> pull_snap(const Snap<N>& m, uint32_t src) {
   Snap<N> r;
   r.started = pull_mask(m.started, src);
   r.resolved = pull_mask(m.resolved, src);
   r.run = pull_mask(m.run, src);
   r.t = pull(m.t, src);
-  r.qfin = pull(m.qfin, src);
-  r.minq = pull(m.minq, src);
+  r.qfin = VAR == kVarAll ? pull(m.qfin, src) : 0u;
+  r.minq = VAR == kVarAll ? pull(m.minq, src) : kInf;
   r.mk = pull(m.mk, src);
   return r;
 }
 
-template <int N>
+template <int N, int VAR>
 __host__ __device__ __forceinline__ SnapPS<N> pull_snap(const SnapPS<N>& m, uint32_t src) {
   SnapPS<N> r;
   r.running = pull_mask(m.running, src);
@@ -1357,7 +1364,9 @@ __host__ __device__ __forceinline__ SnapPS<N> pull_snap(const SnapPS<N>& m, uint
 // prefixes, so the wave-wide masks of a pass stay narrow, and lanes whose
 // prefix is infeasible take no round.  Every lane of the wave must call this
 // function for the same item (lanes beyond the range take part in the pulls).
-template <int N, bool SHARE, class Rec = NoRecord, class Walk>
+//
+// VAR: a variant of the fixed-at-start evaluator (kVar*).
+template <int N, bool SHARE, class Rec = NoRecord, int VAR = kVarAll, class Walk>
 __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
                                                             const uint32_t* __restrict__ tab,
                                                             const uint32_t* __restrict__ lds,
@@ -1381,7 +1390,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
   for (uint32_t j = 0; j < J; ++j) inner |= M(1) << tu[enum_lab_base(N) + j];
   const M big = load_mask<N>(tu, kHdrBigLo);
 
-  using S = typename std::conditional<SHARE, SimPS<N>, Sim<N>>::type;
+  using S = typename std::conditional<SHARE, SimPS<N>, Sim<N, VAR>>::type;
   using SS = typename std::conditional<SHARE, SnapPS<N>, Snap<N>>::type;
   // (fixed at start: one pass more than a plain evaluation may take, the
   // deferred tools' GPU ready time)
@@ -1464,8 +1473,8 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
     const uint32_t pr = r0i + wl;
     const uint32_t q = (pr * cinv) >> 16, c = pr - q * C;
     const uint32_t src = pull(owner_of_rank, q < W ? q : 0u);
-    const SS ss = pull_snap<N>(sm, src);
-    const M sgn = pull_mask(ogn, src), sgq = pull_mask(ogq, src);
+    const SS ss = pull_snap<N, VAR>(sm, src);
+    const M sgn = pull_mask(ogn, src), sgq = VAR == kVarAll ? pull_mask(ogq, src) : M(0);
     const I sxo = I(pull(uint32_t(xo64), src)) |
                   I(sizeof(I) > 4 ? (uint64_t(pull(uint32_t(xo64 >> 32), src)) << 32) : 0u);
     const int sps = int(pull(uint32_t(pstar), src));
@@ -1478,7 +1487,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
       snap_load<N>(snap0 + src, ss, sim);
       sim.gnm = sgn | (m0 == 1u ? b0 : M(0)) | (m1 == 1u ? b1 : M(0));
       sim.gqm = sgq | (m0 == 2u ? b0 : M(0)) | (m1 == 2u ? b1 : M(0));
-      sim.dead = ((sim.gnm | sim.gqm) & big) != 0;
+      sim.dead = VAR != kVarFree && ((sim.gnm | sim.gqm) & big) != 0;
       if (const M defer = deferred()) sim.settle_deferred(tab, defer);
       const I x = sxo + I(d0) * w0 + I(d1) * w1;
       uint32_t ms = kInf;
@@ -1514,7 +1523,7 @@ static_assert(sizeof(SearchArgs) % 8 == 0 && sizeof(EvalArgs) % 8 == 0 &&
 // work items (kBlock consecutive outer combinations each) with a stride of
 // blocks_per_table.  Each lane keeps its own (makespan, index) minimum; the
 // block's minimum goes to partials[b].
-template <int N, bool FULL, bool SHARE>
+template <int N, bool FULL, bool SHARE, int VAR = kVarAll>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(
     SHARE ? (FULL && N <= kPrefixMaxNShare ? (N <= 19 ? 5 : 4)  // LDS: 1.5N words per lane
                                       : DEVMAP_SHARE_WAVES)
@@ -1559,7 +1568,11 @@ search_kernel(SearchArgs a, TableArg) {
     const TabWalk walk{Tab{tab}};
     const uint64_t items = (walk_n_outer(walk) + (kBlock - 1)) / kBlock;
     const RecordTo rec{a.record};
-    if constexpr (kPrefix) {
+    if constexpr (VAR != kVarAll) {
+      for (uint64_t item = bb; item < items; item += nb)
+        lane_search_prefix<N, SHARE, RecordTo, VAR>(walk, tab, s_lds, item, threadIdx.x, slot,
+                                                    s_snap + threadIdx.x, best_ms, best_x, rec);
+    } else if constexpr (kPrefix) {
       if (walk.t[kHdrPrefix]) {
         for (uint64_t item = bb; item < items; item += nb)
           lane_search_prefix<N, SHARE>(walk, tab, s_lds, item, threadIdx.x, slot,
@@ -1700,6 +1713,17 @@ hipError_t launch_search_n(const SearchArgs& a, hipStream_t s) {
     else
       hipLaunchKernelGGL((search_kernel<N, false, true>), dim3(blocks), dim3(kBlock), shm, s, a, t);
   } else {
+    if constexpr (N >= kVarMinN && N <= kPrefixMaxN) {
+      if (a.variant == kVarNoQueue || a.variant == kVarFree) {
+        if (a.variant == kVarFree)
+          hipLaunchKernelGGL((search_kernel<N, true, false, kVarFree>), dim3(blocks), dim3(kBlock),
+                             shm, s, a, t);
+        else
+          hipLaunchKernelGGL((search_kernel<N, true, false, kVarNoQueue>), dim3(blocks),
+                             dim3(kBlock), shm, s, a, t);
+        return hipGetLastError();
+      }
+    }
     if (a.full_range)
       hipLaunchKernelGGL((search_kernel<N, true, false>), dim3(blocks), dim3(kBlock), shm, s, a, t);
     else
