@@ -247,7 +247,8 @@ int sched_eval_reprobes(const sched_problem *p, uint64_t base_index, const sched
 /* Counters of one pruned search. */
 typedef struct {
     uint64_t prefixes;          /* assignments of the prefix tools that were bounded */
-    uint64_t prefixes_searched; /* prefixes whose subspace was searched exhaustively */
+    uint64_t prefixes_searched; /* prefixes taken up for search (their extensions bounded
+                                   again, the survivors searched exhaustively) */
     uint64_t mappings_searched; /* mappings scored by those searches */
     int64_t initial_bound_us;   /* makespan of the descent's mapping (INT64_MAX if none) */
     int32_t prefix_tools;       /* tools in the prefix (0: one exhaustive search) */
@@ -263,8 +264,9 @@ typedef struct {
  * Algorithm 1 from index 0.  The tools whose modes move the bound most form a
  * prefix; every prefix assignment gets a lower bound (critical path of the
  * shortest durations, queued durations summed) and only assignments whose
- * bound does not exceed the best makespan found so far have their remaining
- * tools searched exhaustively, most promising first.  Spaces below 2^22
+ * bound does not exceed the best makespan found so far are taken up, most
+ * promising first: extended by the next tools, bounded again, and what
+ * survives has its remaining tools searched exhaustively.  Spaces below 2^22
  * mappings get one exhaustive search.  d_workspace: at least
  * sched_pruned_workspace_bytes(p) bytes, 256-byte aligned.  stats: optional
  * counters (host). */

@@ -77,7 +77,21 @@ enum : uint32_t {
   kHdrInnerDigits = 22,
   kHdrInnerCount = 23,
   kHdrPrefix = 24,
-  kHdrWords = 25,
+  // The outer combinations of a walk may come from a list of (bound, y) pairs
+  // (its device address; 0: none): the outer combination numbered k then has
+  // the digits of k mod kHdrListRest, and above them those of y of entry
+  // k / kHdrListRest.
+  kHdrListLo = 25,
+  kHdrListHi = 26,
+  kHdrListRest = 27,
+  // Bounds of the children of listed assignments (device address; 0: of all
+  // assignments): the one numbered k extends y of entry k / kHdrChildren by the
+  // digits of k mod kHdrChildren, above the kHdrParents assignments there are.
+  kHdrParentLo = 28,
+  kHdrParentHi = 29,
+  kHdrParents = 30,
+  kHdrChildren = 31,
+  kHdrWords = 32,
 };
 
 // A fan-out (no edges) whose footprints all fit the budget together, scored

@@ -999,7 +999,9 @@ struct RecordTo {
 // The walk of a search: from the launch's arguments (a partial range in index
 // order, and the host harness), or from a table's header (full order: tables
 // of one launch may differ).
-__host__ __device__ __forceinline__ uint64_t walk_outer_lo(const SearchArgs& a) { return a.outer_lo; }
+__host__ __device__ __forceinline__ uint64_t walk_outer(const SearchArgs& a, uint64_t rel) {
+  return a.outer_lo + rel;
+}
 __host__ __device__ __forceinline__ uint64_t walk_n_outer(const SearchArgs& a) { return a.n_outer; }
 __host__ __device__ __forceinline__ uint32_t walk_inner_digits(const SearchArgs& a) {
   return a.inner_digits;
@@ -1010,8 +1012,16 @@ __host__ __device__ __forceinline__ uint32_t walk_inner_count(const SearchArgs& 
 struct TabWalk {
   Tab t;
 };
-__host__ __device__ __forceinline__ uint64_t walk_outer_lo(const TabWalk& w) {
-  return uint64_t(w.t[kHdrOuterLoLo]) | (uint64_t(w.t[kHdrOuterLoHi]) << 32);
+// (an address that is 0 or that of the pairs)
+__host__ __device__ __forceinline__ const uint2* list_at(Tab t, uint32_t lo_word) {
+  return reinterpret_cast<const uint2*>(uint64_t(t[lo_word]) | (uint64_t(t[lo_word + 1]) << 32));
+}
+__host__ __device__ __forceinline__ uint64_t walk_outer(const TabWalk& w, uint64_t rel) {
+  const uint64_t rest = opaque(w.t[kHdrListRest]);
+  if (rest == 0) return (uint64_t(w.t[kHdrOuterLoLo]) | (uint64_t(w.t[kHdrOuterLoHi]) << 32)) + rel;
+  DEVMAP_KEEP_BRANCH();
+  const uint64_t k = rel / rest;
+  return uint64_t(list_at(w.t, kHdrListLo)[k].y) * rest + (rel - k * rest);
 }
 __host__ __device__ __forceinline__ uint64_t walk_n_outer(const TabWalk& w) {
   return uint64_t(w.t[kHdrNOuterLo]) | (uint64_t(w.t[kHdrNOuterHi]) << 32);
@@ -1046,7 +1056,7 @@ __host__ __device__ __forceinline__ void lane_search(const Walk& a,
   const uint32_t levels = tab[kHdrLevels];
   const uint32_t budget = tab[kHdrBudget];
   const uint32_t J = walk_inner_digits(a), inner_count = walk_inner_count(a);
-  const uint64_t o = walk_outer_lo(a) + rel;
+  const uint64_t o = walk_outer(a, rel);
   M ogn, ogq;
   uint64_t xo64;  // index weight of the outer digits
   decode_positions<N>(tab, o, J, tab[kHdrPositions], ogn, ogq, xo64);
@@ -1411,7 +1421,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
   int pstar = -1;
   SS sm{};
   if (rel < walk_n_outer(a)) {
-    decode_positions<N>(tab, walk_outer_lo(a) + rel, J, tab[kHdrPositions], ogn, ogq, xo64);
+    decode_positions<N>(tab, walk_outer(a, rel), J, tab[kHdrPositions], ogn, ogq, xo64);
     // The prefix: inner tools on the CPU (their modes are never read).
     S sim;
     sim.init(tab, ogn, ogq);
@@ -1672,7 +1682,8 @@ __host__ __device__ __forceinline__ uint32_t prefix_bound(const uint32_t* __rest
   return umax32(lb, qsum);
 }
 
-// Bounds of prefixes [0, n): prefix y holds the mixed-radix digits of the
+// Bounds of prefixes [0, n), or of n children of listed prefixes (kHdrParent*):
+// prefix y holds the mixed-radix digits of the
 // table's enumeration positions [0, K); known = the labels of those tools
 // and of the tools with a single allowed mode.  Prefixes whose bound does
 // not exceed ub are appended to out as (bound, y) pairs; *count (zero on
@@ -1682,15 +1693,22 @@ __global__ __launch_bounds__(kBlock) void bound_kernel(const uint32_t* __restric
                                                        uint32_t K, uint64_t known, int64_t n,
                                                        uint32_t ub, uint32_t* __restrict__ count,
                                                        uint2* __restrict__ out) {
+  const Tab tp{tab};
+  const uint2* const parents = list_at(tp, kHdrParentLo);
+  const uint32_t children = tp[kHdrChildren], n_parents = tp[kHdrParents];
   for (int64_t y = int64_t(blockIdx.x) * kBlock + threadIdx.x; y < n;
        y += int64_t(gridDim.x) * kBlock) {
     MaskT<N> gn, gq;
-    uint64_t x;
-    decode_positions<N>(tab, uint64_t(y), 0, K, gn, gq, x);
+    uint64_t x, py = uint64_t(y);
+    if (parents) {
+      const uint64_t k = py / children;
+      py = parents[k].y + (py - k * children) * n_parents;
+    }
+    decode_positions<N>(tab, py, 0, K, gn, gq, x);
     const uint32_t lb = prefix_bound<N>(tab, gn, gq, MaskT<N>(known));
     if (lb != kInf && lb <= ub) {
       const uint32_t slot = atomicAdd(count, 1u);
-      out[slot] = make_uint2(lb, uint32_t(y));
+      out[slot] = make_uint2(lb, uint32_t(py));
     }
   }
 }

@@ -1,0 +1,27 @@
+"""The pruned search's second level of bounds, against the exhaustive search:
+spaces whose prefixes survive in several chunks (small latencies, many ties),
+spaces with few tools left for the extension, and restricted ones."""
+import pytest
+import torch  # (before the library: one HIP runtime in the process)
+
+import paper_2607_22242_amd as S
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+assert torch.version.hip
+
+
+@pytest.mark.parametrize("n,shape,small,masked,share", [
+    (14, "random", True, False, False), (17, "random", True, False, False),
+    (17, "fanout", True, False, False), (18, "permuted", True, False, False),
+    (16, "permuted", True, False, True), (24, "permuted", False, True, False),
+    (30, "permuted", False, True, False)])
+def test_children_match_exhaustive(n, shape, small, masked, share):
+    inst = synth.random_instance(9600 + n, n, shape, tight=shape != "fanout", small_values=small)
+    allowed = [(3, 7, 6, 1, 5, 3, 2, 3)[v % 8] for v in range(n)] if masked else None
+    P = S.Problem.from_instance(inst, allowed, sharing=share)
+    print(f"pruned {n} tools, {shape}: {P.n_mappings} mappings", flush=True)
+    x, ms, st = S.sched_pruned_argmin(P.handle, S.pruned_workspace(P.handle))
+    assert (x, ms) == S.sched_bruteforce_argmin(P.handle, 0, P.n_mappings, S.workspace([P.handle]))
+    print(st, flush=True)
+    assert st["launches"] >= 1 and st["mappings_searched"] <= P.n_mappings
