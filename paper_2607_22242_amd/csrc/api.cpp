@@ -401,6 +401,19 @@ uint64_t inner_count(const sched_problem& p, const Seq& seq, int J) {
   return c;
 }
 
+// Lanes per wave of a shared-prefix search over a space too small to fill the
+// GPU with full waves of prefixes (0: one mapping per lane in place of it).
+// With as many prefixes as make four rounds of combinations, 2^17 prefixes
+// still give the GPU 4,681 waves: 13 tools, 177,147 prefixes, whole calls
+// 102 us layered and 126 tight, 152 and 147 with a mapping per lane (full
+// waves: 133 and 190; two rounds per wave 117 and 128).  At 12 tools a mapping
+// per lane is the shorter way (68 us; two rounds 71, four 83).
+uint32_t thin_lanes(const sched_problem& p) {
+  const uint64_t inner = shared_inner_count(p);
+  return prefix_able(p, p.n) && inner >= 6 && p.n_mappings / inner >= (1ull << 17)
+             ? uint32_t(256u / inner) : 0u;
+}
+
 // Split [lo, hi) x n_tables into blocks of kBlock lanes; each lane owns one
 // outer combination and enumerates the inner ones.  J grows while the lanes
 // still number about kTargetLanes.
@@ -411,9 +424,15 @@ void plan_search(const sched_problem& p, uint64_t lo, uint64_t hi, uint32_t n_ta
   const unsigned __int128 work = (unsigned __int128)(hi - lo) * n_tables;
   int J = 0;
   const bool prefix = full && prefix_plan(p, n_tables);
+  a.lanes = 64;
+  a.thin = 0;
   if (prefix) {
     J = int(kSharedInner);
     a.variant = p.variant;
+  } else if (const uint32_t lanes = n_tables == 1 && full ? thin_lanes(p) : 0u) {
+    a.thin = 1;
+    J = int(kSharedInner);
+    a.lanes = lanes;
   } else {
     while (J < kMaxInnerDigits && J < P) {
       const uint64_t next = inner_count(p, enumeration(p, full, J + 1, false), J + 1);
@@ -421,7 +440,7 @@ void plan_search(const sched_problem& p, uint64_t lo, uint64_t hi, uint32_t n_ta
       ++J;
     }
   }
-  const uint64_t inner = inner_count(p, enumeration(p, full, J, prefix), J);
+  const uint64_t inner = inner_count(p, enumeration(p, full, J, prefix || a.thin), J);
   a.lo = lo;
   a.hi = hi;
   a.inner_digits = uint32_t(J);
@@ -429,7 +448,8 @@ void plan_search(const sched_problem& p, uint64_t lo, uint64_t hi, uint32_t n_ta
   a.outer_lo = lo / inner;
   const uint64_t outer_hi = hi / inner + (hi % inner ? 1 : 0);
   a.n_outer = outer_hi - a.outer_lo;
-  a.items_per_table = (a.n_outer + kBlock - 1) / kBlock;
+  const uint64_t per_item = uint64_t(a.lanes) * (kBlock / 64);
+  a.items_per_table = (a.n_outer + per_item - 1) / per_item;
   const uint64_t cap = std::max<uint64_t>(1, kMaxBlocks / n_tables);
   a.blocks_per_table = uint32_t(std::min<uint64_t>(a.items_per_table, cap));
   a.n_tables = n_tables;
@@ -448,7 +468,8 @@ void write_walk(const SearchArgs& a, uint32_t* table) {
   table[kHdrNOuterHi] = uint32_t(a.n_outer >> 32);
   table[kHdrInnerDigits] = a.inner_digits;
   table[kHdrInnerCount] = a.inner_count;
-  table[kHdrPrefix] = a.prefix;
+  table[kHdrPrefix] = a.prefix | a.thin;
+  table[kHdrLanes] = a.lanes ? a.lanes : 64u;
 }
 
 // Labels walked per lane by a closed-form launch over `work` mappings (0: the
@@ -726,7 +747,7 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
     SearchArgs a{};
     plan_search(*p, 0, p->n_mappings, 1, a);
     p->table_full = p->table;
-    set_enumeration(*p, enumeration(*p, true, int(a.inner_digits), a.prefix != 0),
+    set_enumeration(*p, enumeration(*p, true, int(a.inner_digits), a.prefix != 0 || a.thin != 0),
                     p->table_full.data());
     write_walk(a, p->table_full.data());
   } catch (const std::bad_alloc&) {
@@ -1474,16 +1495,15 @@ int sched_eval_mappings(const sched_problem* p, const uint64_t* h_idx, int64_t n
   if (h_idx == nullptr || h_makespan == nullptr) return SCHED_E_NULL;
   for (int64_t i = 0; i < n; ++i)
     if (h_idx[i] >= p->n_mappings) return SCHED_E_RANGE;
-  // the table, then chunks of indices and makespans (8 bytes each) in the
-  // rest of the workspace
+  // the table, then chunks of indices in the rest of the workspace, overwritten
+  // by their makespans
   const size_t head = align_up(size_t(p->table_words) * 4);
   int rc = check_workspace(d_workspace, ws_bytes, head + kAlign + 16);
   if (rc != SCHED_OK) return rc;
-  // chunk indices, then chunk makespans at the next 256-byte boundary: fits
-  const int64_t chunk = int64_t(std::min<size_t>((ws_bytes - head - kAlign) / 16, size_t(1) << 24));
+  const int64_t chunk = int64_t(std::min<size_t>((ws_bytes - head - kAlign) / 8, size_t(1) << 24));
   char* ws = static_cast<char*>(d_workspace);
   uint64_t* d_idx = reinterpret_cast<uint64_t*>(ws + head);
-  int64_t* d_out = reinterpret_cast<int64_t*>(ws + head + align_up(size_t(chunk) * 8));
+  int64_t* d_out = reinterpret_cast<int64_t*>(d_idx);  // (each index read before it is overwritten)
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   for (int64_t at = 0; at < n; at += chunk) {
     const int64_t m = std::min(chunk, n - at);
@@ -1715,13 +1735,14 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       plan_search(sub, 0, sub.n_mappings, n_rest, a);
       // One table over all of the children.
       const uint64_t rest = sub.n_mappings / a.inner_count;  // outer combinations of a child
-      const Seq low = enumeration(sub, true, int(a.inner_digits), a.prefix != 0);
+      const Seq low = enumeration(sub, true, int(a.inner_digits), (a.prefix | a.thin) != 0);
       seq.assign(low.v, low.v + low.n);
       seq.insert(seq.end(), upper.begin(), upper.end());
       set_enumeration(*p, seq, stab.data());
       a.outer_lo = 0;
       a.n_outer = rest * n_rest;
       a.n_tables = 1;
+      a.lanes = 64;
       a.items_per_table = (a.n_outer + kBlock - 1) / kBlock;
       a.blocks_per_table = a.n_blocks =
           uint32_t(std::min<uint64_t>(a.items_per_table, kMaxBlocks));
@@ -1749,7 +1770,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       }
       st.mappings_searched += uint64_t(n_rest) * sub.n_mappings;
       st.launches += 1;
-      st.shared_prefix_launches += a.prefix ? 1 : 0;
+      st.shared_prefix_launches += a.prefix | a.thin;
     }
     h_out->best_index = best_ms == INT64_MAX ? ~0ull : best_x;
     h_out->makespan_us = best_ms;

@@ -91,7 +91,8 @@ enum : uint32_t {
   kHdrParentHi = 29,
   kHdrParents = 30,
   kHdrChildren = 31,
-  kHdrWords = 32,
+  kHdrLanes = 32,     // lanes per wave that take an outer combination (SearchArgs::lanes)
+  kHdrWords = 33,
 };
 
 // A fan-out (no edges) whose footprints all fit the budget together, scored
@@ -228,6 +229,9 @@ struct SearchArgs {
   uint32_t closed;            // kClosed*: all tables are of this kind; inner_digits is then the
                               // number of last labels walked per lane
   int32_t variant;            // kVar*
+  uint32_t lanes;             // lanes per wave that take an outer combination: all 64, or fewer
+                              // where the GPU has waves to spare
+  uint32_t thin;              // 1: shared prefixes as with prefix, but in such waves
   uint32_t one_result;        // 1: the tables are parts of one search, results has one entry
   uint32_t* record;           // full range, one table: every scored mapping's makespan
                               // (kInf if infeasible) goes to record[index]; null: none

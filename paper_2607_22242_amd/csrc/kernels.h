@@ -1009,9 +1009,27 @@ __host__ __device__ __forceinline__ uint32_t walk_inner_digits(const SearchArgs&
 __host__ __device__ __forceinline__ uint32_t walk_inner_count(const SearchArgs& a) {
   return a.inner_count;
 }
+// The outer combination (from the walk's first) of a lane in a work item, or
+// one beyond them all.
+__host__ __device__ __forceinline__ uint64_t walk_rel(const SearchArgs&, uint64_t item,
+                                                     uint32_t lane) {
+  return item * kBlock + lane;
+}
 struct TabWalk {
   Tab t;
 };
+__host__ __device__ __forceinline__ uint32_t walk_lanes(const TabWalk& w) {
+  return w.t[kHdrLanes];
+}
+__host__ __device__ __forceinline__ uint64_t walk_rel(const TabWalk& w, uint64_t item,
+                                                     uint32_t lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t lanes = walk_lanes(w), wl = lane & 63u;
+  return wl < lanes ? (item * (kBlock / 64) + (lane >> 6)) * lanes + wl : ~0ull;
+#else
+  return item * kBlock + lane;
+#endif
+}
 // (an address that is 0 or that of the pairs)
 __host__ __device__ __forceinline__ const uint2* list_at(Tab t, uint32_t lo_word) {
   return reinterpret_cast<const uint2*>(uint64_t(t[lo_word]) | (uint64_t(t[lo_word + 1]) << 32));
@@ -1051,7 +1069,7 @@ __host__ __device__ __forceinline__ void lane_search(const Walk& a,
                                                      uint64_t& best_x, Rec rec = Rec()) {
   using M = MaskT<N>;
   using I = IdxT<N>;
-  const uint64_t rel = item * kBlock + lane;
+  const uint64_t rel = walk_rel(a, item, lane);
   if (rel >= walk_n_outer(a)) return;
   const uint32_t levels = tab[kHdrLevels];
   const uint32_t budget = tab[kHdrBudget];
@@ -1386,7 +1404,7 @@ __host__ __device__ __forceinline__ void lane_search_prefix(const Walk& a,
                                                             Rec rec = Rec()) {
   using M = MaskT<N>;
   using I = IdxT<N>;
-  const uint64_t rel = item * kBlock + lane;
+  const uint64_t rel = walk_rel(a, item, lane);
   const uint32_t wl = lane_in_wave(lane);
   uint32_t* const snap0 = snap - wl;  // LDS column of the wave's lane 0
   const uint32_t levels = tab[kHdrLevels];
@@ -1576,7 +1594,8 @@ search_kernel(SearchArgs a, TableArg) {
   uint64_t best_x = ~0ull;
   if constexpr (FULL) {
     const TabWalk walk{Tab{tab}};
-    const uint64_t items = (walk_n_outer(walk) + (kBlock - 1)) / kBlock;
+    const uint32_t per_item = walk_lanes(walk) * (kBlock / 64);
+    const uint64_t items = (walk_n_outer(walk) + (per_item - 1)) / per_item;
     const RecordTo rec{a.record};
     if constexpr (VAR != kVarAll) {
       for (uint64_t item = bb; item < items; item += nb)
@@ -1763,10 +1782,10 @@ hipError_t launch_bound_n(const uint32_t* tab, uint32_t K, uint64_t known, int64
 
 template <int N>
 hipError_t launch_eval_n(const EvalArgs& e, uint32_t host_words, uint32_t flags, hipStream_t s) {
+  EvalArgs a = e;
   int64_t blocks = (e.n + kBlock - 1) / kBlock;
   if (blocks > 65536) blocks = 65536;
   if (blocks < 1) blocks = 1;
-  EvalArgs a = e;
   TableArg t;
   if (flags & kEvalHostTable) {
     if (host_words > kArgWords) return hipErrorInvalidValue;
