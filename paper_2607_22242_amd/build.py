@@ -12,12 +12,12 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libsched.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
-# (source, extra flags); the kernel instantiations are split by tool count so
-# that they compile in parallel.
-INST_PARTS = [(1, 12), (13, 17), (18, 21), (22, 25), (26, 29), (30, 32), (33, 36), (37, 40)]
-UNITS = [("api.cpp", []), ("monitor.cpp", []), ("dispatch.hip", []), ("probe.hip", []),
-         ("scratch.hip", []), ("closed.hip", [])] + [
-    ("inst.hip", [f"-DINST_LO={lo}", f"-DINST_HI={hi}"]) for lo, hi in INST_PARTS]
+# (source, extra flags); the kernel instantiations are one unit per tool count,
+# the longest to compile first, so that they fill the compiler jobs evenly.
+INST_PARTS = [(n, n) for n in range(40, 0, -1)]
+UNITS = [("inst.hip", [f"-DINST_LO={lo}", f"-DINST_HI={hi}"]) for lo, hi in INST_PARTS] + [
+    ("api.cpp", []), ("monitor.cpp", []), ("dispatch.hip", []), ("probe.hip", []),
+    ("scratch.hip", []), ("closed.hip", [])]
 ARCH = "gfx950"
 
 
