@@ -167,9 +167,11 @@ int sched_bruteforce_argmin(const sched_problem *p, uint64_t lo, uint64_t hi,
 /* For callers that cannot allocate device memory or pass a workspace (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): sched_bruteforce_argmin without a workspace argument.  The
- * table, block partials and result live in a fixed per-GPU array of the
+ * tables, block partials and result live in a fixed per-GPU array of the
  * library (2 MiB, held by each GPU the library runs on until the process
- * ends); the call allocates nothing (no hipMalloc, hipFree or heap memory).
+ * ends; the tables of a partial range are put together in 128 KiB of host
+ * memory per GPU, fixed too); the call allocates nothing (no hipMalloc,
+ * hipFree or heap memory).
  * Every call on a GPU shares that GPU's array: calls that overlap on one GPU
  * (several host threads or streams at once) race and must be serialized by
  * the caller.  Nothing in the array needs to start at zero: each call writes

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <numeric>
@@ -522,9 +523,10 @@ struct Part {
 constexpr uint64_t kPartMin = 19683;
 constexpr int kMaxParts = 24;
 
-// The tables of a launch over parts, and where they are staged: a stack buffer
-// (the entry point that allocates nothing searches this way too).
-constexpr size_t kStageWords = size_t(1) << 15;
+// Words that the tables of a launch over parts and their first blocks take.
+size_t parts_words(const sched_problem& p) {
+  return size_t(kMaxParts) * p.table_words + kMaxParts + 1;
+}
 
 int split_range(const sched_problem& p, uint64_t lo, uint64_t hi, Part* out) {
   const int P = int(p.enum_tools.size());
@@ -570,8 +572,7 @@ bool range_in_parts(const sched_problem& p, uint64_t lo, uint64_t hi) {
   if (p.n >= kCompactSnapN || !prefix_able(p, p.n)) return false;
   uint64_t inner = 1;
   for (uint32_t j = 0; j < kSharedInner; ++j) inner *= 3;
-  return (hi - lo) / inner >= kTargetLanes &&
-         size_t(kMaxParts) * p.table_words + kMaxParts + 1 <= kStageWords;
+  return (hi - lo) / inner >= kTargetLanes && parts_words(p) <= kStageWords;
 }
 
 // Enumeration order of a part: its free tools deepest first, then the tools
@@ -984,8 +985,7 @@ PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
 // Bytes of the tables of one search: one table, or those of a range's parts
 // and their first blocks.
 size_t one_search_tables(const sched_problem& p) {
-  const size_t table = size_t(p.table_words) * 4;
-  return range_in_parts(p, 0, p.n_mappings) ? kMaxParts * table + (kMaxParts + 1) * 4 : table;
+  return 4 * (range_in_parts(p, 0, p.n_mappings) ? parts_words(p) : size_t(p.table_words));
 }
 
 // Workspace bytes of one search.
@@ -994,7 +994,7 @@ size_t one_search_bytes(const sched_problem& p) {
 }
 
 // Plan and tables of a search over the parts of [lo, hi), staged in `stage`
-// (kStageWords): n_tables tables, then their first blocks.  Returns the number
+// (parts_words): n_tables tables, then their first blocks.  Returns the number
 // of staged words.
 size_t stage_parts(const sched_problem& p, uint64_t lo, uint64_t hi, SearchArgs& a,
                    uint32_t* stage) {
@@ -1036,23 +1036,31 @@ size_t stage_parts(const sched_problem& p, uint64_t lo, uint64_t hi, SearchArgs&
   return size_t(n) * p.table_words + size_t(n) + 1;
 }
 
-// A partial range searched in parts, in workspace ws.  Allocates nothing.
+// A partial range searched in parts, in workspace ws, its tables staged in
+// `stage` (kStageWords; null: heap memory of this call's, for the tables of 24
+// parts are more than a small thread stack holds).
 int search_parts(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
-                 sched_result* h_out) {
+                 uint32_t* stage, sched_result* h_out) {
   const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
   SearchArgs a{};
-  uint32_t stage[kStageWords];
+  std::unique_ptr<uint32_t[]> heap;
+  if (stage == nullptr) {
+    heap.reset(new (std::nothrow) uint32_t[parts_words(p)]);
+    if (heap == nullptr) return SCHED_E_NOMEM;
+    stage = heap.get();
+  }
   const size_t words = stage_parts(p, lo, hi, a, stage);
   a.tables = reinterpret_cast<const uint32_t*>(ws + L.tables);
   a.table_stride = p.table_words;
   a.block_first = a.tables + size_t(a.n_tables) * p.table_words;
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
   a.results = reinterpret_cast<DevResult*>(ws + L.results);
-  HIP_TRY(hipMemcpyAsync(ws + L.tables, stage, words * 4, hipMemcpyHostToDevice, s));
-  HIP_TRY(launch_search(p.n, a, s));
   DevResult r;
-  HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  hipError_t e = hipMemcpyAsync(ws + L.tables, stage, words * 4, hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = launch_search(p.n, a, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s);
+  HIP_TRY(hipStreamSynchronize(s));  // (after an error too: the copy may still read the stage)
+  HIP_TRY(e);
   h_out->best_index = r.index;
   h_out->makespan_us = r.makespan;
   return SCHED_OK;
@@ -1186,14 +1194,15 @@ static_assert(kHostPartials * sizeof(Partial) <= kSlotBytes, "partials of a smal
 
 // One search of [lo, hi) in workspace ws (at least one_search_bytes) on stream
 // s, then the result.  record: every mapping's makespan (full ranges only;
-// null: none).  slots: whether the call may use page-locked memory (which the
-// first call allocates); otherwise it allocates nothing.
+// null: none).  stage: null, or kStageWords of host memory for the tables of a
+// range's parts: the call then allocates nothing, page-locked slots (which the
+// first call that wants one allocates) included.
 int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
-               uint32_t* record, bool slots, sched_result* h_out) {
+               uint32_t* record, uint32_t* stage, sched_result* h_out) {
   const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
   SearchArgs a{};
   if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi))
-    return search_parts(p, lo, hi, ws, s, h_out);
+    return search_parts(p, lo, hi, ws, s, stage, h_out);
   plan_search(p, lo, hi, 1, a);
   if (a.full_range) plan_closed(p, a);
   const std::vector<uint32_t>& table = a.full_range ? p.table_full : p.table;
@@ -1211,8 +1220,8 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipSt
   }
   DevResult r;
   std::optional<Slot> slot;
-  if (slots) slot.emplace(s);
-  char* const h = slots ? slot->data() : nullptr;
+  if (stage == nullptr) slot.emplace(s);
+  char* const h = slot ? slot->data() : nullptr;
   if (h != nullptr) {
     const bool small = a.n_blocks <= kHostPartials;
     if (small) {
@@ -1338,7 +1347,7 @@ int sched_bruteforce_argmin(const sched_problem* p, uint64_t lo, uint64_t hi, vo
   const int rc = check_workspace(d_workspace, ws_bytes, one_search_bytes(*p));
   if (rc != SCHED_OK) return rc;
   return search_one(*p, lo, hi, static_cast<char*>(d_workspace),
-                    reinterpret_cast<hipStream_t>(hip_stream), nullptr, true, h_out);
+                    reinterpret_cast<hipStream_t>(hip_stream), nullptr, nullptr, h_out);
 }
 
 int sched_bruteforce_argmin_noalloc(const sched_problem* p, uint64_t lo, uint64_t hi,
@@ -1347,9 +1356,10 @@ int sched_bruteforce_argmin_noalloc(const sched_problem* p, uint64_t lo, uint64_
   if (lo >= hi || hi > p->n_mappings) return SCHED_E_RANGE;
   if (one_search_bytes(*p) > kScratchBytes) return SCHED_E_WORKSPACE;
   void* ws = nullptr;
-  HIP_TRY(scratch_buffer(&ws));
+  uint32_t* stage = nullptr;
+  HIP_TRY(scratch_buffer(&ws, &stage));
   return search_one(*p, lo, hi, static_cast<char*>(ws), reinterpret_cast<hipStream_t>(hip_stream),
-                    nullptr, false, h_out);
+                    nullptr, stage, h_out);
 }
 
 int sched_bruteforce_record(const sched_problem* p, void* d_workspace, size_t ws_bytes,
@@ -1360,7 +1370,7 @@ int sched_bruteforce_record(const sched_problem* p, void* d_workspace, size_t ws
   const int rc = check_workspace(d_workspace, ws_bytes, one_search_bytes(*p));
   if (rc != SCHED_OK) return rc;
   return search_one(*p, 0, p->n_mappings, static_cast<char*>(d_workspace),
-                    reinterpret_cast<hipStream_t>(hip_stream), d_makespan, true, h_out);
+                    reinterpret_cast<hipStream_t>(hip_stream), d_makespan, nullptr, h_out);
 }
 
 int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,

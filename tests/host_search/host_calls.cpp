@@ -1,0 +1,350 @@
+// host_calls.cpp -- test harness: the library's calls (api.cpp) on a stand-in
+// for the HIP runtime, so that their host side can be checked on the CPU.
+// Copies and launches wait in their stream's list, each with the arguments it
+// was given, and run when the stream is waited for; "device" memory is host
+// memory.  A launch over tables of HOST_CALLS_N tools (macro, a list) runs the
+// kernels' per-lane code, one lane per wave, block by block; a closed-form
+// launch scores the table's mappings one by one.
+//
+// argv[1] is the check to run; problems come on stdin, each as: n_tools share
+// n_edges n_levels budget, then n_tools lines "gpu cpu load xfer mem allowed",
+// n_edges lines "src dst", then the n_levels Q16 contention factors.
+#include "../../paper_2607_22242_amd/csrc/api.cpp"
+#include "../../paper_2607_22242_amd/csrc/kernels.h"
+
+#include <pthread.h>
+
+#include <atomic>
+#include <cstdio>
+#include <cstdlib>
+#include <functional>
+#include <map>
+#include <string>
+
+#ifndef HOST_CALLS_N
+#define HOST_CALLS_N 6, 10
+#endif
+
+// ---------------------------------------------------------------------------
+// The runtime.
+
+static std::mutex g_mutex;
+static std::map<hipStream_t, std::vector<std::function<void()>>> g_work;
+static std::atomic<int> g_page_locked{0};     // successful hipHostMalloc calls
+static std::atomic<int> g_fail_page_locked{0};  // calls that will fail
+static bool g_plan_only = false;              // launches score nothing
+static thread_local long t_news = 0;          // heap allocations of this thread
+
+static void enqueue(hipStream_t s, std::function<void()> f) {
+  std::lock_guard<std::mutex> lock(g_mutex);
+  g_work[s].push_back(std::move(f));
+}
+
+void* operator new(size_t n) {
+  ++t_news;
+  if (void* p = malloc(n)) return p;
+  throw std::bad_alloc();
+}
+void* operator new[](size_t n) { return operator new(n); }
+void* operator new(size_t n, const std::nothrow_t&) noexcept { ++t_news; return malloc(n); }
+void* operator new[](size_t n, const std::nothrow_t&) noexcept { ++t_news; return malloc(n); }
+void operator delete(void* p) noexcept { free(p); }
+void operator delete[](void* p) noexcept { free(p); }
+void operator delete(void* p, size_t) noexcept { free(p); }
+void operator delete[](void* p, size_t) noexcept { free(p); }
+
+// The stand-in's own allocations are not the library's.
+struct Uncounted {
+  long at = t_news;
+  ~Uncounted() { t_news = at; }
+};
+
+extern "C" {
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
+  if (g_fail_page_locked > 0) {
+    --g_fail_page_locked;
+    return hipErrorOutOfMemory;
+  }
+  ++g_page_locked;
+  *p = calloc(1, n);
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
+  Uncounted u;
+  enqueue(st, [=] { memcpy(d, s, n); });
+  return hipSuccess;
+}
+hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) {
+  Uncounted u;
+  enqueue(st, [=] { memset(d, v, n); });
+  return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t st) {
+  Uncounted u;
+  std::vector<std::function<void()>> w;
+  {
+    std::lock_guard<std::mutex> lock(g_mutex);
+    w.swap(g_work[st]);
+  }
+  for (auto& f : w) f();
+  return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+}
+
+// ---------------------------------------------------------------------------
+// The kernels.
+
+// What the launches did.
+static std::atomic<int> g_launches{0}, g_shared{0}, g_max_tables{0};
+
+namespace devmap {
+
+template <int N, bool SHARE>
+static uint32_t score_y(const uint32_t* tab, const uint32_t* lds, uint64_t y, uint64_t& x) {
+  MaskT<N> gn, gq, slot = 0;
+  decode_positions<N>(tab, y, 0, tab[kHdrPositions], gn, gq, x);
+  if constexpr (SHARE)
+    return evaluate_sharing<N>(tab, lds, tab[kHdrLevels], tab[kHdrBudget], gn, gq, &slot);
+  else
+    return evaluate<N>(tab, lds, tab[kHdrLevels], tab[kHdrBudget], gn, gq, &slot);
+}
+
+static void take_min(uint32_t& ms, uint64_t& x, uint32_t m, uint64_t y) {
+  if (m < ms || (m == ms && y < x)) {
+    ms = m;
+    x = y;
+  }
+}
+
+// One search launch, its table (if it came with the arguments) in `own`.
+template <int N, bool SHARE>
+static void search(const SearchArgs& a, const uint32_t* own) {
+  std::vector<uint32_t> snap(snap_words<N, SHARE>() * kBlock);
+  uint64_t word = 0;
+  MaskT<N>* slot = reinterpret_cast<MaskT<N>*>(&word);
+  uint32_t table = 0;
+  for (uint32_t b = 0; b < a.n_blocks; ++b) {
+    uint32_t bb, nb;
+    if (a.block_first != nullptr) {
+      while (a.block_first[table + 1] <= b) ++table;
+      bb = b - a.block_first[table];
+      nb = a.block_first[table + 1] - a.block_first[table];
+    } else {
+      nb = a.blocks_per_table;
+      table = b / nb;
+      bb = b % nb;
+    }
+    const uint32_t* tab = a.tables != nullptr ? a.tables + size_t(table) * a.table_stride : own;
+    std::vector<uint32_t> lds(lds_words_for(N, tab[kHdrLevels]));
+    stage_image<N>(tab, lds.data(), 0, 1);
+    uint32_t ms = kInf;
+    uint64_t x = ~0ull;
+    if (a.closed != kClosedNone) {
+      uint64_t total = 1;
+      for (uint32_t k = 0; k < tab[kHdrPositions]; ++k)
+        total *= opt_radix(tab[enum_opt_base(tab[kHdrN]) + k]);
+      for (uint64_t y = bb; y < total; y += nb) {
+        uint64_t yx;
+        const uint32_t m = score_y<N, SHARE>(tab, lds.data(), y, yx);
+        if (a.record) a.record[yx] = m;
+        take_min(ms, x, m, m == kInf ? ~0ull : yx);
+      }
+    } else if (a.full_range) {
+      const TabWalk walk{Tab{tab}};
+      const RecordTo rec{a.record};
+      const uint64_t items = (walk_n_outer(walk) + kBlock - 1) / kBlock;
+      for (uint64_t item = bb; item < items; item += nb)
+        for (uint32_t lane = 0; lane < uint32_t(kBlock); ++lane)
+          if (tab[kHdrPrefix])
+            lane_search_prefix<N, SHARE>(walk, tab, lds.data(), item, lane, slot,
+                                         snap.data() + lane, ms, x, rec);
+          else
+            lane_search<N, true, SHARE>(walk, tab, lds.data(), item, lane, slot, ms, x, rec);
+    } else {
+      for (uint64_t item = bb; item < a.items_per_table; item += nb)
+        for (uint32_t lane = 0; lane < uint32_t(kBlock); ++lane)
+          lane_search<N, false, SHARE>(a, tab, lds.data(), item, lane, slot, ms, x);
+    }
+    a.partials[b] = Partial{x, ms, 0};
+  }
+}
+
+template <int N>
+static void eval(const EvalArgs& e, const uint32_t* tab, bool share) {
+  std::vector<uint32_t> lds(lds_words<N>());
+  stage_image<N>(tab, lds.data(), 0, 1);
+  for (int64_t i = 0; i < e.n; ++i) {
+    uint64_t x;
+    const uint64_t y = e.idx[i];
+    uint32_t ms = kInf;
+    if (y < e.n_mappings)
+      ms = share ? score_y<N, true>(tab, lds.data(), y, x) : score_y<N, false>(tab, lds.data(), y, x);
+    e.out[i] = ms == kInf ? INT64_MAX : int64_t(ms);
+  }
+}
+
+// Calls f with the integral constant of n among the tool counts built.
+template <class F, int... NS>
+static void on_tools(int n, F f, std::integer_sequence<int, NS...>) {
+  const bool found = ((n == NS ? (f(std::integral_constant<int, NS>{}), true) : false) || ...);
+  if (!found) {
+    fprintf(stderr, "no kernel for %d tools\n", n);
+    abort();
+  }
+}
+using Built = std::integer_sequence<int, HOST_CALLS_N>;
+
+hipError_t launch_search(int n, const SearchArgs& args, hipStream_t s) {
+  Uncounted u;
+  std::vector<uint32_t> own;
+  if (args.tables == nullptr) own.assign(args.host_table, args.host_table + args.host_words);
+  ++g_launches;
+  if (int(args.n_tables) > g_max_tables) g_max_tables = int(args.n_tables);
+  enqueue(s, [=] {
+    SearchArgs a = args;
+    const uint32_t* tab = own.empty() ? a.tables : own.data();
+    if (a.closed == kClosedNone && a.full_range && tab[kHdrPrefix]) ++g_shared;
+    if (g_plan_only)
+      for (uint32_t b = 0; b < a.n_blocks; ++b) a.partials[b] = Partial{a.n_tables, a.n_blocks, 0};
+    else
+      on_tools(n, [&](auto N) {
+        a.sharing ? search<N(), true>(a, own.data()) : search<N(), false>(a, own.data());
+      }, Built{});
+    if (a.results == nullptr) return;
+    const uint32_t results = a.one_result ? 1u : a.n_tables;
+    for (uint32_t r = 0; r < results; ++r) {
+      const bool listed = !a.one_result && a.block_first != nullptr;
+      const uint32_t per = a.n_blocks / results;
+      const uint32_t lo = listed ? a.block_first[r] : r * per;
+      const uint32_t hi = listed ? a.block_first[r + 1] : lo + per;
+      uint32_t ms = kInf;
+      uint64_t x = ~0ull;
+      for (uint32_t b = lo; b < hi; ++b) take_min(ms, x, a.partials[b].makespan, a.partials[b].index);
+      a.results[r] = DevResult{ms == kInf ? ~0ull : x, ms == kInf ? INT64_MAX : int64_t(ms)};
+    }
+  });
+  return hipSuccess;
+}
+
+hipError_t launch_eval(int n, const uint32_t* tab, const uint64_t* idx, int64_t m,
+                       uint64_t n_mappings, int64_t* out, uint32_t flags, hipStream_t s) {
+  Uncounted u;
+  std::vector<uint32_t> own;
+  if (flags & kEvalHostTable) own.assign(tab, tab + bound_base(uint32_t(n), tab[kHdrLevels]));
+  enqueue(s, [=] {
+    const uint32_t* t = own.empty() ? tab : own.data();
+    const EvalArgs e{t, idx, m, n_mappings, out};
+    on_tools(n, [&](auto N) { eval<N()>(e, t, (flags & kEvalSharing) != 0); }, Built{});
+  });
+  return hipSuccess;
+}
+
+hipError_t launch_bound(int, const uint32_t*, uint32_t, uint64_t, int64_t, uint32_t, uint32_t*,
+                        uint2*, hipStream_t) {
+  return hipErrorUnknown;
+}
+hipError_t launch_valu_probe(uint32_t, uint32_t, uint32_t*, hipStream_t, double*) {
+  return hipErrorUnknown;
+}
+hipError_t launch_wave_or_probe(const uint64_t*, const uint8_t*, uint32_t, uint64_t*, uint32_t*,
+                                hipStream_t) {
+  return hipErrorUnknown;
+}
+hipError_t scratch_buffer(void** ptr, uint32_t** stage) {
+  static char* const buf = static_cast<char*>(aligned_alloc(256, kScratchBytes));
+  static uint32_t words[kStageWords];
+  *ptr = buf;
+  *stage = words;
+  return hipSuccess;
+}
+}  // namespace devmap
+
+using namespace devmap;
+
+// ---------------------------------------------------------------------------
+// Problems and workspaces.
+
+static sched_problem* read_problem() {
+  int n, share, ne, nl;
+  long long budget;
+  if (scanf("%d %d %d %d %lld", &n, &share, &ne, &nl, &budget) != 5) return nullptr;
+  std::vector<sched_tool> tools(n);
+  std::vector<uint8_t> allowed(n);
+  for (int v = 0; v < n; ++v) {
+    long long g, c, l, x, m;
+    int al;
+    if (scanf("%lld %lld %lld %lld %lld %d", &g, &c, &l, &x, &m, &al) != 6) return nullptr;
+    tools[v] = sched_tool{g, c, l, x, m};
+    allowed[v] = uint8_t(al);
+  }
+  std::vector<sched_edge> e(ne);
+  for (auto& x : e)
+    if (scanf("%d %d", &x.src, &x.dst) != 2) return nullptr;
+  std::vector<uint32_t> f(nl);
+  for (auto& x : f)
+    if (scanf("%u", &x) != 1) return nullptr;
+  sched_problem* p = nullptr;
+  sched_problem_desc d{tools.data(), n, e.data(), ne, f.data(), nl, budget, allowed.data(), share};
+  return sched_problem_create_desc(&d, &p) == SCHED_OK ? p : nullptr;
+}
+
+#define CHECK(cond)                                                   \
+  do {                                                                \
+    if (!(cond)) {                                                    \
+      fprintf(stderr, "%s:%d: not %s\n", __FILE__, __LINE__, #cond);  \
+      exit(1);                                                        \
+    }                                                                 \
+  } while (0)
+
+struct Workspace {
+  size_t bytes;
+  void* p;
+  explicit Workspace(size_t n) : bytes(n), p(aligned_alloc(256, (n + 255) / 256 * 256)) {}
+  ~Workspace() { free(p); }
+};
+
+static size_t bytes_for(const std::vector<sched_problem*>& ps, int replicas) {
+  size_t n = 0;
+  CHECK(sched_workspace_bytes(ps.data(), int(ps.size()), replicas, &n) == SCHED_OK);
+  return n;
+}
+
+// ---------------------------------------------------------------------------
+// Checks.
+
+// A range in parts, called with little stack: both entry points, and no heap
+// allocation in the one that promises none.
+static sched_problem* g_problem;
+static void* range_call(void*) {
+  sched_problem* const p = g_problem;
+  Workspace ws(bytes_for({p}, 0));
+  sched_result a{}, b{};
+  const uint64_t lo = 1, hi = p->n_mappings - 1;
+  CHECK(sched_bruteforce_argmin(p, lo, hi, ws.p, ws.bytes, nullptr, &a) == SCHED_OK);
+  CHECK(a.best_index > 1);  // (the tables of the launch)
+  const long news = t_news;
+  CHECK(sched_bruteforce_argmin_noalloc(p, lo, hi, nullptr, &b) == SCHED_OK);
+  CHECK(t_news == news);
+  CHECK(a.best_index == b.best_index && a.makespan_us == b.makespan_us);
+  return nullptr;
+}
+static void check_stack() {
+  g_plan_only = true;
+  CHECK((g_problem = read_problem()) != nullptr);
+  CHECK(range_in_parts(*g_problem, 1, g_problem->n_mappings - 1));
+  pthread_attr_t attr;
+  pthread_attr_init(&attr);
+  CHECK(pthread_attr_setstacksize(&attr, 64 << 10) == 0);
+  pthread_t t;
+  CHECK(pthread_create(&t, &attr, range_call, nullptr) == 0);
+  pthread_join(t, nullptr);
+}
+
+int main(int argc, char** argv) {
+  const std::string what = argc > 1 ? argv[1] : "";
+  if (what == "stack") check_stack();
+  else return 2;
+  puts("ok");
+  return 0;
+}

@@ -33,7 +33,7 @@ hipError_t launch_wave_or_probe(const uint64_t*, const uint8_t*, uint32_t, uint6
                                 hipStream_t) {
   return hipErrorUnknown;
 }
-hipError_t scratch_buffer(void**) { return hipErrorUnknown; }
+hipError_t scratch_buffer(void**, uint32_t**) { return hipErrorUnknown; }
 }  // namespace devmap
 
 using namespace devmap;

@@ -1,0 +1,48 @@
+"""The host side of the library's calls, on the CPU: tests/host_search/host_calls.cpp
+runs api.cpp on a stand-in for the HIP runtime whose streams do their work
+when they are waited for."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from workloads import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def host_calls(tmp_path_factory):
+    cc = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
+    cc = cc if os.path.exists(cc) else shutil.which("hipcc")
+    if cc is None:
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("host_calls") / "host_calls")
+    subprocess.check_call([cc, "-O2", "-std=c++17", "-pthread", "-x", "hip", "--offload-arch=gfx950",
+                           "--cuda-host-only",
+                           "-I" + os.path.join(ROOT, "include"),
+                           "-I" + os.path.join(ROOT, "paper_2607_22242_amd", "csrc"),
+                           os.path.join(ROOT, "tests", "host_search", "host_calls.cpp"),
+                           "-o", exe], stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+
+    def run(what, *problems):
+        text = []
+        for inst, allowed, share in problems:
+            allowed = allowed or [7] * len(inst["tools"])
+            text.append(f"{len(allowed)} {int(share)} {len(inst['edges'])} "
+                        f"{len(inst['contention_q16'])} {inst['vram_budget_mib']}")
+            text += [" ".join(map(str, t)) + f" {a}" for t, a in zip(inst["tools"], allowed)]
+            text += [f"{u} {v}" for u, v in inst["edges"]]
+            text.append(" ".join(map(str, inst["contention_q16"])))
+        r = subprocess.run([exe, what], input="\n".join(text) + "\n", capture_output=True, text=True,
+                           timeout=300)
+        assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+        assert r.stdout.endswith("ok\n")
+        return r.stdout.split("\n")[:-2]
+    return run
+
+
+@pytest.mark.parametrize("n,levels", [(15, 4), (19, 19)])
+def test_range_in_parts_needs_little_stack(host_calls, n, levels):
+    host_calls("stack", (synth.random_instance(9900 + n, n, "random", levels=levels), None, False))
