@@ -506,6 +506,17 @@ void plan_closed(const sched_problem& p, SearchArgs& a) {
   a.n_blocks = a.blocks_per_table = uint32_t(std::min<uint64_t>(items, kMaxBlocks));
 }
 
+// The plan of a one-table full-range search.
+void plan_full(const sched_problem& p, SearchArgs& a) {
+  plan_search(p, 0, p.n_mappings, 1, a);
+  plan_closed(p, a);
+}
+
+// Whether a plan's launch shares schedule prefixes (a closed-form one does not).
+int32_t shares_prefixes(const SearchArgs& a) {
+  return a.closed == kClosedNone && (a.prefix | a.thin) != 0 ? 1 : 0;
+}
+
 // A partial range [lo, hi) as parts of a full-order search.  A part of level k
 // is a run of aligned blocks of W_k mappings (W_k: the product of the radices
 // of the first k tools with a choice): the modes of those k tools are free in
@@ -1203,8 +1214,10 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipSt
   SearchArgs a{};
   if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi))
     return search_parts(p, lo, hi, ws, s, stage, h_out);
-  plan_search(p, lo, hi, 1, a);
-  if (a.full_range) plan_closed(p, a);
+  if (lo == 0 && hi == p.n_mappings)
+    plan_full(p, a);
+  else
+    plan_search(p, lo, hi, 1, a);
   const std::vector<uint32_t>& table = a.full_range ? p.table_full : p.table;
   a.table_stride = p.table_words;
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
@@ -1601,7 +1614,9 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       st.prefixes_searched = 1;
       st.mappings_searched = p->n_mappings;
       st.launches = 1;
-      st.shared_prefix_launches = prefix_plan(*p, 1) ? 1 : 0;
+      SearchArgs a{};
+      plan_full(*p, a);
+      st.shared_prefix_launches = shares_prefixes(a);
       st.initial_bound_us = INT64_MAX;
       *stats = st;
     }
@@ -1780,7 +1795,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       }
       st.mappings_searched += uint64_t(n_rest) * sub.n_mappings;
       st.launches += 1;
-      st.shared_prefix_launches += a.prefix | a.thin;
+      st.shared_prefix_launches += shares_prefixes(a);
     }
     h_out->best_index = best_ms == INT64_MAX ? ~0ull : best_x;
     h_out->makespan_us = best_ms;

@@ -341,9 +341,26 @@ static void check_stack() {
   pthread_join(t, nullptr);
 }
 
+// The counters of a pruned search over a space that is searched whole, against
+// what was launched; prints the launches that shared prefixes.
+static void check_stats() {
+  g_plan_only = true;
+  sched_problem* const p = read_problem();
+  CHECK(p != nullptr);
+  size_t n = 0;
+  CHECK(sched_pruned_workspace_bytes(p, &n) == SCHED_OK);
+  Workspace ws(n);
+  sched_result r;
+  sched_prune_stats st;
+  CHECK(sched_pruned_argmin(p, ws.p, ws.bytes, nullptr, &r, &st) == SCHED_OK);
+  CHECK(st.launches == g_launches && st.shared_prefix_launches == g_shared);
+  printf("%d\n", st.shared_prefix_launches);
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
+  else if (what == "stats") check_stats();
   else return 2;
   puts("ok");
   return 0;

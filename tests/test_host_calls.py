@@ -46,3 +46,14 @@ def host_calls(tmp_path_factory):
 @pytest.mark.parametrize("n,levels", [(15, 4), (19, 19)])
 def test_range_in_parts_needs_little_stack(host_calls, n, levels):
     host_calls("stack", (synth.random_instance(9900 + n, n, "random", levels=levels), None, False))
+
+
+@pytest.mark.parametrize("n,shape,masks,shared", [
+    (13, "random", [7] * 13, 1),                # shared prefixes in thin waves
+    (21, "chain", [3] * 21, 0),                 # closed form, in a space that has prefixes enough
+    (21, "permuted", [3] * 21, 1),              # shared prefixes in full waves
+    (12, "random", [7] * 12, 0)])               # too few prefixes
+def test_counters_of_a_space_searched_whole(host_calls, n, shape, masks, shared):
+    inst = synth.random_instance(9920 + n, n, shape)
+    inst["tools"] = [[max(1, x // 20) for x in t[:4]] + [t[4]] for t in inst["tools"]]
+    assert host_calls("stats", (inst, masks, False)) == [str(shared)]
