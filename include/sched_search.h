@@ -27,7 +27,11 @@
  * read (or, for outputs, written) during the call.  The library never
  * allocates device memory: device work runs in the caller's workspace on the
  * caller's HIP stream, and every entry point that launches work waits for
- * that stream before returning.  On error no output is written.
+ * that stream before returning.  The first search, batch or explicit scoring
+ * call page-locks 256 KiB of host memory (8 slots for small calls' indices and
+ * results, shared by all threads and GPUs), held until the process ends; a
+ * call that finds none free copies through its workspace.  On error no output
+ * is written.
  */
 #ifndef SCHED_SEARCH_H
 #define SCHED_SEARCH_H

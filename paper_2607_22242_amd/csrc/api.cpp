@@ -780,28 +780,26 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
 // partial minima) cross the link as part of the kernel.  One allocation of
 // kSlots slots for the process, made at the first call that wants one; a call
 // holds one slot from before its launch until its stream is done with it, and
-// gives it back.  With every slot taken (or none to be had) a call copies
-// through its workspace instead.  A 16-byte result and its copy back measured
+// gives it back.  With every slot taken a call copies through its workspace
+// instead, and so does one whose allocation fails (it may while another thread
+// captures a graph); the next call tries again.  A 16-byte result and its copy back measured
 // 26.4 us from launch to host, written straight to the host 17.6 us.
 constexpr int kSlots = 8;
 constexpr size_t kSlotBytes = size_t(32) << 10;
 std::mutex g_slot_mutex;
 char* g_slots = nullptr;
-bool g_slots_failed = false;
 uint32_t g_slots_taken = 0;
 
 class Slot {
  public:
   explicit Slot(hipStream_t s) : stream_(s) {
     std::lock_guard<std::mutex> lock(g_slot_mutex);
-    if (g_slots == nullptr && !g_slots_failed) {
+    if (g_slots == nullptr) {
       void* p = nullptr;
-      if (hipHostMalloc(&p, kSlots * kSlotBytes, hipHostMallocPortable) == hipSuccess) {
+      if (hipHostMalloc(&p, kSlots * kSlotBytes, hipHostMallocPortable) == hipSuccess)
         g_slots = static_cast<char*>(p);
-      } else {
+      else
         (void)hipGetLastError();
-        g_slots_failed = true;
-      }
     }
     for (int k = 0; g_slots != nullptr && k < kSlots; ++k)
       if (!((g_slots_taken >> k) & 1u)) {

@@ -357,10 +357,96 @@ static void check_stats() {
   printf("%d\n", st.shared_prefix_launches);
 }
 
+// The calls that use slots, against each other's answers: with slots, with none
+// to be had, and with all of them taken.  A failed allocation is tried again.
+struct Answers {
+  std::vector<sched_result> search;
+  std::vector<int64_t> scores;
+  std::vector<sched_probe> probes;
+  std::vector<sched_result> batch;
+  bool operator==(const Answers& o) const {
+    const auto same = [](const auto& a, const auto& b, auto eq) {
+      return a.size() == b.size() && std::equal(a.begin(), a.end(), b.begin(), eq);
+    };
+    const auto res = [](const sched_result& a, const sched_result& b) {
+      return a.best_index == b.best_index && a.makespan_us == b.makespan_us;
+    };
+    const auto probe = [](const sched_probe& a, const sched_probe& b) {
+      return a.index == b.index && a.makespan_us == b.makespan_us && a.kind == b.kind &&
+             a.tool == b.tool && a.mode == b.mode && a.swap_tool == b.swap_tool;
+    };
+    return same(search, o.search, res) && scores == o.scores && same(probes, o.probes, probe) &&
+           same(batch, o.batch, res);
+  }
+};
+
+static Answers call_all(const std::vector<sched_problem*>& ps, int replicas, hipStream_t s) {
+  Answers out;
+  Workspace ws(bytes_for(ps, replicas));
+  for (sched_problem* p : ps) {
+    sched_result r{};
+    CHECK(sched_bruteforce_argmin(p, 0, p->n_mappings, ws.p, ws.bytes, s, &r) == SCHED_OK);
+    out.search.push_back(r);
+    CHECK(sched_bruteforce_argmin(p, 1, p->n_mappings, ws.p, ws.bytes, s, &r) == SCHED_OK);
+    out.search.push_back(r);
+    for (size_t m : {size_t(700), size_t(2048), size_t(2049)}) {
+      std::vector<uint64_t> idx(m);
+      for (size_t k = 0; k < m; ++k) idx[k] = (k * 7919) % p->n_mappings;
+      std::vector<int64_t> ms(m, -1);
+      CHECK(sched_eval_mappings(p, idx.data(), int64_t(m), ws.p, ws.bytes, s, ms.data()) == SCHED_OK);
+      out.scores.insert(out.scores.end(), ms.begin(), ms.end());
+    }
+    std::vector<sched_probe> pr(size_t(1 + 2 * p->n + p->n * (p->n - 1)));
+    int32_t n = 0;
+    CHECK(sched_eval_reprobes(p, p->n_mappings / 2, nullptr, ws.p, ws.bytes, s, pr.data(),
+                              int32_t(pr.size()), &n) == SCHED_OK);
+    out.probes.insert(out.probes.end(), pr.begin(), pr.begin() + n);
+  }
+  std::vector<int32_t> of;
+  std::vector<sched_lat> lat;
+  for (int r = 0; r < replicas; ++r) {
+    const sched_problem* const p = ps[size_t(r) % ps.size()];
+    of.push_back(int32_t(size_t(r) % ps.size()));
+    for (const sched_tool& t : p->tools)
+      lat.push_back({t.gpu_us + r, t.cpu_us + 3 * r, t.load_us + 2 * r, t.xfer_us + r});
+  }
+  out.batch.resize(size_t(replicas));
+  CHECK(sched_eval_batch(ps.data(), int(ps.size()), of.data(), lat.data(), replicas, ws.p, ws.bytes, s,
+                         out.batch.data()) == SCHED_OK);
+  return out;
+}
+
+static void check_slots() {
+  std::vector<sched_problem*> ps;
+  while (sched_problem* p = read_problem()) ps.push_back(p);
+  CHECK(!ps.empty());
+  g_fail_page_locked = 1 << 20;
+  const Answers none = call_all(ps, 20, nullptr);
+  CHECK(g_page_locked == 0 && g_slots == nullptr);
+  g_fail_page_locked = 0;
+  const Answers some = call_all(ps, 20, nullptr);
+  CHECK(g_page_locked == 1 && g_slots_taken == 0);
+  CHECK(some == none);
+  {
+    std::vector<std::unique_ptr<Slot>> all;
+    for (int k = 0; k < kSlots; ++k) {
+      all.push_back(std::make_unique<Slot>(nullptr));
+      CHECK(all.back()->data() == g_slots + size_t(k) * kSlotBytes);
+    }
+    CHECK(Slot(nullptr).data() == nullptr);
+    CHECK(call_all(ps, 20, nullptr) == none);
+    all[3].reset();
+    CHECK(Slot(nullptr).data() == g_slots + 3 * kSlotBytes);
+    CHECK(call_all(ps, 20, nullptr) == none);
+  }
+  CHECK(g_page_locked == 1 && g_slots_taken == 0);
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
   else if (what == "stats") check_stats();
+  else if (what == "slots") check_slots();
   else return 2;
   puts("ok");
   return 0;

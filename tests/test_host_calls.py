@@ -57,3 +57,17 @@ def test_counters_of_a_space_searched_whole(host_calls, n, shape, masks, shared)
     inst = synth.random_instance(9920 + n, n, shape)
     inst["tools"] = [[max(1, x // 20) for x in t[:4]] + [t[4]] for t in inst["tools"]]
     assert host_calls("stats", (inst, masks, False)) == [str(shared)]
+
+
+def small_problems():
+    """Four problems of 6 and 10 tools: both contention readings, a chain, a
+    fan-out that fits its budget, restricted modes."""
+    fan = synth.random_instance(9942, 6, "fanout")
+    fan["vram_budget_mib"] = sum(t[4] for t in fan["tools"])
+    return [(synth.random_instance(9940, 6, "random", tight=True), None, False),
+            (synth.random_instance(9941, 6, "chain"), None, True), (fan, None, False),
+            (synth.random_instance(9943, 10, "permuted"), [3, 7, 1, 5, 3, 7, 2, 3, 6, 3], False)]
+
+
+def test_calls_without_a_slot(host_calls):
+    host_calls("slots", *small_problems())
