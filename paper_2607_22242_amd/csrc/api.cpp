@@ -1452,11 +1452,12 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     }
 
     HIP_TRY(hipMemcpyAsync(d_tables, host.data(), host.size() * 4, hipMemcpyHostToDevice, s));
-    Slot slot(s);
-    char* const h = R * sizeof(DevResult) <= kSlotBytes ? slot.data() : nullptr;
+    std::optional<Slot> slot;
+    if (R * sizeof(DevResult) <= kSlotBytes) slot.emplace(s);
+    char* const h = slot ? slot->data() : nullptr;
     DevResult* const results = reinterpret_cast<DevResult*>(h ? h : ws + L.results);
     const uint32_t* d_first = d_tables + R * stride;
-    if (h) slot.launched();
+    if (h) slot->launched();
     for (Launch& g : launches) {
       SearchArgs& a = g.a;
       a.tables = d_tables + g.first * stride;
@@ -1471,8 +1472,10 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     if (!h)
       HIP_TRY(hipMemcpyAsync(res.data(), results, R * sizeof(DevResult), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    slot.waited();
-    if (h) std::memcpy(res.data(), h, R * sizeof(DevResult));
+    if (h) {
+      slot->waited();
+      std::memcpy(res.data(), h, R * sizeof(DevResult));
+    }
     for (size_t i = 0; i < R; ++i) {
       h_out[order[i]].best_index = res[i].index;
       h_out[order[i]].makespan_us = res[i].makespan;

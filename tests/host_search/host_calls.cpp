@@ -97,6 +97,7 @@ hipError_t hipGetLastError(void) { return hipSuccess; }
 
 // What the launches did.
 static std::atomic<int> g_launches{0}, g_shared{0}, g_max_tables{0};
+static std::atomic<uint32_t> g_slots_held{0};  // by the calls of the launches
 
 namespace devmap {
 
@@ -201,6 +202,10 @@ hipError_t launch_search(int n, const SearchArgs& args, hipStream_t s) {
   if (args.tables == nullptr) own.assign(args.host_table, args.host_table + args.host_words);
   ++g_launches;
   if (int(args.n_tables) > g_max_tables) g_max_tables = int(args.n_tables);
+  {
+    std::lock_guard<std::mutex> lock(g_slot_mutex);
+    g_slots_held |= g_slots_taken;
+  }
   enqueue(s, [=] {
     SearchArgs a = args;
     const uint32_t* tab = own.empty() ? a.tables : own.data();
@@ -442,11 +447,39 @@ static void check_slots() {
   CHECK(g_page_locked == 1 && g_slots_taken == 0);
 }
 
+// Batches whose results fit a slot, fill it, and do not fit: each replica's
+// answer is that of a search of its own.
+static void check_replicas() {
+  sched_problem* const p = read_problem();
+  CHECK(p != nullptr);
+  for (int R : {1, 2048, 2049, 3000}) {
+    std::vector<int32_t> of(size_t(R), 0);
+    std::vector<sched_lat> lat;
+    for (int r = 0; r < R; ++r)
+      for (const sched_tool& t : p->tools)
+        lat.push_back({t.gpu_us + r % 37 * 1000, t.cpu_us + r % 5, t.load_us, t.xfer_us + r % 11});
+    Workspace ws(bytes_for({p}, R));
+    std::vector<sched_result> got(static_cast<size_t>(R));
+    g_slots_held = 0;
+    CHECK(sched_eval_batch(&p, 1, of.data(), lat.data(), R, ws.p, ws.bytes, nullptr, got.data()) ==
+          SCHED_OK);
+    CHECK(g_slots_held == (R <= 2048 ? 1u : 0u) && g_slots_taken == 0);
+    for (int r = 0; r < R; r += R / 40 + 1) {
+      sched_problem q = *p;
+      CHECK(fill_latencies(q, &lat[size_t(r) * p->n], q.table_full.data(), true) == SCHED_OK);
+      sched_result want{};
+      CHECK(sched_bruteforce_argmin(&q, 0, q.n_mappings, ws.p, ws.bytes, nullptr, &want) == SCHED_OK);
+      CHECK(want.best_index == got[r].best_index && want.makespan_us == got[r].makespan_us);
+    }
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
   else if (what == "stats") check_stats();
   else if (what == "slots") check_slots();
+  else if (what == "replicas") check_replicas();
   else return 2;
   puts("ok");
   return 0;

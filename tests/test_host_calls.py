@@ -71,3 +71,8 @@ def small_problems():
 
 def test_calls_without_a_slot(host_calls):
     host_calls("slots", *small_problems())
+
+
+def test_batches_around_a_full_slot(host_calls):
+    host_calls("replicas", (synth.random_instance(9950, 6, "permuted", tight=True),
+                            [3, 7, 1, 5, 3, 2], False))
