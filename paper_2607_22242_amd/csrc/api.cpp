@@ -480,7 +480,7 @@ void write_walk(const SearchArgs& a, uint32_t* table) {
 // with 5, a 14-tool fan-out 42.9 with 3 and 58.9 with 4.  A chain is worth it
 // at any size (8 tools: 23 us, event loop 36), a fan-out from 2^15 lanes of 9
 // (12 tools: 29.7 us, one by one 41.9; 11 tools 28.9 either way).
-uint32_t closed_inner(uint32_t closed, uint64_t work) {
+uint32_t closed_inner(uint32_t closed, unsigned __int128 work) {
   uint32_t j = closed == kClosedChain ? 1 : 0;
   if (closed == kClosedFanout && work / 9 >= (1ull << 15)) j = 2;
   if (j == 0) return 0;
@@ -1080,7 +1080,7 @@ int search_parts(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hip
 struct Launch {
   size_t first, last;
   int lay;
-  uint64_t work;  // mappings of its replicas
+  unsigned __int128 work;  // mappings of its replicas (two of 3^40 pass 64 bits)
   SearchArgs a;
 };
 
@@ -1115,7 +1115,7 @@ void plan_batch(const sched_problem* const* problems, const int32_t* replica_pro
   order.resize(R);
   std::iota(order.begin(), order.end(), 0);
   // closed forms with work enough for one of their launches
-  uint64_t work[3] = {};
+  unsigned __int128 work[3] = {};
   for (size_t r = 0; r < R; ++r)
     work[problems[replica_problem[r]]->closed] += problems[replica_problem[r]]->n_mappings;
   const auto kind = [&](int32_t i) {

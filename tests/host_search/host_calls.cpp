@@ -33,6 +33,7 @@ static std::map<hipStream_t, std::vector<std::function<void()>>> g_work;
 static std::atomic<int> g_page_locked{0};     // successful hipHostMalloc calls
 static std::atomic<int> g_fail_page_locked{0};  // calls that will fail
 static bool g_plan_only = false;              // launches score nothing
+static uint32_t g_most_blocks = 65536;        // partials that a workspace has room for
 static thread_local long t_news = 0;          // heap allocations of this thread
 
 static void enqueue(hipStream_t s, std::function<void()> f) {
@@ -210,6 +211,10 @@ hipError_t launch_search(int n, const SearchArgs& args, hipStream_t s) {
     SearchArgs a = args;
     const uint32_t* tab = own.empty() ? a.tables : own.data();
     if (a.closed == kClosedNone && a.full_range && tab[kHdrPrefix]) ++g_shared;
+    if (a.n_blocks > g_most_blocks) {
+      fprintf(stderr, "a launch of %u blocks\n", a.n_blocks);
+      exit(1);
+    }
     if (g_plan_only)
       for (uint32_t b = 0; b < a.n_blocks; ++b) a.partials[b] = Partial{a.n_tables, a.n_blocks, 0};
     else
@@ -474,12 +479,32 @@ static void check_replicas() {
   }
 }
 
+// Batches of the largest spaces: no launch has more blocks than the workspace
+// has partials.
+static void check_blocks() {
+  g_plan_only = true;
+  sched_problem* const p = read_problem();
+  CHECK(p != nullptr);
+  for (int R : {1, 2, 3, 7, 66000}) {
+    const std::vector<int32_t> of(size_t(R), 0);
+    std::vector<sched_lat> lat;
+    for (int r = 0; r < R; ++r)
+      for (const sched_tool& t : p->tools) lat.push_back({t.gpu_us, t.cpu_us, t.load_us, t.xfer_us});
+    Workspace ws(bytes_for({p}, R));
+    std::vector<sched_result> got(static_cast<size_t>(R));
+    g_most_blocks = uint32_t(std::max(R, 65536));
+    CHECK(sched_eval_batch(&p, 1, of.data(), lat.data(), R, ws.p, ws.bytes, nullptr, got.data()) ==
+          SCHED_OK);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
   else if (what == "stats") check_stats();
   else if (what == "slots") check_slots();
   else if (what == "replicas") check_replicas();
+  else if (what == "blocks") check_blocks();
   else return 2;
   puts("ok");
   return 0;

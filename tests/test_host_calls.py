@@ -76,3 +76,11 @@ def test_calls_without_a_slot(host_calls):
 def test_batches_around_a_full_slot(host_calls):
     host_calls("replicas", (synth.random_instance(9950, 6, "permuted", tight=True),
                             [3, 7, 1, 5, 3, 2], False))
+
+
+# 3^40 mappings: two replicas hold more than 64 bits count
+@pytest.mark.parametrize("shape", ["random", "chain"])
+def test_blocks_of_the_largest_batches(host_calls, shape):
+    inst = synth.random_instance(9960, 40, shape)
+    inst["tools"] = [[1 + t[0] % 99, 1 + t[1] % 99, t[2] % 99, t[3] % 9, t[4]] for t in inst["tools"]]
+    host_calls("blocks", (inst, None, False))
