@@ -156,7 +156,9 @@ int sched_num_mappings(const sched_problem *p, uint64_t *out);
 
 /* Bytes of device workspace sufficient for any call below on these
  * problems with up to n_replicas replicas (n_replicas = 0 for calls without
- * replicas).  Host-only. */
+ * replicas).  A search takes a workspace with room for one table, 65,536 block
+ * partials and a result; where these bytes are more than that, they are for
+ * large partial ranges, which otherwise take longer.  Host-only. */
 int sched_workspace_bytes(const sched_problem *const *problems, int32_t n_problems,
                           int32_t n_replicas, size_t *out);
 
@@ -273,8 +275,9 @@ typedef struct {
  * bound does not exceed the best makespan found so far are taken up, most
  * promising first: extended by the next tools, bounded again, and what
  * survives has its remaining tools searched exhaustively.  Spaces below 2^22
- * mappings get one exhaustive search.  d_workspace: at least
- * sched_pruned_workspace_bytes(p) bytes, 256-byte aligned.  stats: optional
+ * mappings get one exhaustive search.  d_workspace: 256-byte aligned; with
+ * fewer than sched_pruned_workspace_bytes(p) bytes, but room for the bounds of
+ * every prefix assignment, fewer assignments are taken up at a time.  stats: optional
  * counters (host). */
 int sched_pruned_workspace_bytes(const sched_problem *p, size_t *out);
 int sched_pruned_argmin(const sched_problem *p, void *d_workspace, size_t ws_bytes,

@@ -974,7 +974,10 @@ struct PruneLayout {
   size_t chunk;  // prefixes searched together
 };
 
-PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
+// room: bytes of the workspace.  One too small for kChunkPrefixes and their
+// children has smaller chunks (and more launches); total is beyond it if it
+// does not hold one prefix at a time.
+PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl, size_t room) {
   PruneLayout l;
   const size_t probes = size_t(1 + 2 * p.n + p.n * (p.n - 1));
   l.tables = 0;
@@ -983,7 +986,10 @@ PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
   l.bounds = l.results + align_up(sizeof(DevResult));
   // Survivor count (one word, padded) and then (bound, y) pairs: first up to
   // n_prefixes of the prefixes, then a chunk of them and its children.
+  const size_t others = l.bounds + align_up(4) + 2 * align_up(probes * 8);
+  const size_t fit = room > others ? (room - others) / kAlign * kAlign / 8 : 0;
   l.chunk = size_t(std::min<uint64_t>(kChunkPrefixes, pl.n_prefixes));
+  l.chunk = std::max<size_t>(1, std::min(l.chunk, fit / size_t(1 + pl.n_children)));
   const size_t pairs = std::max<size_t>(size_t(pl.n_prefixes), l.chunk * size_t(1 + pl.n_children));
   l.probe_idx = l.bounds + align_up(4) + align_up(pairs * 8);
   l.probe_ms = l.probe_idx + align_up(probes * 8);
@@ -991,15 +997,19 @@ PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
   return l;
 }
 
-// Bytes of the tables of one search: one table, or those of a range's parts
-// and their first blocks.
-size_t one_search_tables(const sched_problem& p) {
-  return 4 * (range_in_parts(p, 0, p.n_mappings) ? parts_words(p) : size_t(p.table_words));
+// Workspace of a search over one table, which is the least that a call takes,
+// and of one over a range's parts (their tables and first blocks).
+Layout one_table_layout(const sched_problem& p) {
+  return layout_for(4 * size_t(p.table_words), partial_capacity(1), 1);
 }
 
-// Workspace bytes of one search.
+Layout parts_layout(const sched_problem& p) {
+  return layout_for(4 * parts_words(p), partial_capacity(1), 1);
+}
+
+// Workspace bytes with which any search of the problem goes its best way.
 size_t one_search_bytes(const sched_problem& p) {
-  return layout_for(one_search_tables(p), partial_capacity(1), 1).total;
+  return (range_in_parts(p, 0, p.n_mappings) ? parts_layout(p) : one_table_layout(p)).total;
 }
 
 // Plan and tables of a search over the parts of [lo, hi), staged in `stage`
@@ -1045,12 +1055,12 @@ size_t stage_parts(const sched_problem& p, uint64_t lo, uint64_t hi, SearchArgs&
   return size_t(n) * p.table_words + size_t(n) + 1;
 }
 
-// A partial range searched in parts, in workspace ws, its tables staged in
+// A partial range searched in parts, in workspace ws (parts_layout), its tables staged in
 // `stage` (kStageWords; null: heap memory of this call's, for the tables of 24
 // parts are more than a small thread stack holds).
 int search_parts(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
                  uint32_t* stage, sched_result* h_out) {
-  const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
+  const Layout L = parts_layout(p);
   SearchArgs a{};
   std::unique_ptr<uint32_t[]> heap;
   if (stage == nullptr) {
@@ -1201,16 +1211,18 @@ uint64_t table_items(const uint32_t* table) {
 constexpr uint32_t kHostPartials = 2048;
 static_assert(kHostPartials * sizeof(Partial) <= kSlotBytes, "partials of a small search");
 
-// One search of [lo, hi) in workspace ws (at least one_search_bytes) on stream
-// s, then the result.  record: every mapping's makespan (full ranges only;
-// null: none).  stage: null, or kStageWords of host memory for the tables of a
+// One search of [lo, hi) in workspace ws of ws_bytes (at least those of
+// one_table_layout; with fewer than parts_layout has, every partial range is
+// walked in index order) on stream s, then the result.  record: every
+// mapping's makespan (full ranges only; null: none).  stage: null, or kStageWords of host memory for the tables of a
 // range's parts: the call then allocates nothing, page-locked slots (which the
 // first call that wants one allocates) included.
-int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hipStream_t s,
-               uint32_t* record, uint32_t* stage, sched_result* h_out) {
-  const Layout L = layout_for(one_search_tables(p), partial_capacity(1), 1);
+int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, size_t ws_bytes,
+               hipStream_t s, uint32_t* record, uint32_t* stage, sched_result* h_out) {
+  const Layout L = one_table_layout(p);
   SearchArgs a{};
-  if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi))
+  if ((lo > 0 || hi < p.n_mappings) && range_in_parts(p, lo, hi) &&
+      ws_bytes >= parts_layout(p).total)
     return search_parts(p, lo, hi, ws, s, stage, h_out);
   if (lo == 0 && hi == p.n_mappings)
     plan_full(p, a);
@@ -1355,9 +1367,9 @@ int sched_bruteforce_argmin(const sched_problem* p, uint64_t lo, uint64_t hi, vo
                             size_t ws_bytes, void* hip_stream, sched_result* h_out) {
   if (p == nullptr || h_out == nullptr) return SCHED_E_NULL;
   if (lo >= hi || hi > p->n_mappings) return SCHED_E_RANGE;
-  const int rc = check_workspace(d_workspace, ws_bytes, one_search_bytes(*p));
+  const int rc = check_workspace(d_workspace, ws_bytes, one_table_layout(*p).total);
   if (rc != SCHED_OK) return rc;
-  return search_one(*p, lo, hi, static_cast<char*>(d_workspace),
+  return search_one(*p, lo, hi, static_cast<char*>(d_workspace), ws_bytes,
                     reinterpret_cast<hipStream_t>(hip_stream), nullptr, nullptr, h_out);
 }
 
@@ -1369,8 +1381,8 @@ int sched_bruteforce_argmin_noalloc(const sched_problem* p, uint64_t lo, uint64_
   void* ws = nullptr;
   uint32_t* stage = nullptr;
   HIP_TRY(scratch_buffer(&ws, &stage));
-  return search_one(*p, lo, hi, static_cast<char*>(ws), reinterpret_cast<hipStream_t>(hip_stream),
-                    nullptr, stage, h_out);
+  return search_one(*p, lo, hi, static_cast<char*>(ws), kScratchBytes,
+                    reinterpret_cast<hipStream_t>(hip_stream), nullptr, stage, h_out);
 }
 
 int sched_bruteforce_record(const sched_problem* p, void* d_workspace, size_t ws_bytes,
@@ -1378,9 +1390,9 @@ int sched_bruteforce_record(const sched_problem* p, void* d_workspace, size_t ws
                             sched_result* h_out) {
   if (p == nullptr || h_out == nullptr || d_makespan == nullptr) return SCHED_E_NULL;
   if (capacity < p->n_mappings) return SCHED_E_WORKSPACE;
-  const int rc = check_workspace(d_workspace, ws_bytes, one_search_bytes(*p));
+  const int rc = check_workspace(d_workspace, ws_bytes, one_table_layout(*p).total);
   if (rc != SCHED_OK) return rc;
-  return search_one(*p, 0, p->n_mappings, static_cast<char*>(d_workspace),
+  return search_one(*p, 0, p->n_mappings, static_cast<char*>(d_workspace), ws_bytes,
                     reinterpret_cast<hipStream_t>(hip_stream), d_makespan, nullptr, h_out);
 }
 
@@ -1546,7 +1558,7 @@ int sched_eval_reprobes(const sched_problem* p, uint64_t base_index, const sched
   const int n = p->n;
   const int64_t worst = 1 + 2 * int64_t(n) + int64_t(n) * (n - 1);
   if (capacity < worst) return SCHED_E_SIZE;
-  const Layout L = layout_for(one_search_tables(*p), partial_capacity(1), 1);
+  const Layout L = one_table_layout(*p);
   int rc = check_workspace(d_workspace, ws_bytes, L.total);
   if (rc != SCHED_OK) return rc;
 
@@ -1598,7 +1610,7 @@ int sched_eval_reprobes(const sched_problem* p, uint64_t base_index, const sched
 int sched_pruned_workspace_bytes(const sched_problem* p, size_t* out) {
   if (p == nullptr || out == nullptr) return SCHED_E_NULL;
   size_t need = one_search_bytes(*p);
-  if (p->n_mappings >= kPruneMinSpace) need = std::max(need, prune_layout(*p, plan_prune(*p)).total);
+  if (p->n_mappings >= kPruneMinSpace) need = std::max(need, prune_layout(*p, plan_prune(*p), SIZE_MAX).total);
   *out = need;
   return SCHED_OK;
 }
@@ -1625,7 +1637,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
   }
   const int n = p->n;
   const PrunePlan pl = plan_prune(*p);
-  const PruneLayout L = prune_layout(*p, pl);
+  const PruneLayout L = prune_layout(*p, pl, ws_bytes);
   int rc = check_workspace(d_workspace, ws_bytes, L.total);
   if (rc != SCHED_OK) return rc;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);

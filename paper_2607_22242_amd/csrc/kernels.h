@@ -1705,6 +1705,16 @@ __host__ __device__ __forceinline__ uint32_t prefix_bound(const uint32_t* __rest
   return umax32(lb, qsum);
 }
 
+// The assignment that number y of a launch over bounds stands for: y itself,
+// or a child of a listed assignment (see kHdrParentLo).
+__host__ __device__ __forceinline__ uint64_t bound_assignment(const uint2* parents,
+                                                              uint32_t children,
+                                                              uint32_t n_parents, uint64_t y) {
+  if (parents == nullptr) return y;
+  const uint64_t k = y / children;
+  return parents[k].y + (y - k * children) * n_parents;
+}
+
 // Bounds of prefixes [0, n), or of n children of listed prefixes (kHdrParent*):
 // prefix y holds the mixed-radix digits of the
 // table's enumeration positions [0, K); known = the labels of those tools
@@ -1722,11 +1732,8 @@ __global__ __launch_bounds__(kBlock) void bound_kernel(const uint32_t* __restric
   for (int64_t y = int64_t(blockIdx.x) * kBlock + threadIdx.x; y < n;
        y += int64_t(gridDim.x) * kBlock) {
     MaskT<N> gn, gq;
-    uint64_t x, py = uint64_t(y);
-    if (parents) {
-      const uint64_t k = py / children;
-      py = parents[k].y + (py - k * children) * n_parents;
-    }
+    uint64_t x;
+    const uint64_t py = bound_assignment(parents, children, n_parents, uint64_t(y));
     decode_positions<N>(tab, py, 0, K, gn, gq, x);
     const uint32_t lb = prefix_bound<N>(tab, gn, gq, MaskT<N>(known));
     if (lb != kInf && lb <= ub) {

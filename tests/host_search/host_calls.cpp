@@ -22,7 +22,7 @@
 #include <string>
 
 #ifndef HOST_CALLS_N
-#define HOST_CALLS_N 6, 10
+#define HOST_CALLS_N 6, 10, 15
 #endif
 
 // ---------------------------------------------------------------------------
@@ -250,9 +250,24 @@ hipError_t launch_eval(int n, const uint32_t* tab, const uint64_t* idx, int64_t 
   return hipSuccess;
 }
 
-hipError_t launch_bound(int, const uint32_t*, uint32_t, uint64_t, int64_t, uint32_t, uint32_t*,
-                        uint2*, hipStream_t) {
-  return hipErrorUnknown;
+hipError_t launch_bound(int n, const uint32_t* tab, uint32_t K, uint64_t known, int64_t m,
+                        uint32_t ub, uint32_t* count, uint2* out, hipStream_t s) {
+  Uncounted u;
+  enqueue(s, [=] {
+    const uint2* const parents = list_at(Tab{tab}, kHdrParentLo);
+    on_tools(n, [&](auto N) {
+      for (int64_t k = 0; k < m; ++k) {
+        const uint64_t y =
+            bound_assignment(parents, tab[kHdrChildren], tab[kHdrParents], uint64_t(k));
+        MaskT<N()> gn, gq;
+        uint64_t x;
+        decode_positions<N()>(tab, y, 0, K, gn, gq, x);
+        const uint32_t lb = prefix_bound<N()>(tab, gn, gq, MaskT<N()>(known));
+        if (lb != kInf && lb <= ub) out[(*count)++] = make_uint2(lb, uint32_t(y));
+      }
+    }, Built{});
+  });
+  return hipSuccess;
 }
 hipError_t launch_valu_probe(uint32_t, uint32_t, uint32_t*, hipStream_t, double*) {
   return hipErrorUnknown;
@@ -498,6 +513,56 @@ static void check_blocks() {
   }
 }
 
+// Workspaces from one table, the partials and a result upwards: every search
+// takes them, a range in parts where they hold its tables; and a pruned search
+// gives the same answer in fewer bytes.  Prints that answer.
+static void check_room() {
+  sched_problem* const p = read_problem();
+  CHECK(p != nullptr);
+  const size_t least = one_table_layout(*p).total, most = bytes_for({p}, 0);
+  const uint64_t M = p->n_mappings;
+  CHECK(range_in_parts(*p, 0, M) && most > least);
+  Workspace ws(most);
+  g_plan_only = true;
+  for (size_t n : {least - 1, least, most - 1, most}) {
+    const int want = n < least ? SCHED_E_WORKSPACE : SCHED_OK;
+    sched_result r;
+    std::vector<uint32_t> all(M);
+    std::vector<sched_probe> pr(size_t(1 + 2 * p->n + p->n * (p->n - 1)));
+    int32_t k = 0;
+    CHECK(sched_bruteforce_argmin(p, 0, M, ws.p, n, nullptr, &r) == want);
+    CHECK(sched_bruteforce_record(p, ws.p, n, nullptr, all.data(), M, &r) == want);
+    CHECK(sched_eval_reprobes(p, 0, nullptr, ws.p, n, nullptr, pr.data(), int32_t(pr.size()), &k) ==
+          want);
+    g_max_tables = 0;
+    CHECK(sched_bruteforce_argmin(p, 1, M, ws.p, n, nullptr, &r) == want);
+    CHECK(n < least || (g_max_tables > 1) == (n == most));
+  }
+  g_plan_only = false;
+  size_t full = 0;
+  CHECK(sched_pruned_workspace_bytes(p, &full) == SCHED_OK);
+  const PrunePlan pl = plan_prune(*p);
+  CHECK(prune_layout(*p, pl, full).chunk == prune_layout(*p, pl, SIZE_MAX).chunk);
+  const size_t one = prune_layout(*p, pl, 0).total;  // one prefix at a time
+  CHECK(one < full);
+  sched_result want{};
+  int launches = 0;
+  for (size_t n : {full, (one + full) / 2, one + (full - one) / 16, one, one - 1}) {
+    CHECK(n <= one || prune_layout(*p, pl, n).total <= n);
+    Workspace w(n);
+    sched_result r{};
+    sched_prune_stats st{};
+    const int rc = sched_pruned_argmin(p, w.p, n, nullptr, &r, &st);
+    CHECK(rc == (n < one ? SCHED_E_WORKSPACE : SCHED_OK));
+    if (rc != SCHED_OK) continue;
+    if (n == full) want = r;
+    CHECK(r.best_index == want.best_index && r.makespan_us == want.makespan_us);
+    CHECK(st.launches >= launches);
+    launches = st.launches;
+  }
+  printf("%llu %lld\n", (unsigned long long)want.best_index, (long long)want.makespan_us);
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
@@ -505,6 +570,7 @@ int main(int argc, char** argv) {
   else if (what == "slots") check_slots();
   else if (what == "replicas") check_replicas();
   else if (what == "blocks") check_blocks();
+  else if (what == "room") check_room();
   else return 2;
   puts("ok");
   return 0;

@@ -84,3 +84,12 @@ def test_blocks_of_the_largest_batches(host_calls, shape):
     inst = synth.random_instance(9960, 40, shape)
     inst["tools"] = [[1 + t[0] % 99, 1 + t[1] % 99, t[2] % 99, t[3] % 9, t[4]] for t in inst["tools"]]
     host_calls("blocks", (inst, None, False))
+
+
+def test_workspaces_of_fewer_bytes(host_calls, oracle_mod):
+    inst = synth.random_instance(9970, 15, "random", tight=True)
+    allowed = [7] * 15
+    got = host_calls("room", (inst, allowed, False))
+    print(got)
+    x, ms = map(int, got[0].split())
+    assert (x, ms) == oracle_mod.Problem.from_instance(inst).argmin()
