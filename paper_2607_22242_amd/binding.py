@@ -387,6 +387,16 @@ def sched_wave_or_probe(d_in, d_active, blocks: int, d_out64, d_out32, stream=No
            "sched_wave_or_probe")
 
 
+def _lat_array(lat, n: int):
+    """n sched_lat of the rows of lat (any iterable; values missing from a row
+    are 0)."""
+    rows = list(lat)
+    flat = [int(x) for r in rows for x in r[:4]]
+    if len(flat) == 4 * n and all(len(r) >= 4 for r in rows):  # (no object per row)
+        return (ctypes.c_int64 * (4 * n))(*flat)
+    return (sched_lat * n)(*[sched_lat(*map(int, r[:4])) for r in rows])
+
+
 def sched_eval_reprobes(handle, base_index: int, workspace, lat=None,
                         stream=None) -> List[dict]:
     """What-if probes around base_index (see the header); each probe as a
@@ -395,13 +405,7 @@ def sched_eval_reprobes(handle, base_index: int, workspace, lat=None,
     cap = 1 + 2 * n + n * (n - 1)
     out = (sched_probe * cap)()
     got = ctypes.c_int32()
-    latp = None
-    if lat is not None:
-        flat = [int(x) for r in lat for x in r[:4]]
-        if len(flat) == 4 * n and all(len(r) >= 4 for r in lat):
-            latp = (ctypes.c_int64 * (4 * n))(*flat)
-        else:
-            latp = (sched_lat * n)(*[sched_lat(*map(int, r[:4])) for r in lat])
+    latp = None if lat is None else _lat_array(lat, n)
     wp, wb = _ws(workspace)
     _check(lib().sched_eval_reprobes(handle, base_index, latp, wp, wb, _stream_ptr(stream), out,
                                      cap, ctypes.byref(got)), "sched_eval_reprobes")

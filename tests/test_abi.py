@@ -211,3 +211,15 @@ def test_valu_probe_argument_validation():
     assert B.ERRORS[L.sched_valu_probe(1, 0, dummy, None, ctypes.byref(ops))] == "SCHED_E_SIZE"
     assert B.ERRORS[L.sched_valu_probe((1 << 24) + 1, 1, dummy, None,
                                        ctypes.byref(ops))] == "SCHED_E_SIZE"
+
+
+def test_rows_of_latencies_from_any_iterable():
+    rows = [[5, 6, 7, 8], (9, 10, 11), [1, 2, 3, 4, 5]]  # (a row may end early or go on)
+    want = [5, 6, 7, 8, 9, 10, 11, 0, 1, 2, 3, 4]
+    for lat in (rows, iter(rows)):
+        a = B._lat_array(lat, 3)
+        assert list((ctypes.c_int64 * 12).from_buffer(a)) == want
+    for lat in (rows[::2], iter(rows[::2])):
+        assert list((ctypes.c_int64 * 8).from_buffer(B._lat_array(lat, 2))) == [5, 6, 7, 8, 1, 2, 3, 4]
+        with pytest.raises(IndexError):
+            B._lat_array(rows, 2)
