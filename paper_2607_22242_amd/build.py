@@ -14,8 +14,7 @@ LIB = os.path.join(HERE, "libsched.so")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 # (source, extra flags); the kernel instantiations are one unit per tool count,
 # the longest to compile first, so that they fill the compiler jobs evenly.
-INST_PARTS = [(n, n) for n in range(40, 0, -1)]
-UNITS = [("inst.hip", [f"-DINST_LO={lo}", f"-DINST_HI={hi}"]) for lo, hi in INST_PARTS] + [
+UNITS = [("inst.hip", [f"-DINST_N={n}"]) for n in range(40, 0, -1)] + [
     ("api.cpp", []), ("monitor.cpp", []), ("dispatch.hip", []), ("probe.hip", []),
     ("scratch.hip", []), ("closed.hip", [])]
 ARCH = "gfx950"

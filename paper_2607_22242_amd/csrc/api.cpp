@@ -526,7 +526,8 @@ int32_t shares_prefixes(const SearchArgs& a) {
 // level takes what it can of the two ends, down to kPartMin mappings, and
 // what is left at the ends is walked in index order, one mapping per lane.
 // Two parts a level: kMaxParts reaches ten levels below the middle, so an end
-// left over by that limit holds less than 3^-10 of the range.
+// left over by that limit is shorter than the block of the tenth, W_k over the
+// product of ten radices (2^-10 to 3^-10 of the middle's blocks).
 struct Part {
   uint64_t lo, hi;
   int level;  // k; 0: index order

@@ -95,7 +95,7 @@ constexpr uint32_t kClosedInf = 0xC0000000u;  // infeasible, with a time added t
 
 }  // namespace
 
-// Serial chains (kFlagChain): one tool runs at a time, so nothing is slowed,
+// Serial chains (kClosedChain): one tool runs at a time, so nothing is slowed,
 // queued behind another or kept waiting for VRAM, and the makespan is the sum
 // of the durations and of the transfers between neighbours on different
 // devices.  The inner tools' sum is the same for every lane but for the
@@ -170,7 +170,7 @@ __global__ __launch_bounds__(kBlock) void chain_kernel(SearchArgs a, TableArg) {
   for (uint64_t item = sh.bb; item * kBlock < n_outer; item += sh.nb) {
     uint64_t y = item * kBlock + threadIdx.x;
     if (y >= n_outer) break;
-    uint64_t x = uint64_t(tab[kHdrBaseLo]) | (uint64_t(tab[kHdrBaseHi]) << 32);
+    uint64_t x = 0;
     uint32_t sum = 0, last = 0;
     bool never = false;
     for (uint32_t i = 0; i < outer; ++i) {
@@ -265,7 +265,7 @@ struct FanWalk {
 
 }  // namespace
 
-// Fan-outs whose footprints all fit the budget together (kFlagFreeFanout; the
+// Fan-outs whose footprints all fit the budget together (kClosedFanout; the
 // schedule is that of evaluate_fanout): with at most four contention levels, a
 // queued tool that starts at s runs at 1 + (s < M1) + (s < M2) + (s < M3), M1
 // to M3 the three latest finishes of the gpu_now tools, which is all that the
@@ -320,7 +320,7 @@ __global__ __launch_bounds__(kBlock) void fanout_kernel(SearchArgs a, TableArg) 
   for (uint64_t item = sh.bb; item * kBlock < n_outer; item += sh.nb) {
     uint64_t y = item * kBlock + threadIdx.x;
     if (y >= n_outer) break;
-    f.x = uint64_t(tab[kHdrBaseLo]) | (uint64_t(tab[kHdrBaseHi]) << 32);
+    f.x = 0;
     uint32_t gn = 0, gq = 0, cpu = 0;
     for (uint32_t i = 0; i < outer; ++i) {
       const uint32_t o = t.opt[i], d = take_digit(y, o), m = opt_mode(o, d);

@@ -60,39 +60,37 @@ enum : uint32_t {
   kHdrFixGnHi = 8,    //                                   (bits 32..63)
   kHdrFixGqLo = 9,    // labels of tools fixed on gpu_queue
   kHdrFixGqHi = 10,
-  kHdrBaseLo = 11,    // index contribution of the fixed tools (a subspace's
-  kHdrBaseHi = 12,    // offset in the mapping index)
-  kHdrBoundOff = 13,  // word offset of the bound table
-  kHdrShareOff = 14,  // word offset of the processor-sharing table
-  kHdrFlags = 15,     // kFlag* bits
-  kHdrDeferLo = 16,   // inner tools of a shared-prefix search that are sinks with
-  kHdrDeferHi = 17,   // predecessors: the search defers them (bits 0..31, 32..63)
+  kHdrBoundOff = 11,  // word offset of the bound table
+  kHdrShareOff = 12,  // word offset of the processor-sharing table
+  kHdrFlags = 13,     // kFlag* bits
+  kHdrDeferLo = 14,   // inner tools of a shared-prefix search that are sinks with
+  kHdrDeferHi = 15,   // predecessors: the search defers them (bits 0..31, 32..63)
   // The walk of a full-order search over this table: which outer combinations
   // it covers and how (see SearchArgs, whose fields of the same names these
   // are).  In the table, so that one launch can serve tables of different sizes.
-  kHdrOuterLoLo = 18,
-  kHdrOuterLoHi = 19,
-  kHdrNOuterLo = 20,
-  kHdrNOuterHi = 21,
-  kHdrInnerDigits = 22,
-  kHdrInnerCount = 23,
-  kHdrPrefix = 24,
+  kHdrOuterLoLo = 16,
+  kHdrOuterLoHi = 17,
+  kHdrNOuterLo = 18,
+  kHdrNOuterHi = 19,
+  kHdrInnerDigits = 20,
+  kHdrInnerCount = 21,
+  kHdrPrefix = 22,
   // The outer combinations of a walk may come from a list of (bound, y) pairs
   // (its device address; 0: none): the outer combination numbered k then has
   // the digits of k mod kHdrListRest, and above them those of y of entry
   // k / kHdrListRest.
-  kHdrListLo = 25,
-  kHdrListHi = 26,
-  kHdrListRest = 27,
+  kHdrListLo = 23,
+  kHdrListHi = 24,
+  kHdrListRest = 25,
   // Bounds of the children of listed assignments (device address; 0: of all
   // assignments): the one numbered k extends y of entry k / kHdrChildren by the
   // digits of k mod kHdrChildren, above the kHdrParents assignments there are.
-  kHdrParentLo = 28,
-  kHdrParentHi = 29,
-  kHdrParents = 30,
-  kHdrChildren = 31,
-  kHdrLanes = 32,     // lanes per wave that take an outer combination (SearchArgs::lanes)
-  kHdrWords = 33,
+  kHdrParentLo = 26,
+  kHdrParentHi = 27,
+  kHdrParents = 28,
+  kHdrChildren = 29,
+  kHdrLanes = 30,     // lanes per wave that take an outer combination (SearchArgs::lanes)
+  kHdrWords = 32,     // (one to spare: the tool records start on a 128-byte line)
 };
 
 // A fan-out (no edges) whose footprints all fit the budget together, scored

@@ -928,7 +928,7 @@ __device__ __forceinline__ void stage_tables(const uint32_t* tab, uint32_t* lds)
 
 // Mode masks and index of the mapping whose enumeration positions [p0, p1)
 // hold the mixed-radix digits of y (lowest first), together with the tools
-// whose mode is fixed (their index contribution is the table's base).
+// whose mode is fixed (which add nothing to the index).
 template <int N>
 __host__ __device__ __forceinline__ void decode_positions(const uint32_t* __restrict__ tab,
                                                          uint64_t y, uint32_t p0, uint32_t p1,
@@ -937,7 +937,7 @@ __host__ __device__ __forceinline__ void decode_positions(const uint32_t* __rest
   using M = MaskT<N>;
   gn = load_mask<N>(Tab{tab}, kHdrFixGnLo);
   gq = load_mask<N>(Tab{tab}, kHdrFixGqLo);
-  x = uint64_t(tab[kHdrBaseLo]) | (uint64_t(tab[kHdrBaseHi]) << 32);
+  x = 0;
   for (uint32_t p = p0; p < p1; ++p) {
     const uint32_t o = tab[enum_opt_base(N) + p];
     const uint64_t q = opt_radix(o) == 3u ? y / 3u : y >> 1;
@@ -1551,9 +1551,9 @@ __device__ __forceinline__ const uint32_t* table_or_args(const uint32_t* table, 
 static_assert(sizeof(SearchArgs) % 8 == 0 && sizeof(EvalArgs) % 8 == 0 &&
               sizeof(SearchArgs) + sizeof(TableArg) <= 4096, "kernel arguments");
 
-// Exhaustive search.  Block b serves table b / blocks_per_table and walks its
-// work items (kBlock consecutive outer combinations each) with a stride of
-// blocks_per_table.  Each lane keeps its own (makespan, index) minimum; the
+// Exhaustive search.  Every table has a run of blocks (block_first, found by
+// bisection, or blocks_per_table each), which walk its work items (the outer
+// combinations of kBlock lanes each) with a stride of their number.  Each lane keeps its own (makespan, index) minimum; the
 // block's minimum goes to partials[b].
 template <int N, bool FULL, bool SHARE, int VAR = kVarAll>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(

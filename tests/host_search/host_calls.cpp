@@ -22,7 +22,7 @@
 #include <string>
 
 #ifndef HOST_CALLS_N
-#define HOST_CALLS_N 6, 10, 15
+#define HOST_CALLS_N 6, 10, 15, 34
 #endif
 
 // ---------------------------------------------------------------------------
@@ -100,6 +100,21 @@ hipError_t hipGetLastError(void) { return hipSuccess; }
 static std::atomic<int> g_launches{0}, g_shared{0}, g_max_tables{0};
 static std::atomic<uint32_t> g_slots_held{0};  // by the calls of the launches
 
+// Observer of a full-order launch: as RecordTo, and how often each mapping was
+// scored by the launches over lists, if that is kept.
+static std::vector<uint8_t>* g_times = nullptr;
+struct Watch {
+  uint32_t* out;
+  std::vector<uint8_t>* times;
+  bool on() const { return out != nullptr || times != nullptr; }
+  void operator()(uint64_t x, uint32_t ms) const {
+    if (out != nullptr) out[x] = ms;
+    if (times != nullptr) ++times->at(x);
+  }
+};
+// The y of the pairs of the lists that were walked.
+static std::vector<uint32_t> g_listed;
+
 namespace devmap {
 
 template <int N, bool SHARE>
@@ -154,7 +169,13 @@ static void search(const SearchArgs& a, const uint32_t* own) {
       }
     } else if (a.full_range) {
       const TabWalk walk{Tab{tab}};
-      const RecordTo rec{a.record};
+      const bool listed = tab[kHdrListRest] != 0;
+      const Watch rec{a.record, listed ? g_times : nullptr};
+      if (listed && b == 0) {
+        const uint2* const list = list_at(Tab{tab}, kHdrListLo);
+        for (uint64_t k = 0; k < walk_n_outer(walk) / tab[kHdrListRest]; ++k)
+          g_listed.push_back(list[k].y);
+      }
       const uint64_t items = (walk_n_outer(walk) + kBlock - 1) / kBlock;
       for (uint64_t item = bb; item < items; item += nb)
         for (uint32_t lane = 0; lane < uint32_t(kBlock); ++lane)
@@ -563,6 +584,42 @@ static void check_room() {
   printf("%llu %lld\n", (unsigned long long)want.best_index, (long long)want.makespan_us);
 }
 
+// A pruned search's launches over lists of children: every mapping of a listed
+// child is scored once, no other is, and the answer is printed.  With the
+// fewest bytes: chunks of a few prefixes, lists of several launches.
+static void check_children(bool fewest) {
+  sched_problem* const p = read_problem();
+  CHECK(p != nullptr && p->n_mappings >= kPruneMinSpace);
+  const PrunePlan pl = plan_prune(*p);
+  std::vector<uint8_t> times(p->n_mappings);
+  g_times = &times;
+  const size_t n = prune_layout(*p, pl, fewest ? 0 : SIZE_MAX).total;
+  Workspace ws(n);
+  sched_result r{};
+  sched_prune_stats st{};
+  CHECK(sched_pruned_argmin(p, ws.p, n, nullptr, &r, &st) == SCHED_OK);
+  std::sort(g_listed.begin(), g_listed.end());
+  CHECK(!g_listed.empty() && std::adjacent_find(g_listed.begin(), g_listed.end()) == g_listed.end());
+  std::vector<int32_t> upper(pl.prefix), modes(size_t(p->n));
+  upper.insert(upper.end(), pl.ext.begin(), pl.ext.end());
+  uint64_t scored = 0;
+  for (uint64_t x = 0; x < p->n_mappings; ++x) {
+    if (times[x] == 0) continue;
+    CHECK(times[x] == 1);
+    ++scored;
+    CHECK(sched_mapping_modes(p, x, modes.data()) == SCHED_OK);
+    uint64_t y = 0, w = 1;
+    for (int32_t v : upper) {
+      y += w * uint64_t(digit_of_mode(*p, v, modes[size_t(v)]));
+      w *= p->radix[v];
+    }
+    CHECK(std::binary_search(g_listed.begin(), g_listed.end(), uint32_t(y)));
+  }
+  CHECK(scored == g_listed.size() * pl.rest && scored == st.mappings_searched);
+  printf("%llu %lld %d %d\n", (unsigned long long)r.best_index, (long long)r.makespan_us,
+         st.launches, st.shared_prefix_launches);
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
@@ -571,6 +628,8 @@ int main(int argc, char** argv) {
   else if (what == "replicas") check_replicas();
   else if (what == "blocks") check_blocks();
   else if (what == "room") check_room();
+  else if (what == "children") check_children(true);
+  else if (what == "children at once") check_children(false);
   else return 2;
   puts("ok");
   return 0;

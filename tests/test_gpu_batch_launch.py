@@ -40,3 +40,32 @@ def test_mixed_launch_matches_single_searches(name, problems):
     got = S.sched_eval_batch(handles, [rp[i] for i in order], [lat[i] for i in order],
                              S.workspace(handles, len(rp)))
     assert got == [want[i] for i in order]
+
+
+def test_mixed_fan_outs_in_closed_form(oracle_mod):
+    """Fan-outs of several tool counts, masks and contention levels in one
+    launch of their closed form, against the oracle over each whole space."""
+    import numpy as np
+    handles, keep, rp, lat, want = [], [], [], [], []
+    for k, (n, levels, masked) in enumerate([(12, 4, False), (13, 1, True), (15, 3, True), (14, 2, True),
+                                             (5, 4, False)]):
+        inst = synth.random_instance(9350 + k, n, "fanout", levels=levels)
+        inst["vram_budget_mib"] = sum(t[4] for t in inst["tools"])
+        allowed = [(3, 7, 6, 7, 7, 2, 7, 5)[(v + k) % 8] if masked else 7 for v in range(n)]
+        keep.append(S.Problem.from_instance(inst, allowed))
+        handles.append(keep[-1].handle)
+        space = oracle_mod.Space(allowed)
+        idx = space.base3(np.arange(space.size(), dtype=np.uint64))
+        for rep in range(2):
+            new = synth.perturb(inst["tools"], 10 * k + rep)
+            Q = oracle_mod.Problem.from_instance(
+                dict(inst, tools=[r + [t[4]] for r, t in zip(new, inst["tools"])]))
+            ms = Q.eval_many(idx)
+            want.append((int(ms.argmin()), int(ms.min())))
+            rp.append(k)
+            lat.append(new)
+    order = sorted(range(len(rp)), key=lambda i: (i * 7) % len(rp))
+    print(f"batch of fan-outs: {len(rp)} replicas", flush=True)
+    got = S.sched_eval_batch(handles, [rp[i] for i in order], [lat[i] for i in order],
+                             S.workspace(handles, len(rp)))
+    assert got == [want[i] for i in order]

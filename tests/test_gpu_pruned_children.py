@@ -25,3 +25,19 @@ def test_children_match_exhaustive(n, shape, small, masked, share):
     assert (x, ms) == S.sched_bruteforce_argmin(P.handle, 0, P.n_mappings, S.workspace([P.handle]))
     print(st, flush=True)
     assert st["launches"] >= 1 and st["mappings_searched"] <= P.n_mappings
+
+
+# 64-bit masks: the children's list walked without shared prefixes, up to six inner digits
+@pytest.mark.parametrize("n,share", [(33, False), (36, True), (40, False)])
+def test_children_of_wide_problems(n, share):
+    inst = synth.random_instance(9650 + n, n, "permuted", tight=True)
+    # 2^12 * 3^7 mappings: 12 tools with two modes, 7 with three, spread over the labels
+    allowed = [1] * n
+    for k in range(19):
+        allowed[(7 * k) % n] = 7 if k % 8 in (1, 4, 6) else (3, 5)[k % 2]
+    P = S.Problem.from_instance(inst, allowed, sharing=share)
+    print(f"pruned {n} tools: {P.n_mappings} mappings", flush=True)
+    assert 1 << 22 <= P.n_mappings <= 1 << 25
+    x, ms, st = S.sched_pruned_argmin(P.handle, S.pruned_workspace(P.handle))
+    assert (x, ms) == S.sched_bruteforce_argmin(P.handle, 0, P.n_mappings, S.workspace([P.handle]))
+    assert st["prefix_tools"] >= 1 and st["launches"] >= 1 and st["shared_prefix_launches"] == 0
