@@ -215,7 +215,8 @@ int sched_eval_batch(const sched_problem *const *problems, int32_t n_problems,
  * entries) receives each mapping's makespan in us, or INT64_MAX when it is
  * infeasible.  The library copies the indices through d_workspace in chunks
  * (at least one index beyond the problem table must fit; the bytes of
- * sched_workspace_bytes take 131,072 per chunk) and waits for the stream. */
+ * sched_workspace_bytes take 131,072 or a few more per chunk) and waits for
+ * the stream. */
 int sched_eval_mappings(const sched_problem *p, const uint64_t *h_idx, int64_t n,
                         void *d_workspace, size_t ws_bytes, void *hip_stream,
                         int64_t *h_makespan);

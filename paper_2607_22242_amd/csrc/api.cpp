@@ -923,8 +923,8 @@ constexpr uint64_t kMinRest = 81;                // mappings left per extended p
 // and its children bounded again, with more modes known, before what is left
 // of them is searched: a bound costs about a tenth of a mapping's score, and
 // most of a surviving prefix does not survive its own children.  Tight 24-tool
-// DAG, whole calls: 6.5 ms without the second bounds (2,048 tables of 19,683
-// mappings per launch), 3.1 ms with them; 18 tools 532 us and 307 us.
+// DAG, whole calls: 6.8 ms without the second bounds (2,048 tables of 19,683
+// mappings per launch), 2.5 ms with them; 18 tools 469 us and 431 us.
 struct PrunePlan {
   std::vector<int32_t> prefix;  // prefix tools, digit order of the prefix index
   uint64_t n_prefixes = 1;

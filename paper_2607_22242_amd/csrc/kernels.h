@@ -541,6 +541,7 @@ __host__ __device__ __forceinline__ uint32_t evaluate_fanout(const uint32_t* __r
   using M = MaskT<N>;
   const uint32_t* s_dur = lds + lds_dur_off<N>();
   constexpr uint32_t kRow = 2u * uint32_t(N);
+  // (11 and 20 tools take the same time with the records left to the optimiser)
   const Tab tp = fresh(tab);
   // tools some lane of the wave has on gpu_now / gpu_queue
   M wn, wq, wx;
@@ -699,9 +700,11 @@ struct SimPS {
     (void)pass;
     ms = kInf;
     if (dead) return true;
-    // the modes and the tool records, re-read each pass (see Sim::step): the
-    // tests of loop-invariant values would otherwise be hoisted out of the
-    // event loop as scalar lane masks, more than the scalar registers hold
+    // the modes, re-read each pass (see Sim::step): the tests of loop-invariant
+    // values would otherwise be hoisted out of the event loop as scalar lane
+    // masks, more than the scalar registers hold.  The tool records are re-read
+    // too; left to the optimiser, as in Sim::step, 18 tools took 26.8 ms in
+    // place of 26.7, 19 tools 74.7 either way.
     gnm = opaque_v(gnm);
     gqm = opaque_v(gqm);
     const Tab tp = fresh(tab);
