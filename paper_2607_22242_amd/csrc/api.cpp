@@ -488,18 +488,33 @@ uint32_t closed_inner(uint32_t closed, unsigned __int128 work) {
   return j;
 }
 
-// Outer combinations of a closed-form walk of problem p over its last j labels.
-uint64_t closed_outer(const sched_problem& p, uint32_t j) {
+// Combinations of the last j labels of problem p, and the outer ones of a
+// closed-form walk over them.
+uint64_t closed_combos(const sched_problem& p, uint32_t j) {
   uint64_t inner = 1;
   for (uint32_t k = 0; k < j; ++k) inner *= p.radix[p.order[p.n - 1 - int(k)]];
-  return p.n_mappings / inner;
+  return inner;
+}
+
+uint64_t closed_outer(const sched_problem& p, uint32_t j) {
+  return p.n_mappings / closed_combos(p, j);
+}
+
+// Whether problem p gains from its closed form over its last j labels.  A
+// fan-out's lane runs the outer tools' queue for every set of inner tools on
+// gpu_now, which has to serve more than a mapping or two: where three labels
+// or more hold fewer than three combinations (tools of one mode), one by one is
+// the shorter way (30 tools with five such labels, 6.7e7 mappings: 1.27 ms, in
+// closed form 2.69; with three combinations 172 us against 260).
+bool closed_pays(const sched_problem& p, uint32_t j) {
+  return j > 0 && (p.closed != kClosedFanout || j == 2 || closed_combos(p, j) >= 3);
 }
 
 // Turns the plan of a one-table full-range search into a closed-form one where
 // the problem has one.
 void plan_closed(const sched_problem& p, SearchArgs& a) {
   const uint32_t j = closed_inner(p.closed, p.n_mappings);
-  if (j == 0) return;
+  if (!closed_pays(p, j)) return;
   a.closed = p.closed;
   a.inner_digits = j;
   const uint64_t items = (closed_outer(p, j) + kBlock - 1) / kBlock;
@@ -1114,28 +1129,38 @@ size_t batch_table_bytes(size_t stride, size_t n_replicas) {
 
 // Launches of a batch.  Replicas of one tool count and contention reading
 // share a launch, whatever their shapes, masks and sizes, but that serial
-// chains and free fan-outs, where they are enough, have a launch of their own
-// kind (of any tool counts).  A launch that would
+// chains and free fan-outs, where they are enough and gain from it, have a
+// launch of their own kind (of any tool counts).  A launch that would
 // leave the GPU partly idle (fewer mappings than kTargetLanes lanes) joins the
 // next larger tool count: its tables are laid out for more tools, at the cost
 // of one more resolution per added tool, instead of a launch in series.  13
 // scenarios of 4 to 9 tools, 8 replicas each: 108 us in one launch, 320 us in
 // eleven.
-void plan_batch(const sched_problem* const* problems, const int32_t* replica_problem, size_t R,
-                std::vector<Launch>& launches, std::vector<int32_t>& order) {
+void plan_batch(const sched_problem* const* problems, int32_t n_problems,
+                const int32_t* replica_problem, size_t R, std::vector<Launch>& launches,
+                std::vector<int32_t>& order) {
   order.resize(R);
   std::iota(order.begin(), order.end(), 0);
-  // closed forms with work enough for one of their launches
-  unsigned __int128 work[3] = {};
-  for (size_t r = 0; r < R; ++r)
-    work[problems[replica_problem[r]]->closed] += problems[replica_problem[r]]->n_mappings;
-  const auto kind = [&](int32_t i) {
+  // Labels walked by the launch of each closed form: the most for which the
+  // problems that gain from it have work enough (0: none).
+  std::vector<uint32_t> replicas(size_t(n_problems), 0u), kind(size_t(n_problems), kClosedNone);
+  for (size_t r = 0; r < R; ++r) ++replicas[size_t(replica_problem[r])];
+  uint32_t walked[3] = {};
+  for (uint32_t c : {uint32_t(kClosedChain), uint32_t(kClosedFanout)})
+    for (uint32_t j = kClosedInner; j > 0 && walked[c] == 0; --j) {
+      unsigned __int128 work = 0;
+      for (int32_t i = 0; i < n_problems; ++i)
+        if (problems[i]->closed == c && closed_pays(*problems[i], j))
+          work += (unsigned __int128)problems[i]->n_mappings * replicas[size_t(i)];
+      if (work > 0 && closed_inner(c, work) >= j) walked[c] = j;
+    }
+  for (int32_t i = 0; i < n_problems; ++i) {
     const uint32_t c = problems[i]->closed;
-    return closed_inner(c, work[c]) > 0 ? c : uint32_t(kClosedNone);
-  };
+    if (c != kClosedNone && closed_pays(*problems[i], walked[c])) kind[size_t(i)] = c;
+  }
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
     const int32_t a = replica_problem[x], b = replica_problem[y];
-    if (kind(a) != kind(b)) return kind(a) < kind(b);
+    if (kind[size_t(a)] != kind[size_t(b)]) return kind[size_t(a)] < kind[size_t(b)];
     if (problems[a]->sharing != problems[b]->sharing)
       return problems[a]->sharing < problems[b]->sharing;
     if (problems[a]->n != problems[b]->n) return problems[a]->n < problems[b]->n;
@@ -1143,14 +1168,14 @@ void plan_batch(const sched_problem* const* problems, const int32_t* replica_pro
   });
   for (size_t i = 0; i < R; ++i) {
     const sched_problem& p = *problems[replica_problem[order[i]]];
-    const uint32_t closed = kind(replica_problem[order[i]]);
+    const uint32_t closed = kind[size_t(replica_problem[order[i]])];
     Launch* const g = launches.empty() ? nullptr : &launches.back();
     if (g == nullptr || g->a.closed != closed || g->a.sharing != uint32_t(p.sharing) ||
         (closed == kClosedNone && g->lay != p.n && g->work >= kTargetLanes)) {
       Launch n{i, i, p.n, 0, SearchArgs{}};
       n.a.full_range = 1;
       n.a.closed = closed;
-      n.a.inner_digits = closed_inner(closed, work[closed]);
+      n.a.inner_digits = walked[closed];
       n.a.sharing = uint32_t(p.sharing);
       launches.push_back(n);
     }
@@ -1427,7 +1452,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     }
     std::vector<Launch> launches;
     std::vector<int32_t> order;  // replicas in launch order
-    plan_batch(problems, replica_problem, R, launches, order);
+    plan_batch(problems, n_problems, replica_problem, R, launches, order);
 
     // The tables: what does not depend on latencies once per problem, then
     // each replica's latencies; behind them each launch's first blocks.

@@ -620,6 +620,26 @@ static void check_children(bool fewest) {
          st.launches, st.shared_prefix_launches);
 }
 
+// The labels walked in closed form by a search of each problem (0: none), and
+// by the launch each problem's replica has in a batch of one replica each.
+static void check_closed() {
+  std::vector<const sched_problem*> ps;
+  while (const sched_problem* p = read_problem()) ps.push_back(p);
+  std::vector<int32_t> of(ps.size()), order;
+  std::iota(of.begin(), of.end(), 0);
+  std::vector<Launch> launches;
+  plan_batch(ps.data(), int32_t(ps.size()), of.data(), ps.size(), launches, order);
+  std::vector<uint32_t> batch(ps.size());
+  for (const Launch& l : launches)
+    for (size_t i = l.first; i < l.last; ++i)
+      batch[size_t(order[i])] = l.a.closed == kClosedNone ? 0 : l.a.inner_digits;
+  for (size_t i = 0; i < ps.size(); ++i) {
+    SearchArgs a{};
+    plan_full(*ps[i], a);
+    printf("%u %u\n", a.closed == kClosedNone ? 0 : a.inner_digits, batch[i]);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
@@ -628,6 +648,7 @@ int main(int argc, char** argv) {
   else if (what == "replicas") check_replicas();
   else if (what == "blocks") check_blocks();
   else if (what == "room") check_room();
+  else if (what == "closed") check_closed();
   else if (what == "children") check_children(true);
   else if (what == "children at once") check_children(false);
   else return 2;

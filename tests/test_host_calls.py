@@ -116,3 +116,24 @@ def test_children_are_scored_once(host_calls, oracle_mod, n, share, long):
     assert launches >= (2 if n == 15 and not long else 1) and (shared > 0) == long
     Q, space = oracle_mod.Problem.from_instance(inst, sharing=share), oracle_mod.Space(allowed)
     assert int(Q.eval_many(space.base3(np.array([x], dtype=np.uint64)))[0]) == ms
+
+
+def test_closed_forms_where_they_gain(host_calls):
+    """A fan-out's last labels have to hold combinations: with tools of one
+    mode there, it is scored one by one."""
+    def fan(n, allowed, shape="fanout"):
+        inst = synth.random_instance(9990 + n, n, shape)
+        inst["tools"] = [[max(1, x // 20) for x in t[:4]] + [t[4]] for t in inst["tools"]]
+        inst["vram_budget_mib"] = sum(t[4] for t in inst["tools"])
+        return inst, allowed, False
+
+    got = host_calls("closed",
+                     fan(14, [7] * 14),                       # 3^14: 3 labels, 27 combinations
+                     fan(24, [3] * 19 + [1] * 5),             # 2^19: 2 labels, 1 combination
+                     fan(29, [3] * 24 + [1] * 5),             # 2^24: 5 labels, 1 combination
+                     fan(28, [3] * 23 + [1, 1, 1, 1, 3]),     # 5 labels, 2 combinations
+                     fan(28, [3] * 22 + [1, 1, 7, 1, 1, 1]),  # 4 labels, 3 combinations
+                     fan(29, [3] * 24 + [1] * 5, "chain"))
+    assert got == ["3 5", "2 0", "0 0", "0 0", "4 5", "5 5"]
+    # work enough for two labels only, which need hold no more than one
+    assert host_calls("closed", fan(24, [3] * 19 + [1] * 5), fan(10, [7] * 10)) == ["2 2", "0 2"]
