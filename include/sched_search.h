@@ -257,7 +257,8 @@ int sched_eval_reprobes(const sched_problem *p, uint64_t base_index, const sched
 typedef struct {
     uint64_t prefixes;          /* assignments of the prefix tools that were bounded */
     uint64_t prefixes_searched; /* prefixes taken up for search (their extensions bounded
-                                   again, the survivors searched exhaustively) */
+                                   again, the survivors searched exhaustively, or the
+                                   prefixes where most survive) */
     uint64_t mappings_searched; /* mappings scored by those searches */
     int64_t initial_bound_us;   /* makespan of the descent's mapping (INT64_MAX if none) */
     int32_t prefix_tools;       /* tools in the prefix (0: one exhaustive search) */
@@ -275,7 +276,8 @@ typedef struct {
  * shortest durations, queued durations summed) and only assignments whose
  * bound does not exceed the best makespan found so far are taken up, most
  * promising first: extended by the next tools, bounded again, and what
- * survives has its remaining tools searched exhaustively.  Spaces below 2^22
+ * survives has its remaining tools searched exhaustively (the assignments
+ * themselves where few extensions are ruled out).  Spaces below 2^22
  * mappings get one exhaustive search.  d_workspace: 256-byte aligned; with
  * fewer than sched_pruned_workspace_bytes(p) bytes, but room for the bounds of
  * every prefix assignment, fewer assignments are taken up at a time.  stats: optional

@@ -1743,22 +1743,30 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
     std::sort(live.begin(), live.end());
 
     // 3. Chunks of survivors, most promising first: their children's bounds,
-    // then a search over the rest of the children that survive (one table;
-    // the children's list gives the outer combinations their upper digits).
-    sched_problem sub = *p;  // the rest: what a child leaves free
-    std::vector<int32_t> upper(pl.prefix);
-    upper.insert(upper.end(), pl.ext.begin(), pl.ext.end());
-    for (int32_t v : upper) sub.allowed[v] = uint8_t(1u << mode_of_digit(*p, v, 0));
-    sub.enum_tools.clear();
-    sub.n_mappings = 1;
-    for (int v = 0; v < n; ++v) {
-      const uint8_t a = sub.allowed[v];
-      sub.radix[v] = uint8_t((a & 1) + ((a >> 1) & 1) + ((a >> 2) & 1));
-      if (sub.radix[v] > 1) sub.enum_tools.push_back(v);
-      sub.n_mappings *= sub.radix[v];
-    }
-    seq = upper;
-    for (int32_t v : sub.enum_tools) seq.push_back(v);
+    // then a search over the rest of the children that survive, or of the
+    // chunk (one table; the list of either gives the outer combinations their
+    // upper digits).  rest_of: what the tools in `fixed` leave free.
+    const auto rest_of = [&](const std::vector<int32_t>& fixed) {
+      sched_problem r = *p;
+      for (int32_t v : fixed) r.allowed[v] = uint8_t(1u << mode_of_digit(*p, v, 0));
+      r.enum_tools.clear();
+      r.n_mappings = 1;
+      for (int v = 0; v < n; ++v) {
+        const uint8_t a = r.allowed[v];
+        r.radix[v] = uint8_t((a & 1) + ((a >> 1) & 1) + ((a >> 2) & 1));
+        if (r.radix[v] > 1) r.enum_tools.push_back(v);
+        r.n_mappings *= r.radix[v];
+      }
+      return r;
+    };
+    std::vector<int32_t> both(pl.prefix);
+    both.insert(both.end(), pl.ext.begin(), pl.ext.end());
+    const sched_problem child_rest = rest_of(both);
+    std::optional<sched_problem> prefix_rest;
+    // (a table counts the outer combinations of a listed assignment in a word)
+    const bool prefix_outer_fits = pl.subspace <= 0xFFFFFFFFull;
+    seq = both;
+    for (int32_t v : child_rest.enum_tools) seq.push_back(v);
     set_enumeration(*p, seq, btab.data());
     for (int32_t v : pl.ext) known |= 1ull << p->table[pos_base(uint32_t(n)) + uint32_t(v)];
     uint2* const d_chunk = d_live;
@@ -1791,7 +1799,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       HIP_TRY(hipMemcpyAsync(ws + L.tables, btab.data(), size_t(stride) * 4, hipMemcpyHostToDevice,
                              s));
       HIP_TRY(hipMemsetAsync(d_count, 0, 4, s));
-      HIP_TRY(launch_bound(n, d_tab, uint32_t(upper.size()), known, candidates,
+      HIP_TRY(launch_bound(n, d_tab, uint32_t(both.size()), known, candidates,
                            best_ms == INT64_MAX ? kInf - 1 : uint32_t(best_ms), d_count, d_children,
                            s));
       uint32_t n_rest = 0;
@@ -1799,6 +1807,17 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       HIP_TRY(hipStreamSynchronize(s));
       if (n_rest == 0) continue;
       if (int64_t(n_rest) > candidates) return SCHED_E_DEVICE;
+      // Where their bounds rule out less than a quarter of the children, the
+      // prefixes are searched themselves: a wave's lanes then share a prefix in
+      // place of holding several children, which differ in tools that act
+      // early.  30 tools, 76 % left: 39.2 ms by child, 25.0 by prefix; between
+      // a half and three quarters left the children are mostly the shorter way
+      // (32 tools, 52 %: 3.9 and 6.3 ms).
+      const bool whole = 4 * int64_t(n_rest) > 3 * candidates && prefix_outer_fits;
+      if (whole && !prefix_rest) prefix_rest.emplace(rest_of(pl.prefix));
+      const sched_problem& sub = whole ? *prefix_rest : child_rest;
+      const std::vector<int32_t>& upper = whole ? pl.prefix : both;
+      if (whole) n_rest = uint32_t(chunk.size());
       SearchArgs a{};
       plan_search(sub, 0, sub.n_mappings, n_rest, a);
       // One table over all of the children.
@@ -1815,7 +1834,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       a.blocks_per_table = a.n_blocks =
           uint32_t(std::min<uint64_t>(a.items_per_table, kMaxBlocks));
       write_walk(a, stab.data());
-      put_address(stab.data(), kHdrListLo, d_children);
+      put_address(stab.data(), kHdrListLo, whole ? d_chunk : d_children);
       stab[kHdrListRest] = uint32_t(rest);
       if (fits_arguments(stab.data())) {
         a.host_table = stab.data();

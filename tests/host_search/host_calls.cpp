@@ -112,8 +112,9 @@ struct Watch {
     if (times != nullptr) ++times->at(x);
   }
 };
-// The y of the pairs of the lists that were walked.
-static std::vector<uint32_t> g_listed;
+// The y of the pairs of the lists that were walked, by the mappings that each
+// entry stands for.
+static std::map<uint64_t, std::vector<uint32_t>> g_listed;
 
 namespace devmap {
 
@@ -174,7 +175,7 @@ static void search(const SearchArgs& a, const uint32_t* own) {
       if (listed && b == 0) {
         const uint2* const list = list_at(Tab{tab}, kHdrListLo);
         for (uint64_t k = 0; k < walk_n_outer(walk) / tab[kHdrListRest]; ++k)
-          g_listed.push_back(list[k].y);
+          g_listed[uint64_t(tab[kHdrListRest]) * tab[kHdrInnerCount]].push_back(list[k].y);
       }
       const uint64_t items = (walk_n_outer(walk) + kBlock - 1) / kBlock;
       for (uint64_t item = bb; item < items; item += nb)
@@ -584,8 +585,9 @@ static void check_room() {
   printf("%llu %lld\n", (unsigned long long)want.best_index, (long long)want.makespan_us);
 }
 
-// A pruned search's launches over lists of children: every mapping of a listed
-// child is scored once, no other is, and the answer is printed.  With the
+// A pruned search's launches over lists of children or prefixes: every mapping
+// of a listed one is scored once, no other is; prints the answer and how many
+// of either were listed.  With the
 // fewest bytes: chunks of a few prefixes, lists of several launches.
 static void check_children(bool fewest) {
   sched_problem* const p = read_problem();
@@ -598,8 +600,13 @@ static void check_children(bool fewest) {
   sched_result r{};
   sched_prune_stats st{};
   CHECK(sched_pruned_argmin(p, ws.p, n, nullptr, &r, &st) == SCHED_OK);
-  std::sort(g_listed.begin(), g_listed.end());
-  CHECK(!g_listed.empty() && std::adjacent_find(g_listed.begin(), g_listed.end()) == g_listed.end());
+  std::vector<uint32_t>& children = g_listed[pl.rest];
+  std::vector<uint32_t>& prefixes = g_listed[pl.subspace];
+  CHECK(g_listed.size() == 2 && pl.rest < pl.subspace && children.size() + prefixes.size() > 0);
+  for (auto* list : {&children, &prefixes}) {
+    std::sort(list->begin(), list->end());
+    CHECK(std::adjacent_find(list->begin(), list->end()) == list->end());
+  }
   std::vector<int32_t> upper(pl.prefix), modes(size_t(p->n));
   upper.insert(upper.end(), pl.ext.begin(), pl.ext.end());
   uint64_t scored = 0;
@@ -613,11 +620,13 @@ static void check_children(bool fewest) {
       y += w * uint64_t(digit_of_mode(*p, v, modes[size_t(v)]));
       w *= p->radix[v];
     }
-    CHECK(std::binary_search(g_listed.begin(), g_listed.end(), uint32_t(y)));
+    CHECK(std::binary_search(children.begin(), children.end(), uint32_t(y)) !=
+          std::binary_search(prefixes.begin(), prefixes.end(), uint32_t(y % pl.n_prefixes)));
   }
-  CHECK(scored == g_listed.size() * pl.rest && scored == st.mappings_searched);
-  printf("%llu %lld %d %d\n", (unsigned long long)r.best_index, (long long)r.makespan_us,
-         st.launches, st.shared_prefix_launches);
+  CHECK(scored == children.size() * pl.rest + prefixes.size() * pl.subspace &&
+        scored == st.mappings_searched);
+  printf("%llu %lld %d %d %zu %zu\n", (unsigned long long)r.best_index, (long long)r.makespan_us,
+         st.launches, st.shared_prefix_launches, children.size(), prefixes.size());
 }
 
 // The labels walked in closed form by a search of each problem (0: none), and

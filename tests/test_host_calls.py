@@ -97,7 +97,7 @@ def test_workspaces_of_fewer_bytes(host_calls, oracle_mod):
 
 
 # 15 tools; 34 tools (2^12 * 3^7 mappings, 64-bit masks); and 15 tools of which one outlasts the
-# others whatever they do, so that most mappings are searched, with shared prefixes
+# others whatever they do, so that no child is ruled out: its prefixes are searched, and shared
 @pytest.mark.parametrize("n,share,long", [(15, False, False), (15, True, False), (34, False, False),
                                           (15, False, True)])
 def test_children_are_scored_once(host_calls, oracle_mod, n, share, long):
@@ -111,9 +111,10 @@ def test_children_are_scored_once(host_calls, oracle_mod, n, share, long):
         inst["tools"][6][:2] = [100_000, 100_000]
         inst["edges"] = [e for e in inst["edges"] if 6 not in e]
         allowed[6] = 3
-    x, ms, launches, shared = map(int, host_calls("children at once" if long else "children",
-                                                  (inst, allowed, share))[0].split())
+    x, ms, launches, shared, children, prefixes = map(int, host_calls(
+        "children at once" if long else "children", (inst, allowed, share))[0].split())
     assert launches >= (2 if n == 15 and not long else 1) and (shared > 0) == long
+    assert (children > 0) != long and (prefixes > 0) == long
     Q, space = oracle_mod.Problem.from_instance(inst, sharing=share), oracle_mod.Space(allowed)
     assert int(Q.eval_many(space.base3(np.array([x], dtype=np.uint64)))[0]) == ms
 
