@@ -927,9 +927,11 @@ void neighbourhood(const sched_problem& p, uint64_t base, std::vector<uint64_t>&
 constexpr uint64_t kPruneMinSpace = 1ull << 22;  // smaller spaces: one exhaustive search
 constexpr uint64_t kMaxPrefixes = 1ull << 24;    // bounded prefix assignments per call
 constexpr uint64_t kMinSubspace = 1ull << 12;    // mappings per searched subspace, at least
-// Prefixes searched together, in the first chunk and in the others: the first
-// mostly lowers the bound for all that follow, so it is kept short.  Two modes,
-// 34 tools: 8.3 ms with a first chunk of 2,048, 14.9 with 8,192 prefixes.
+// Prefixes searched together, in the first chunk of several and in the others:
+// the first mostly lowers the bound for all that follow, so it is kept short
+// (two modes, 34 tools: 6.9 ms with a first chunk of 2,048, 14.9 with 8,192
+// prefixes; 19 tools, 8,019 survivors: 1.1 and 2.4 ms).  A chunk more costs 90
+// us, so twice as many are still searched at once.
 constexpr uint32_t kFirstPrefixes = 2048, kChunkPrefixes = 8192;
 constexpr uint64_t kMaxChildren = 243;           // assignments of the extension tools
 constexpr uint64_t kMinRest = 81;                // mappings left per extended prefix, at least
@@ -1787,7 +1789,8 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
     while (next < live.size()) {
       if (best_ms != INT64_MAX && int64_t(live[next].first) > best_ms) break;
       chunk.clear();
-      const size_t most = next == 0 ? std::min<size_t>(L.chunk, kFirstPrefixes) : L.chunk;
+      const size_t most = next == 0 && live.size() > 2 * kFirstPrefixes
+                              ? std::min<size_t>(L.chunk, kFirstPrefixes) : L.chunk;
       while (next < live.size() && chunk.size() < most &&
              (best_ms == INT64_MAX || int64_t(live[next].first) <= best_ms)) {
         chunk.push_back(make_uint2(live[next].first, uint32_t(live[next].second)));
