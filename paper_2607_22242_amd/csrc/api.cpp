@@ -500,21 +500,28 @@ uint64_t closed_outer(const sched_problem& p, uint32_t j) {
   return p.n_mappings / closed_combos(p, j);
 }
 
-// Whether problem p gains from its closed form over its last j labels.  A
-// fan-out's lane runs the outer tools' queue for every set of inner tools on
-// gpu_now, which has to serve more than a mapping or two: where three labels
-// or more hold fewer than three combinations (tools of one mode), one by one is
-// the shorter way (30 tools with five such labels, 6.7e7 mappings: 1.27 ms, in
-// closed form 2.69; with three combinations 172 us against 260).
-bool closed_pays(const sched_problem& p, uint32_t j) {
-  return j > 0 && (p.closed != kClosedFanout || j == 2 || closed_combos(p, j) >= 3);
+// Whether problem p gains from its closed form over its last j labels, in a
+// launch whose problems of this kind have `work` mappings.  A fan-out's lane
+// runs the outer tools' queue for every set of inner tools on gpu_now, which has
+// to serve more than a mapping or two: where the labels hold fewer than three
+// combinations (tools of one mode), one by one is the shorter way but for small
+// searches (30 tools with five such labels, 6.7e7 mappings: 1.27 ms, in closed
+// form 2.69; with three combinations 172 us against 260).  Work for two labels
+// (up to 1.8e6 mappings) is mostly launch and wait: two combinations take 0.54
+// to 0.80 times as long as one by one (0.79 to 1.23 with work for three labels),
+// one 0.82 to 0.88 times up to 1e6 mappings and 1.09 beyond.
+bool closed_pays(const sched_problem& p, uint32_t j, unsigned __int128 work) {
+  if (j == 0 || p.closed != kClosedFanout) return j > 0;
+  const uint64_t combos = closed_combos(p, j);
+  return combos >= 3 || (j == 2 && closed_inner(kClosedFanout, work) == 2 &&
+                         (combos == 2 || work < (1u << 20)));
 }
 
 // Turns the plan of a one-table full-range search into a closed-form one where
 // the problem has one.
 void plan_closed(const sched_problem& p, SearchArgs& a) {
   const uint32_t j = closed_inner(p.closed, p.n_mappings);
-  if (!closed_pays(p, j)) return;
+  if (!closed_pays(p, j, p.n_mappings)) return;
   a.closed = p.closed;
   a.inner_digits = j;
   const uint64_t items = (closed_outer(p, j) + kBlock - 1) / kBlock;
@@ -1155,13 +1162,16 @@ void plan_batch(const sched_problem* const* problems, int32_t n_problems,
     for (uint32_t j = kClosedInner; j > 0 && walked[c] == 0; --j) {
       unsigned __int128 work = 0;
       for (int32_t i = 0; i < n_problems; ++i)
-        if (problems[i]->closed == c && closed_pays(*problems[i], j))
+        if (problems[i]->closed == c && closed_pays(*problems[i], j, all[c]))
           work += (unsigned __int128)problems[i]->n_mappings * replicas[size_t(i)];
       if (work > 0 && closed_inner(c, work) >= j) walked[c] = j;
+  unsigned __int128 all[3] = {};  // mappings of each kind
+  for (int32_t i = 0; i < n_problems; ++i)
+    all[problems[i]->closed] += (unsigned __int128)problems[i]->n_mappings * replicas[size_t(i)];
     }
   for (int32_t i = 0; i < n_problems; ++i) {
     const uint32_t c = problems[i]->closed;
-    if (c != kClosedNone && closed_pays(*problems[i], walked[c])) kind[size_t(i)] = c;
+    if (c != kClosedNone && closed_pays(*problems[i], walked[c], all[c])) kind[size_t(i)] = c;
   }
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
     const int32_t a = replica_problem[x], b = replica_problem[y];

@@ -133,8 +133,15 @@ def test_closed_forms_where_they_gain(host_calls):
                      fan(24, [3] * 19 + [1] * 5),             # 2^19: 2 labels, 1 combination
                      fan(29, [3] * 24 + [1] * 5),             # 2^24: 5 labels, 1 combination
                      fan(28, [3] * 23 + [1, 1, 1, 1, 3]),     # 5 labels, 2 combinations
+                     fan(24, [3] * 20 + [1] * 4),             # 2^20: 2 labels, 1 combination
+                     fan(25, [3] * 20 + [1, 1, 1, 1, 7]),     # 3 labels, 3 combinations
                      fan(28, [3] * 22 + [1, 1, 7, 1, 1, 1]),  # 4 labels, 3 combinations
                      fan(29, [3] * 24 + [1] * 5, "chain"))
-    assert got == ["3 5", "2 0", "0 0", "0 0", "4 5", "5 5"]
-    # work enough for two labels only, which need hold no more than one
+    assert got == ["3 5", "2 0", "0 0", "0 0", "0 0", "3 5", "4 5", "5 5"]
+    # work for two labels in all, which need hold no more than one combination
     assert host_calls("closed", fan(24, [3] * 19 + [1] * 5), fan(10, [7] * 10)) == ["2 2", "0 2"]
+    # more work, too little of it in fan-outs that gain
+    assert host_calls("closed", fan(29, [3] * 24 + [1] * 5), fan(10, [7] * 10)) == ["0 0", "0 0"]
+    # three labels' work, of which two gain from it
+    assert host_calls("closed", fan(25, [3] * 20 + [1, 1, 1, 1, 7]), fan(13, [7] * 11 + [1, 3]),
+                      fan(15, [3] * 12 + [1] * 3)) == ["3 3", "2 3", "0 0"]
