@@ -601,12 +601,20 @@ int split_range(const sched_problem& p, uint64_t lo, uint64_t hi, Part* out) {
 // range has lanes enough left to fill the GPU with kSharedInner inner digits
 // (the rule of a full search).  Below that, one mapping per lane in index
 // order is the shorter chain.  145 M of 3^19 mappings (mixed DAG): 3.97 ms in parts,
-// 19.9 ms in index order.
+// 19.9 ms in index order.  Without edges every tool is read in the first pass:
+// a prefix then shares next to nothing, and parts gain only by their rounds,
+// from three times as many lanes on (16 tools: 5e6 to 1.2e7 mappings take up to
+// 1.2 times as long in parts, 1.5e7 0.78 times), and with two modes per tool never
+// (24 tools, 1.4e7 mappings: 771 us in parts, 605 in index order).
 bool range_in_parts(const sched_problem& p, uint64_t lo, uint64_t hi) {
   if (p.n >= kCompactSnapN || !prefix_able(p, p.n)) return false;
   uint64_t inner = 1;
   for (uint32_t j = 0; j < kSharedInner; ++j) inner *= 3;
-  return (hi - lo) / inner >= kTargetLanes && parts_words(p) <= kStageWords;
+  bool edges = false, three = false;
+  for (const auto& pl : p.preds) edges = edges || !pl.empty();
+  for (uint8_t r : p.radix) three = three || r == 3;
+  if (!edges && !three) return false;
+  return (hi - lo) / inner >= (edges ? 1 : 3) * kTargetLanes && parts_words(p) <= kStageWords;
 }
 
 // Enumeration order of a part: its free tools deepest first, then the tools
@@ -1157,6 +1165,9 @@ void plan_batch(const sched_problem* const* problems, int32_t n_problems,
   // problems that gain from it have work enough (0: none).
   std::vector<uint32_t> replicas(size_t(n_problems), 0u), kind(size_t(n_problems), kClosedNone);
   for (size_t r = 0; r < R; ++r) ++replicas[size_t(replica_problem[r])];
+  unsigned __int128 all[3] = {};  // mappings of each kind
+  for (int32_t i = 0; i < n_problems; ++i)
+    all[problems[i]->closed] += (unsigned __int128)problems[i]->n_mappings * replicas[size_t(i)];
   uint32_t walked[3] = {};
   for (uint32_t c : {uint32_t(kClosedChain), uint32_t(kClosedFanout)})
     for (uint32_t j = kClosedInner; j > 0 && walked[c] == 0; --j) {
@@ -1165,9 +1176,6 @@ void plan_batch(const sched_problem* const* problems, int32_t n_problems,
         if (problems[i]->closed == c && closed_pays(*problems[i], j, all[c]))
           work += (unsigned __int128)problems[i]->n_mappings * replicas[size_t(i)];
       if (work > 0 && closed_inner(c, work) >= j) walked[c] = j;
-  unsigned __int128 all[3] = {};  // mappings of each kind
-  for (int32_t i = 0; i < n_problems; ++i)
-    all[problems[i]->closed] += (unsigned __int128)problems[i]->n_mappings * replicas[size_t(i)];
     }
   for (int32_t i = 0; i < n_problems; ++i) {
     const uint32_t c = problems[i]->closed;

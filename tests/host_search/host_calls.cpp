@@ -649,6 +649,18 @@ static void check_closed() {
   }
 }
 
+// From how many mappings on a range of each problem goes in parts (0: never).
+static void check_parts() {
+  while (const sched_problem* p = read_problem()) {
+    uint64_t lo = 0, hi = p->n_mappings;
+    if (range_in_parts(*p, 0, hi))
+      while (hi - lo > 1) (range_in_parts(*p, 0, lo + (hi - lo) / 2) ? hi : lo) = lo + (hi - lo) / 2;
+    else
+      hi = 0;
+    printf("%llu\n", (unsigned long long)hi);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string what = argc > 1 ? argv[1] : "";
   if (what == "stack") check_stack();
@@ -658,6 +670,7 @@ int main(int argc, char** argv) {
   else if (what == "blocks") check_blocks();
   else if (what == "room") check_room();
   else if (what == "closed") check_closed();
+  else if (what == "parts") check_parts();
   else if (what == "children") check_children(true);
   else if (what == "children at once") check_children(false);
   else return 2;

@@ -145,3 +145,16 @@ def test_closed_forms_where_they_gain(host_calls):
     # three labels' work, of which two gain from it
     assert host_calls("closed", fan(25, [3] * 20 + [1, 1, 1, 1, 7]), fan(13, [7] * 11 + [1, 3]),
                       fan(15, [3] * 12 + [1] * 3)) == ["3 3", "2 3", "0 0"]
+
+
+def test_ranges_in_parts_where_they_gain(host_calls):
+    """Problems without edges need three times as many mappings, and a tool of
+    three modes."""
+    def tight(n, shape, allowed):
+        return synth.random_instance(10000 + n, n, shape, tight=True), allowed, False
+
+    lanes = 9 << 19
+    assert host_calls("parts", tight(16, "random", [7] * 16), tight(24, "random", [3] * 24),
+                      tight(16, "fanout", [7] * 16), tight(24, "fanout", [3] * 23 + [7]),
+                      tight(24, "fanout", [3] * 24), tight(14, "fanout", [7] * 14)) == \
+        [str(lanes), str(lanes), str(3 * lanes), str(3 * lanes), "0", "0"]
