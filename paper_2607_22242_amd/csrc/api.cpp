@@ -1512,6 +1512,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
       g.a.n_blocks = blocks;
     }
 
+    std::vector<DevResult> res(R);  // (nothing is allocated from the copy to the wait)
     HIP_TRY(hipMemcpyAsync(d_tables, host.data(), host.size() * 4, hipMemcpyHostToDevice, s));
     std::optional<Slot> slot;
     if (R * sizeof(DevResult) <= kSlotBytes) slot.emplace(s);
@@ -1529,7 +1530,6 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
       HIP_TRY(launch_search(g.lay, a, s));
       d_first += g.last - g.first + 1;
     }
-    std::vector<DevResult> res(R);
     if (!h)
       HIP_TRY(hipMemcpyAsync(res.data(), results, R * sizeof(DevResult), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));

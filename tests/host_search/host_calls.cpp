@@ -35,20 +35,23 @@ static std::atomic<int> g_fail_page_locked{0};  // calls that will fail
 static bool g_plan_only = false;              // launches score nothing
 static uint32_t g_most_blocks = 65536;        // partials that a workspace has room for
 static thread_local long t_news = 0;          // heap allocations of this thread
+static thread_local long t_last_news = -1;    // those after this number fail (-1: none)
 
 static void enqueue(hipStream_t s, std::function<void()> f) {
   std::lock_guard<std::mutex> lock(g_mutex);
   g_work[s].push_back(std::move(f));
 }
 
+static void* allocate(size_t n) {
+  return ++t_news > t_last_news && t_last_news >= 0 ? nullptr : malloc(n);
+}
 void* operator new(size_t n) {
-  ++t_news;
-  if (void* p = malloc(n)) return p;
+  if (void* p = allocate(n)) return p;
   throw std::bad_alloc();
 }
 void* operator new[](size_t n) { return operator new(n); }
-void* operator new(size_t n, const std::nothrow_t&) noexcept { ++t_news; return malloc(n); }
-void* operator new[](size_t n, const std::nothrow_t&) noexcept { ++t_news; return malloc(n); }
+void* operator new(size_t n, const std::nothrow_t&) noexcept { return allocate(n); }
+void* operator new[](size_t n, const std::nothrow_t&) noexcept { return allocate(n); }
 void operator delete(void* p) noexcept { free(p); }
 void operator delete[](void* p) noexcept { free(p); }
 void operator delete(void* p, size_t) noexcept { free(p); }
@@ -56,8 +59,12 @@ void operator delete[](void* p, size_t) noexcept { free(p); }
 
 // The stand-in's own allocations are not the library's.
 struct Uncounted {
-  long at = t_news;
-  ~Uncounted() { t_news = at; }
+  long at = t_news, last = t_last_news;
+  Uncounted() { t_last_news = -1; }
+  ~Uncounted() {
+    t_news = at;
+    t_last_news = last;
+  }
 };
 
 extern "C" {
@@ -463,6 +470,55 @@ static Answers call_all(const std::vector<sched_problem*>& ps, int replicas, hip
   return out;
 }
 
+// Every allocation of every call fails in turn: the call says so, and nothing
+// is left in its stream (which would go on in memory that is no longer there).
+static void check_allocations() {
+  std::vector<sched_problem*> ps;
+  while (sched_problem* p = read_problem()) ps.push_back(p);
+  CHECK(ps.size() >= 2);
+  sched_problem* const big = ps.back();  // (the others are small)
+  ps.pop_back();
+  g_plan_only = true;
+  const int R = 2100;  // (more results than a slot holds)
+  size_t pruned = 0;
+  CHECK(sched_pruned_workspace_bytes(big, &pruned) == SCHED_OK);
+  Workspace ws(std::max({bytes_for(ps, R), bytes_for({big}, 0), pruned}));
+  std::vector<int32_t> of;
+  std::vector<sched_lat> lat;
+  for (int r = 0; r < R; ++r) {
+    of.push_back(int32_t(size_t(r) % ps.size()));
+    for (const sched_tool& t : ps[size_t(r) % ps.size()]->tools)
+      lat.push_back({t.gpu_us, t.cpu_us, t.load_us, t.xfer_us});
+  }
+  std::vector<sched_result> res(size_t(R), sched_result{7, 7});
+  std::vector<sched_probe> pr(size_t(1 + 2 * big->n + big->n * (big->n - 1)));
+  std::vector<uint64_t> idx(3000, 1);
+  std::vector<int64_t> ms(3000);
+  int32_t n = 0;
+  const std::vector<std::function<int()>> calls = {
+      [&] { return sched_bruteforce_argmin(big, 0, big->n_mappings, ws.p, ws.bytes, nullptr, res.data()); },
+      [&] { return sched_bruteforce_argmin(big, 1, big->n_mappings, ws.p, ws.bytes, nullptr, res.data()); },
+      [&] { return sched_eval_mappings(big, idx.data(), 3000, ws.p, ws.bytes, nullptr, ms.data()); },
+      [&] { return sched_eval_reprobes(big, 0, nullptr, ws.p, ws.bytes, nullptr, pr.data(),
+                                       int32_t(pr.size()), &n); },
+      [&] { return sched_eval_batch(ps.data(), int(ps.size()), of.data(), lat.data(), 3, ws.p, ws.bytes,
+                                    nullptr, res.data()); },
+      [&] { return sched_eval_batch(ps.data(), int(ps.size()), of.data(), lat.data(), R, ws.p, ws.bytes,
+                                    nullptr, res.data()); }};
+  for (const auto& call : calls) {
+    int rc = SCHED_E_NOMEM;
+    for (long k = 0; rc != SCHED_OK; ++k) {
+      res[0] = sched_result{7, 7};
+      t_last_news = t_news + k;
+      rc = call();
+      t_last_news = -1;
+      CHECK(rc == SCHED_OK || (rc == SCHED_E_NOMEM && res[0].best_index == 7));
+      CHECK(g_work[nullptr].empty());
+      CHECK(g_slots_taken == 0);
+    }
+  }
+}
+
 static void check_slots() {
   std::vector<sched_problem*> ps;
   while (sched_problem* p = read_problem()) ps.push_back(p);
@@ -670,6 +726,7 @@ int main(int argc, char** argv) {
   else if (what == "blocks") check_blocks();
   else if (what == "room") check_room();
   else if (what == "closed") check_closed();
+  else if (what == "allocations") check_allocations();
   else if (what == "parts") check_parts();
   else if (what == "children") check_children(true);
   else if (what == "children at once") check_children(false);

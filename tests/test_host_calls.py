@@ -158,3 +158,8 @@ def test_ranges_in_parts_where_they_gain(host_calls):
                       tight(16, "fanout", [7] * 16), tight(24, "fanout", [3] * 23 + [7]),
                       tight(24, "fanout", [3] * 24), tight(14, "fanout", [7] * 14)) == \
         [str(lanes), str(lanes), str(3 * lanes), str(3 * lanes), "0", "0"]
+
+
+def test_failed_allocations(host_calls):
+    big = synth.random_instance(9945, 15, "random", tight=True, small_values=True)
+    host_calls("allocations", *small_problems(), (big, None, False))
