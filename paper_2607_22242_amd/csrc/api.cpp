@@ -1659,7 +1659,12 @@ int sched_eval_reprobes(const sched_problem* p, uint64_t base_index, const sched
 int sched_pruned_workspace_bytes(const sched_problem* p, size_t* out) {
   if (p == nullptr || out == nullptr) return SCHED_E_NULL;
   size_t need = one_search_bytes(*p);
-  if (p->n_mappings >= kPruneMinSpace) need = std::max(need, prune_layout(*p, plan_prune(*p), SIZE_MAX).total);
+  try {
+    if (p->n_mappings >= kPruneMinSpace)
+      need = std::max(need, prune_layout(*p, plan_prune(*p), SIZE_MAX).total);
+  } catch (const std::bad_alloc&) {
+    return SCHED_E_NOMEM;
+  }
   *out = need;
   return SCHED_OK;
 }
@@ -1685,7 +1690,12 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
     return rc;
   }
   const int n = p->n;
-  const PrunePlan pl = plan_prune(*p);
+  PrunePlan pl;
+  try {
+    pl = plan_prune(*p);
+  } catch (const std::bad_alloc&) {
+    return SCHED_E_NOMEM;
+  }
   const PruneLayout L = prune_layout(*p, pl, ws_bytes);
   int rc = check_workspace(d_workspace, ws_bytes, L.total);
   if (rc != SCHED_OK) return rc;

@@ -504,7 +504,9 @@ static void check_allocations() {
       [&] { return sched_eval_batch(ps.data(), int(ps.size()), of.data(), lat.data(), 3, ws.p, ws.bytes,
                                     nullptr, res.data()); },
       [&] { return sched_eval_batch(ps.data(), int(ps.size()), of.data(), lat.data(), R, ws.p, ws.bytes,
-                                    nullptr, res.data()); }};
+                                    nullptr, res.data()); },
+      [&] { return sched_pruned_argmin(big, ws.p, ws.bytes, nullptr, res.data(), nullptr); },
+      [&] { return sched_pruned_workspace_bytes(big, &pruned); }};
   for (const auto& call : calls) {
     int rc = SCHED_E_NOMEM;
     for (long k = 0; rc != SCHED_OK; ++k) {
