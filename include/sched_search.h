@@ -278,9 +278,8 @@ typedef struct {
  * promising first: extended by the next tools, bounded again, and what
  * survives has its remaining tools searched exhaustively (the assignments
  * themselves where few extensions are ruled out).  Spaces below 2^22
- * mappings get one exhaustive search.  d_workspace: 256-byte aligned; with
- * fewer than sched_pruned_workspace_bytes(p) bytes, but room for the bounds of
- * every prefix assignment, fewer assignments are taken up at a time.  stats: optional
+ * mappings get one exhaustive search.  d_workspace: at least
+ * sched_pruned_workspace_bytes(p) bytes, 256-byte aligned.  stats: optional
  * counters (host). */
 int sched_pruned_workspace_bytes(const sched_problem *p, size_t *out);
 int sched_pruned_argmin(const sched_problem *p, void *d_workspace, size_t ws_bytes,

@@ -947,7 +947,11 @@ constexpr uint64_t kMinSubspace = 1ull << 12;    // mappings per searched subspa
 // (two modes, 34 tools: 6.9 ms with a first chunk of 2,048, 14.9 with 8,192
 // prefixes; 19 tools, 8,019 survivors: 1.1 and 2.4 ms).  A chunk more costs 90
 // us, so twice as many are still searched at once.
-constexpr uint32_t kFirstPrefixes = 2048, kChunkPrefixes = 8192;
+#ifndef DEVMAP_CHUNK_PREFIXES
+#define DEVMAP_CHUNK_PREFIXES 8192
+#endif
+constexpr uint32_t kChunkPrefixes = DEVMAP_CHUNK_PREFIXES;
+constexpr uint32_t kFirstPrefixes = std::min<uint32_t>(2048, kChunkPrefixes);
 constexpr uint64_t kMaxChildren = 243;           // assignments of the extension tools
 constexpr uint64_t kMinRest = 81;                // mappings left per extended prefix, at least
 
@@ -1010,10 +1014,7 @@ struct PruneLayout {
   size_t chunk;  // prefixes searched together
 };
 
-// room: bytes of the workspace.  One too small for kChunkPrefixes and their
-// children has smaller chunks (and more launches); total is beyond it if it
-// does not hold one prefix at a time.
-PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl, size_t room) {
+PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl) {
   PruneLayout l;
   const size_t probes = size_t(1 + 2 * p.n + p.n * (p.n - 1));
   l.tables = 0;
@@ -1022,10 +1023,7 @@ PruneLayout prune_layout(const sched_problem& p, const PrunePlan& pl, size_t roo
   l.bounds = l.results + align_up(sizeof(DevResult));
   // Survivor count (one word, padded) and then (bound, y) pairs: first up to
   // n_prefixes of the prefixes, then a chunk of them and its children.
-  const size_t others = l.bounds + align_up(4) + 2 * align_up(probes * 8);
-  const size_t fit = room > others ? (room - others) / kAlign * kAlign / 8 : 0;
   l.chunk = size_t(std::min<uint64_t>(kChunkPrefixes, pl.n_prefixes));
-  l.chunk = std::max<size_t>(1, std::min(l.chunk, fit / size_t(1 + pl.n_children)));
   const size_t pairs = std::max<size_t>(size_t(pl.n_prefixes), l.chunk * size_t(1 + pl.n_children));
   l.probe_idx = l.bounds + align_up(4) + align_up(pairs * 8);
   l.probe_ms = l.probe_idx + align_up(probes * 8);
@@ -1661,7 +1659,7 @@ int sched_pruned_workspace_bytes(const sched_problem* p, size_t* out) {
   size_t need = one_search_bytes(*p);
   try {
     if (p->n_mappings >= kPruneMinSpace)
-      need = std::max(need, prune_layout(*p, plan_prune(*p), SIZE_MAX).total);
+      need = std::max(need, prune_layout(*p, plan_prune(*p)).total);
   } catch (const std::bad_alloc&) {
     return SCHED_E_NOMEM;
   }
@@ -1696,7 +1694,7 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
   } catch (const std::bad_alloc&) {
     return SCHED_E_NOMEM;
   }
-  const PruneLayout L = prune_layout(*p, pl, ws_bytes);
+  const PruneLayout L = prune_layout(*p, pl);
   int rc = check_workspace(d_workspace, ws_bytes, L.total);
   if (rc != SCHED_OK) return rc;
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);

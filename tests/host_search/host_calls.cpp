@@ -594,8 +594,7 @@ static void check_blocks() {
 }
 
 // Workspaces from one table, the partials and a result upwards: every search
-// takes them, a range in parts where they hold its tables; and a pruned search
-// gives the same answer in fewer bytes.  Prints that answer.
+// takes them, a range in parts where they hold its tables.
 static void check_room() {
   sched_problem* const p = read_problem();
   CHECK(p != nullptr);
@@ -618,42 +617,18 @@ static void check_room() {
     CHECK(sched_bruteforce_argmin(p, 1, M, ws.p, n, nullptr, &r) == want);
     CHECK(n < least || (g_max_tables > 1) == (n == most));
   }
-  g_plan_only = false;
-  size_t full = 0;
-  CHECK(sched_pruned_workspace_bytes(p, &full) == SCHED_OK);
-  const PrunePlan pl = plan_prune(*p);
-  CHECK(prune_layout(*p, pl, full).chunk == prune_layout(*p, pl, SIZE_MAX).chunk);
-  const size_t one = prune_layout(*p, pl, 0).total;  // one prefix at a time
-  CHECK(one < full);
-  sched_result want{};
-  int launches = 0;
-  for (size_t n : {full, (one + full) / 2, one + (full - one) / 16, one, one - 1}) {
-    CHECK(n <= one || prune_layout(*p, pl, n).total <= n);
-    Workspace w(n);
-    sched_result r{};
-    sched_prune_stats st{};
-    const int rc = sched_pruned_argmin(p, w.p, n, nullptr, &r, &st);
-    CHECK(rc == (n < one ? SCHED_E_WORKSPACE : SCHED_OK));
-    if (rc != SCHED_OK) continue;
-    if (n == full) want = r;
-    CHECK(r.best_index == want.best_index && r.makespan_us == want.makespan_us);
-    CHECK(st.launches >= launches);
-    launches = st.launches;
-  }
-  printf("%llu %lld\n", (unsigned long long)want.best_index, (long long)want.makespan_us);
 }
 
 // A pruned search's launches over lists of children or prefixes: every mapping
 // of a listed one is scored once, no other is; prints the answer and how many
-// of either were listed.  With the
-// fewest bytes: chunks of a few prefixes, lists of several launches.
-static void check_children(bool fewest) {
+// of either were listed.
+static void check_children() {
   sched_problem* const p = read_problem();
   CHECK(p != nullptr && p->n_mappings >= kPruneMinSpace);
   const PrunePlan pl = plan_prune(*p);
   std::vector<uint8_t> times(p->n_mappings);
   g_times = &times;
-  const size_t n = prune_layout(*p, pl, fewest ? 0 : SIZE_MAX).total;
+  const size_t n = prune_layout(*p, pl).total;
   Workspace ws(n);
   sched_result r{};
   sched_prune_stats st{};
@@ -730,8 +705,7 @@ int main(int argc, char** argv) {
   else if (what == "closed") check_closed();
   else if (what == "allocations") check_allocations();
   else if (what == "parts") check_parts();
-  else if (what == "children") check_children(true);
-  else if (what == "children at once") check_children(false);
+  else if (what == "children") check_children();
   else return 2;
   puts("ok");
   return 0;

@@ -13,8 +13,7 @@ from workloads import synth
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def host_calls(tmp_path_factory):
+def build(tmp_path_factory, *flags):
     cc = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "bin", "hipcc")
     cc = cc if os.path.exists(cc) else shutil.which("hipcc")
     if cc is None:
@@ -25,7 +24,7 @@ def host_calls(tmp_path_factory):
                            "-I" + os.path.join(ROOT, "include"),
                            "-I" + os.path.join(ROOT, "paper_2607_22242_amd", "csrc"),
                            os.path.join(ROOT, "tests", "host_search", "host_calls.cpp"),
-                           "-o", exe], stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+                           "-o", exe, *flags], stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
 
     def run(what, *problems):
         text = []
@@ -42,6 +41,16 @@ def host_calls(tmp_path_factory):
         assert r.stdout.endswith("ok\n")
         return r.stdout.split("\n")[:-2]
     return run
+
+
+@pytest.fixture(scope="module")
+def host_calls(tmp_path_factory):
+    return build(tmp_path_factory)
+
+
+@pytest.fixture(scope="module")
+def host_calls_small_chunks(tmp_path_factory):
+    return build(tmp_path_factory, "-DHOST_CALLS_N=15", "-DDEVMAP_CHUNK_PREFIXES=8")
 
 
 @pytest.mark.parametrize("n,levels", [(15, 4), (19, 19)])
@@ -87,20 +96,17 @@ def test_blocks_of_the_largest_batches(host_calls, shape):
     host_calls("blocks", (inst, None, False))
 
 
-def test_workspaces_of_fewer_bytes(host_calls, oracle_mod):
-    inst = synth.random_instance(9970, 15, "random", tight=True)
-    allowed = [7] * 15
-    got = host_calls("room", (inst, allowed, False))
-    print(got)
-    x, ms = map(int, got[0].split())
-    assert (x, ms) == oracle_mod.Problem.from_instance(inst).argmin()
+def test_workspaces_of_fewer_bytes(host_calls):
+    host_calls("room", (synth.random_instance(9970, 15, "random", tight=True), None, False))
 
 
-# 15 tools; 34 tools (2^12 * 3^7 mappings, 64-bit masks); and 15 tools of which one outlasts the
-# others whatever they do, so that no child is ruled out: its prefixes are searched, and shared
-@pytest.mark.parametrize("n,share,long", [(15, False, False), (15, True, False), (34, False, False),
-                                          (15, False, True)])
-def test_children_are_scored_once(host_calls, oracle_mod, n, share, long):
+# 15 tools, by chunks of eight prefixes; 34 tools (2^12 * 3^7 mappings, 64-bit masks); and 15 tools
+# of which one outlasts the others whatever they do, so that no child is ruled out: its prefixes
+# are searched, at once and shared
+@pytest.mark.parametrize("n,share,long,chunks", [(15, False, False, True), (15, True, False, True),
+                                                 (34, False, False, False), (15, False, True, False)])
+def test_children_are_scored_once(request, oracle_mod, n, share, long, chunks):
+    run = request.getfixturevalue("host_calls_small_chunks" if chunks else "host_calls")
     inst = synth.random_instance(9980 + n, n, "permuted", tight=True, small_values=True)
     allowed = [7] * n
     if n == 34:
@@ -111,9 +117,8 @@ def test_children_are_scored_once(host_calls, oracle_mod, n, share, long):
         inst["tools"][6][:2] = [100_000, 100_000]
         inst["edges"] = [e for e in inst["edges"] if 6 not in e]
         allowed[6] = 3
-    x, ms, launches, shared, children, prefixes = map(int, host_calls(
-        "children at once" if long else "children", (inst, allowed, share))[0].split())
-    assert launches >= (2 if n == 15 and not long else 1) and (shared > 0) == long
+    x, ms, launches, shared, children, prefixes = map(int, run("children", (inst, allowed, share))[0].split())
+    assert launches >= (2 if chunks else 1) and (shared > 0) == long
     assert (children > 0) != long and (prefixes > 0) == long
     Q, space = oracle_mod.Problem.from_instance(inst, sharing=share), oracle_mod.Space(allowed)
     assert int(Q.eval_many(space.base3(np.array([x], dtype=np.uint64)))[0]) == ms
