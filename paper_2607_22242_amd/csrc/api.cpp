@@ -806,6 +806,24 @@ int create_problem(const sched_tool* tools, int32_t n_tools, const sched_edge* e
     if ((expr) != hipSuccess) return SCHED_E_DEVICE;   \
   } while (0)
 
+// Waits for a call's stream where an error leaves the call before its own wait:
+// what the stream has been given may still read host memory of the call.
+class StreamWait {
+ public:
+  explicit StreamWait(hipStream_t s) : stream_(s) {}
+  StreamWait(const StreamWait&) = delete;
+  StreamWait& operator=(const StreamWait&) = delete;
+  ~StreamWait() {
+    if (!waited_) (void)hipStreamSynchronize(stream_);
+  }
+  // The stream has been waited for, or has been given nothing.
+  void waited() { waited_ = true; }
+
+ private:
+  hipStream_t stream_;
+  bool waited_ = false;
+};
+
 // Page-locked host memory that kernels read and write directly, so that a
 // small call needs no copies: its indices and its results (or its blocks'
 // partial minima) cross the link as part of the kernel.  One allocation of
@@ -870,6 +888,7 @@ int score(const sched_problem& p, const uint32_t* table, const uint64_t* idx, si
           int64_t* ms, uint32_t* d_tab, uint64_t* d_idx, int64_t* d_ms, hipStream_t s) {
   uint32_t flags = p.sharing ? kEvalSharing : 0u;
   const uint32_t* tab = table;
+  StreamWait wait(s);
   if (fits_arguments(table)) {
     flags |= kEvalHostTable;
   } else {
@@ -886,6 +905,7 @@ int score(const sched_problem& p, const uint32_t* table, const uint64_t* idx, si
                           h_ms, flags, s));
       HIP_TRY(hipStreamSynchronize(s));
       slot.waited();
+      wait.waited();
       std::memcpy(ms, h_ms, m * 8);
       return SCHED_OK;
     }
@@ -894,6 +914,7 @@ int score(const sched_problem& p, const uint32_t* table, const uint64_t* idx, si
   HIP_TRY(launch_eval(p.n, tab, d_idx, int64_t(m), p.n_mappings, d_ms, flags, s));
   HIP_TRY(hipMemcpyAsync(ms, d_ms, m * 8, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
+  wait.waited();
   return SCHED_OK;
 }
 
@@ -1109,11 +1130,12 @@ int search_parts(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, hip
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
   a.results = reinterpret_cast<DevResult*>(ws + L.results);
   DevResult r;
-  hipError_t e = hipMemcpyAsync(ws + L.tables, stage, words * 4, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = launch_search(p.n, a, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s);
-  HIP_TRY(hipStreamSynchronize(s));  // (after an error too: the copy may still read the stage)
-  HIP_TRY(e);
+  StreamWait wait(s);
+  HIP_TRY(hipMemcpyAsync(ws + L.tables, stage, words * 4, hipMemcpyHostToDevice, s));
+  HIP_TRY(launch_search(p.n, a, s));
+  HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  wait.waited();
   h_out->best_index = r.index;
   h_out->makespan_us = r.makespan;
   return SCHED_OK;
@@ -1280,6 +1302,8 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, size_
   a.partials = reinterpret_cast<Partial*>(ws + L.partials);
   a.results = reinterpret_cast<DevResult*>(ws + L.results);
   a.record = record;
+  DevResult r;
+  StreamWait wait(s);
   if (fits_arguments(table.data())) {
     a.host_table = table.data();
     a.host_words = bound_base(uint32_t(p.n), a.lds_levels);
@@ -1288,7 +1312,6 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, size_
     HIP_TRY(hipMemcpyAsync(ws + L.tables, table.data(), size_t(p.table_words) * 4,
                            hipMemcpyHostToDevice, s));
   }
-  DevResult r;
   std::optional<Slot> slot;
   if (stage == nullptr) slot.emplace(s);
   char* const h = slot ? slot->data() : nullptr;
@@ -1304,6 +1327,7 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, size_
     HIP_TRY(launch_search(p.n, a, s));
     HIP_TRY(hipStreamSynchronize(s));
     slot->waited();
+    wait.waited();
     if (small) {
       const Partial* const part = reinterpret_cast<const Partial*>(h);
       uint32_t ms = kInf;
@@ -1322,6 +1346,7 @@ int search_one(const sched_problem& p, uint64_t lo, uint64_t hi, char* ws, size_
     HIP_TRY(launch_search(p.n, a, s));
     HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    wait.waited();
   }
   h_out->best_index = r.index;
   h_out->makespan_us = r.makespan;
@@ -1511,6 +1536,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     }
 
     std::vector<DevResult> res(R);  // (nothing is allocated from the copy to the wait)
+    StreamWait wait(s);
     HIP_TRY(hipMemcpyAsync(d_tables, host.data(), host.size() * 4, hipMemcpyHostToDevice, s));
     std::optional<Slot> slot;
     if (R * sizeof(DevResult) <= kSlotBytes) slot.emplace(s);
@@ -1531,6 +1557,7 @@ int sched_eval_batch(const sched_problem* const* problems, int32_t n_problems,
     if (!h)
       HIP_TRY(hipMemcpyAsync(res.data(), results, R * sizeof(DevResult), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    wait.waited();
     if (h) {
       slot->waited();
       std::memcpy(res.data(), h, R * sizeof(DevResult));
@@ -1558,6 +1585,7 @@ int sched_eval_mappings_device(const sched_problem* p, const uint64_t* d_idx, in
   hipStream_t s = reinterpret_cast<hipStream_t>(hip_stream);
   uint32_t flags = p->sharing ? kEvalSharing : 0u;
   const uint32_t* tab = p->table.data();
+  StreamWait wait(s);
   if (fits_arguments(tab)) {
     flags |= kEvalHostTable;
   } else {
@@ -1566,6 +1594,7 @@ int sched_eval_mappings_device(const sched_problem* p, const uint64_t* d_idx, in
   }
   HIP_TRY(launch_eval(p->n, tab, d_idx, n, p->n_mappings, d_makespan, flags, s));
   HIP_TRY(hipStreamSynchronize(s));
+  wait.waited();
   return SCHED_OK;
 }
 
@@ -1744,22 +1773,30 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
     for (int32_t v : pl.prefix) known |= 1ull << p->table[pos_base(uint32_t(n)) + uint32_t(v)];
     for (int v = 0; v < n; ++v)
       if (p->radix[v] == 1) known |= 1ull << p->table[pos_base(uint32_t(n)) + uint32_t(v)];
-    HIP_TRY(hipMemcpyAsync(ws + L.tables, btab.data(), size_t(stride) * 4, hipMemcpyHostToDevice,
-                           s));
     uint32_t* d_count = reinterpret_cast<uint32_t*>(ws + L.bounds);
     uint2* d_live = reinterpret_cast<uint2*>(ws + L.bounds + align_up(4));
     const uint32_t ub32 = ub_ms == INT64_MAX ? kInf - 1 : uint32_t(ub_ms);
-    HIP_TRY(hipMemsetAsync(d_count, 0, 4, s));
-    HIP_TRY(launch_bound(n, d_tab, uint32_t(pl.prefix.size()), known, int64_t(pl.n_prefixes), ub32,
-                         d_count, d_live, s));
+    // Bounds of m assignments by btab, of at most `bound`, to out; *live: how many.
+    const auto bounds = [&](size_t tools, int64_t m, uint32_t bound, uint2* out, uint32_t* live) {
+      StreamWait wait(s);
+      HIP_TRY(hipMemcpyAsync(ws + L.tables, btab.data(), size_t(stride) * 4, hipMemcpyHostToDevice,
+                             s));
+      HIP_TRY(hipMemsetAsync(d_count, 0, 4, s));
+      HIP_TRY(launch_bound(n, d_tab, uint32_t(tools), known, m, bound, d_count, out, s));
+      HIP_TRY(hipMemcpyAsync(live, d_count, 4, hipMemcpyDeviceToHost, s));
+      HIP_TRY(hipStreamSynchronize(s));
+      wait.waited();
+      return int64_t(*live) > m ? SCHED_E_DEVICE : SCHED_OK;
+    };
     uint32_t n_live = 0;
-    HIP_TRY(hipMemcpyAsync(&n_live, d_count, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (n_live > pl.n_prefixes) return SCHED_E_DEVICE;
+    rc = bounds(pl.prefix.size(), int64_t(pl.n_prefixes), ub32, d_live, &n_live);
+    if (rc != SCHED_OK) return rc;
     std::vector<uint2> raw(n_live);
     if (n_live) {
+      StreamWait wait(s);
       HIP_TRY(hipMemcpyAsync(raw.data(), d_live, size_t(n_live) * 8, hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
+      wait.waited();
     }
     st.prefixes = pl.n_prefixes;
     st.prefix_tools = int32_t(pl.prefix.size());
@@ -1824,18 +1861,17 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       }
       st.prefixes_searched += chunk.size();
       const int64_t candidates = int64_t(chunk.size() * pl.n_children);
-      HIP_TRY(hipMemcpyAsync(d_chunk, chunk.data(), chunk.size() * 8, hipMemcpyHostToDevice, s));
-      HIP_TRY(hipMemcpyAsync(ws + L.tables, btab.data(), size_t(stride) * 4, hipMemcpyHostToDevice,
-                             s));
-      HIP_TRY(hipMemsetAsync(d_count, 0, 4, s));
-      HIP_TRY(launch_bound(n, d_tab, uint32_t(both.size()), known, candidates,
-                           best_ms == INT64_MAX ? kInf - 1 : uint32_t(best_ms), d_count, d_children,
-                           s));
       uint32_t n_rest = 0;
-      HIP_TRY(hipMemcpyAsync(&n_rest, d_count, 4, hipMemcpyDeviceToHost, s));
-      HIP_TRY(hipStreamSynchronize(s));
-      if (n_rest == 0) continue;
-      if (int64_t(n_rest) > candidates) return SCHED_E_DEVICE;
+      DevResult r;
+      StreamWait wait(s);
+      HIP_TRY(hipMemcpyAsync(d_chunk, chunk.data(), chunk.size() * 8, hipMemcpyHostToDevice, s));
+      rc = bounds(both.size(), candidates, best_ms == INT64_MAX ? kInf - 1 : uint32_t(best_ms),
+                  d_children, &n_rest);
+      if (rc != SCHED_OK) return rc;
+      if (n_rest == 0) {
+        wait.waited();
+        continue;
+      }
       // Where their bounds rule out less than a quarter of the children, the
       // prefixes are searched themselves: a wave's lanes then share a prefix in
       // place of holding several children, which differ in tools that act
@@ -1877,9 +1913,9 @@ int sched_pruned_argmin(const sched_problem* p, void* d_workspace, size_t ws_byt
       a.partials = reinterpret_cast<Partial*>(ws + L.partials);
       a.results = reinterpret_cast<DevResult*>(ws + L.results);
       HIP_TRY(launch_search(n, a, s));
-      DevResult r;
       HIP_TRY(hipMemcpyAsync(&r, a.results, sizeof(r), hipMemcpyDeviceToHost, s));
       HIP_TRY(hipStreamSynchronize(s));
+      wait.waited();
       if (r.makespan < best_ms || (r.makespan == best_ms && r.index < best_x)) {
         best_ms = r.makespan;
         best_x = r.index;

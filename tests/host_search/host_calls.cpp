@@ -37,6 +37,11 @@ static uint32_t g_most_blocks = 65536;        // partials that a workspace has r
 static thread_local long t_news = 0;          // heap allocations of this thread
 static thread_local long t_last_news = -1;    // those after this number fail (-1: none)
 
+static long g_calls = 0;                      // copies, fills and launches asked for
+static long g_last_call = -1;                 // those after this number fail (-1: none)
+
+static bool refused() { return ++g_calls > g_last_call && g_last_call >= 0; }
+
 static void enqueue(hipStream_t s, std::function<void()> f) {
   std::lock_guard<std::mutex> lock(g_mutex);
   g_work[s].push_back(std::move(f));
@@ -79,11 +84,13 @@ hipError_t hipHostMalloc(void** p, size_t n, unsigned) {
 }
 hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind, hipStream_t st) {
   Uncounted u;
+  if (refused()) return hipErrorUnknown;
   enqueue(st, [=] { memcpy(d, s, n); });
   return hipSuccess;
 }
 hipError_t hipMemsetAsync(void* d, int v, size_t n, hipStream_t st) {
   Uncounted u;
+  if (refused()) return hipErrorUnknown;
   enqueue(st, [=] { memset(d, v, n); });
   return hipSuccess;
 }
@@ -228,6 +235,7 @@ using Built = std::integer_sequence<int, HOST_CALLS_N>;
 
 hipError_t launch_search(int n, const SearchArgs& args, hipStream_t s) {
   Uncounted u;
+  if (refused()) return hipErrorUnknown;
   std::vector<uint32_t> own;
   if (args.tables == nullptr) own.assign(args.host_table, args.host_table + args.host_words);
   ++g_launches;
@@ -269,6 +277,7 @@ hipError_t launch_search(int n, const SearchArgs& args, hipStream_t s) {
 hipError_t launch_eval(int n, const uint32_t* tab, const uint64_t* idx, int64_t m,
                        uint64_t n_mappings, int64_t* out, uint32_t flags, hipStream_t s) {
   Uncounted u;
+  if (refused()) return hipErrorUnknown;
   std::vector<uint32_t> own;
   if (flags & kEvalHostTable) own.assign(tab, tab + bound_base(uint32_t(n), tab[kHdrLevels]));
   enqueue(s, [=] {
@@ -282,6 +291,7 @@ hipError_t launch_eval(int n, const uint32_t* tab, const uint64_t* idx, int64_t 
 hipError_t launch_bound(int n, const uint32_t* tab, uint32_t K, uint64_t known, int64_t m,
                         uint32_t ub, uint32_t* count, uint2* out, hipStream_t s) {
   Uncounted u;
+  if (refused()) return hipErrorUnknown;
   enqueue(s, [=] {
     const uint2* const parents = list_at(Tab{tab}, kHdrParentLo);
     on_tools(n, [&](auto N) {
@@ -470,19 +480,23 @@ static Answers call_all(const std::vector<sched_problem*>& ps, int replicas, hip
   return out;
 }
 
-// Every allocation of every call fails in turn: the call says so, and nothing
-// is left in its stream (which would go on in memory that is no longer there).
-static void check_allocations() {
+// Every allocation of every call fails in turn (or every copy, fill and launch):
+// the call says so, and nothing is left in its stream (which would go on in
+// memory that is no longer there).
+static void check_failures(bool runtime) {
   std::vector<sched_problem*> ps;
   while (sched_problem* p = read_problem()) ps.push_back(p);
   CHECK(ps.size() >= 2);
+  sched_problem* const wide = ps.back();  // (a table too large for a kernel's arguments)
+  ps.pop_back();
   sched_problem* const big = ps.back();  // (the others are small)
   ps.pop_back();
+  CHECK(!fits_arguments(wide->table.data()));
   g_plan_only = true;
   const int R = 2100;  // (more results than a slot holds)
   size_t pruned = 0;
   CHECK(sched_pruned_workspace_bytes(big, &pruned) == SCHED_OK);
-  Workspace ws(std::max({bytes_for(ps, R), bytes_for({big}, 0), pruned}));
+  Workspace ws(std::max({bytes_for(ps, R), bytes_for({big}, 0), bytes_for({wide}, 0), pruned}));
   std::vector<int32_t> of;
   std::vector<sched_lat> lat;
   for (int r = 0; r < R; ++r) {
@@ -506,15 +520,20 @@ static void check_allocations() {
       [&] { return sched_eval_batch(ps.data(), int(ps.size()), of.data(), lat.data(), R, ws.p, ws.bytes,
                                     nullptr, res.data()); },
       [&] { return sched_pruned_argmin(big, ws.p, ws.bytes, nullptr, res.data(), nullptr); },
-      [&] { return sched_pruned_workspace_bytes(big, &pruned); }};
+      [&] { return sched_pruned_workspace_bytes(big, &pruned); },
+      [&] { return sched_bruteforce_argmin(wide, 0, 8, ws.p, ws.bytes, nullptr, res.data()); },
+      [&] { return sched_eval_mappings(wide, idx.data(), 3000, ws.p, ws.bytes, nullptr, ms.data()); },
+      [&] { return sched_eval_mappings_device(wide, idx.data(), 3000, ms.data(), ws.p, ws.bytes, nullptr); }};
+  const int failed = runtime ? SCHED_E_DEVICE : SCHED_E_NOMEM;
   for (const auto& call : calls) {
-    int rc = SCHED_E_NOMEM;
+    int rc = failed;
     for (long k = 0; rc != SCHED_OK; ++k) {
       res[0] = sched_result{7, 7};
-      t_last_news = t_news + k;
+      if (runtime) g_last_call = g_calls + k;
+      else t_last_news = t_news + k;
       rc = call();
-      t_last_news = -1;
-      CHECK(rc == SCHED_OK || (rc == SCHED_E_NOMEM && res[0].best_index == 7));
+      t_last_news = g_last_call = -1;
+      CHECK(rc == SCHED_OK || (rc == failed && res[0].best_index == 7));
       CHECK(g_work[nullptr].empty());
       CHECK(g_slots_taken == 0);
     }
@@ -703,7 +722,8 @@ int main(int argc, char** argv) {
   else if (what == "blocks") check_blocks();
   else if (what == "room") check_room();
   else if (what == "closed") check_closed();
-  else if (what == "allocations") check_allocations();
+  else if (what == "allocations") check_failures(false);
+  else if (what == "runtime") check_failures(true);
   else if (what == "parts") check_parts();
   else if (what == "children") check_children();
   else return 2;

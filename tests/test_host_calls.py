@@ -165,6 +165,8 @@ def test_ranges_in_parts_where_they_gain(host_calls):
         [str(lanes), str(lanes), str(3 * lanes), str(3 * lanes), "0", "0"]
 
 
-def test_failed_allocations(host_calls):
+@pytest.mark.parametrize("what", ["allocations", "runtime"])
+def test_failures(host_calls, what):
     big = synth.random_instance(9945, 15, "random", tight=True, small_values=True)
-    host_calls("allocations", *small_problems(), (big, None, False))
+    wide = synth.random_instance(9946, 34, "random", levels=34, small_values=True)
+    host_calls(what, *small_problems(), (big, None, False), (wide, [1] * 22 + [3] * 12, False))
